@@ -214,8 +214,8 @@ struct gc_graph {
   DevBuf c4_dense, c4_touch, c4_cur, c4_blk, c4_keys, c4_keys_alt, tri_scratch;
   // triangles at each vertex (kept for the edge-local passes) and the
   // scratch of those passes
-  DevBuf Tv, dTs, sbt, ce, ae, ae_alt, slot_list, dctr, c4_nch, c4_side, c4_off, pair_edge, pair_len, pair_off,
-      pair_merge, pair_hlen, pair_hoff, k4_s, k4_edge, k4_item, tv_items, tv_ioff;
+  DevBuf Tv, dTs, sbt, ce, ae, ae_alt, slot_list, dctr, c4_nch, c4_side, c4_low, c4_off, pair_edge, pair_idx, pair_len, pair_off,
+      pair_hlen, pair_hoff, k4_s, k4_edge, k4_item, tv_items, tv_ioff;
   int64_t ae_cap = 0, slot_cap = 0, pair_cap = 0;
   // largest affected-edge and 4-cycle-pair demand per update seen in an
   // edge-local pass: later passes size their lists for their batch capacity
@@ -267,6 +267,9 @@ struct gc_graph {
   // rows at least this long go through a whole wave in the per-vertex pass
   // (GC_DEG_WAVE_ROW overrides it: tests lower it to reach that path)
   int32_t deg_wave_row = 1 << 16;
+  // ids covered by the bitmaps of the edge-local 4-cycles, 0: the most
+  // (GC_DELTA_BITS lowers it: tests reach the ids below the window)
+  int32_t delta_bits = 0;
   double region_frac[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
   // counting attempts after the first when scratch proves too small
   // (GC_RETRY_LIMIT overrides it: tests set 0 to reach the failure path)
@@ -707,6 +710,7 @@ void* noalloc_scratch_ptr(int device) {
 void setup_handle(gc_graph* G, const gc_options* opt) {
   if (opt) G->opt = *opt; else gc_options_default(&G->opt);
   if (const char* e = std::getenv("GC_DEG_WAVE_ROW")) G->deg_wave_row = std::max(1, std::min(1 << 16, std::atoi(e)));
+  if (const char* e = std::getenv("GC_DELTA_BITS")) G->delta_bits = std::max(0, std::atoi(e));
   if (const char* e = std::getenv("GC_RETRY_LIMIT")) G->retry_limit = std::max(0, std::min(8, std::atoi(e)));
   if (G->opt.radius < 0 || G->opt.radius > 4) raise(GC_EINVAL, "radius must be in [0, 4]");
   if (!(G->opt.slack >= 0.0f && G->opt.slack <= 16.0f)) raise(GC_EINVAL, "slack must be in [0, 16]");
@@ -975,6 +979,11 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
   D.bits = G->bits;
   D.dirA = W.dirA;
   D.dirD = W.dirD;
+  D.dirR = W.dirR;
+  D.a_beg = W.a_beg;
+  D.na = W.na;
+  D.r_beg = W.r_beg;
+  D.nr = W.nr;
   D.c = G->ctr.as<unsigned long long>();
   D.touched = W.touched;
   D.mark = W.mark;
@@ -997,10 +1006,12 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
   D.dc = G->dctr.as<unsigned long long>();
   D.c4_nch = G->c4_nch.as<int32_t>();
   D.c4_side = G->c4_side.as<int32_t>();
+  D.c4_low = G->c4_low.as<int32_t>();
+  D.c4_ids = (uint32_t)G->delta_bits;
   D.c4_off = G->c4_off.as<int64_t>();
   D.pair_edge = G->pair_edge.as<int32_t>();
+  D.pair_idx = G->pair_idx.as<int32_t>();
   D.pair_len = G->pair_len.as<int32_t>();
-  D.pair_merge = G->pair_merge.as<int32_t>();
   D.k4_s = G->k4_s.as<uint32_t>();
   D.k4_edge = G->k4_edge.as<int64_t>();
   D.k4_item = G->k4_item.as<int32_t>();
@@ -1022,11 +1033,12 @@ void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t slot_need, 
   G->ce.ensure(ce_cap * 8);
   G->c4_nch.ensure(G->ce.cap / 8 * 4);
   G->c4_side.ensure(G->ce.cap / 8 * 4);
+  G->c4_low.ensure(G->ce.cap / 8 * 4);
   G->c4_off.ensure((G->ce.cap / 8 + 1) * 8);
   G->pair_cap = std::max<int64_t>(G->pair_cap, std::max<int64_t>(pair_need, 64 * cap_t + 4096));
   G->pair_edge.ensure(G->pair_cap * 4);
+  G->pair_idx.ensure(G->pair_cap * 4);
   G->pair_len.ensure(G->pair_cap * 4);
-  G->pair_merge.ensure(G->pair_cap * 4);
   G->pair_hlen.ensure(G->pair_cap * 4);
   G->pair_hoff.ensure((G->pair_cap + 1) * 8);
   G->k4_s.ensure(K4_HS_CAP * 4);
@@ -1226,7 +1238,7 @@ std::vector<uint64_t> pass_signature(gc_graph* G, const PassPlan& L, const Count
                           &G->tp, &G->vpos, &G->level, &G->rlist, &G->rlen, &G->lists, &G->c4_dense, &G->c4_touch,
                           &G->c4_cur, &G->c4_blk, &G->c4_keys, &G->c4_keys_alt, &G->tri_scratch, &G->Tv, &G->dTs,
                           &G->sbt, &G->ce, &G->ae, &G->ae_alt, &G->slot_list, &G->dctr, &G->c4_nch, &G->c4_side,
-                          &G->c4_off, &G->pair_edge, &G->pair_len, &G->pair_off, &G->dead_d, &G->pair_merge, &G->pair_hlen, &G->pair_hoff, &G->k4_s, &G->k4_edge, &G->k4_item, &G->tv_items,
+                          &G->c4_low, &G->c4_off, &G->pair_edge, &G->pair_idx, &G->pair_len, &G->pair_off, &G->dead_d, &G->pair_hlen, &G->pair_hoff, &G->k4_s, &G->k4_edge, &G->k4_item, &G->tv_items,
                           &G->tv_ioff};
   for (const DevBuf* b : bufs) v.push_back((uint64_t)(uintptr_t)b->p);
   v.push_back((uint64_t)(uintptr_t)G->pin);

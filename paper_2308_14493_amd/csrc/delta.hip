@@ -27,10 +27,10 @@
 //               neighbours S(e) joined by an edge;
 //   C4          per changed edge: paths s - a - b - o closing the cycle with
 //               e = (s, o), from the common ids of N(a) and N(o) for each
-//               pair (s, a): rows of similar length merged by a wave, a
-//               shorter N(a) walked against an LDS hash table of a small
-//               enough N(o), the others by walking the shorter row and
-//               searching the other.
+//               pair (s, a): the rows N(a) walked against an LDS bitmap of
+//               N(o), or, where that costs more (little to walk for the edge,
+//               or an N(a) far longer than N(o)), the shorter row walked and
+//               searched in the other.
 #include "gc_kernels.h"
 
 namespace {
@@ -113,6 +113,48 @@ __device__ __forceinline__ void wave_window_common(const uint32_t* __restrict__ 
       i0 += (int32_t)__popcll(__ballot(ia <= bmax));
       j0 += 64;
     }
+  }
+}
+
+// The entries of up to 64 row pieces, the wave together: lane l holds piece
+// [b, b + n) of col with a payload; f(payload, entry) on some lane for each
+// entry.  Pieces of at least 32 entries go one at a time through the wave
+// (consecutive lanes, four loads in flight per lane), the others are
+// flattened over the lanes with a search for the piece of each index.
+template <class F>
+__device__ __forceinline__ void wave_rows(const uint32_t* __restrict__ col, int64_t b, int32_t n, uint32_t pay, F f) {
+  const int l = lane_id();
+  const bool lng = n >= 32;
+  for (uint64_t m = __ballot(lng); m; m &= m - 1) {
+    const int src = __builtin_ctzll(m);
+    const uint32_t* row = col + (((int64_t)__builtin_amdgcn_readlane((uint32_t)((uint64_t)b >> 32), src) << 32) |
+                                 (uint32_t)__builtin_amdgcn_readlane((uint32_t)b, src));
+    const int32_t cnt = __builtin_amdgcn_readlane(n, src);
+    const uint32_t ps = __builtin_amdgcn_readlane(pay, src);
+    int32_t k = l;
+    for (; k + 192 < cnt; k += 256) {
+      uint32_t y[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) y[q] = row[k + 64 * q];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) f(ps, y[q]);
+    }
+    for (; k < cnt; k += 64) f(ps, row[k]);
+  }
+  const int32_t ns = lng ? 0 : n;
+  const int32_t incl = wave_incl_scan32(ns), tot = __shfl(incl, 63), excl = incl - ns;
+  for (int32_t at = 0; at < tot; at += 64) {
+    const int32_t idx = at + l;
+    int lo = 0, hi = 64;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      const int mid = (lo + hi) >> 1;
+      if (__shfl(excl, mid) <= idx) lo = mid; else hi = mid;
+    }
+    const int64_t bb = __shfl(b, lo);
+    const int32_t ex = __shfl(excl, lo);
+    const uint32_t ps = __shfl(pay, lo);
+    if (idx < tot) f(ps, col[bb + (idx - ex)]);
   }
 }
 
@@ -600,16 +642,40 @@ __global__ void k_delta_tv(DeltaArgs D, const unsigned long long* __restrict__ k
 
 // ------------------------------------------------------------- 4-cycles
 // Through a changed edge e = (s, o) run the 4-cycles s - a - b - o with
-// a in N(s) - {o}, b in N(a) & N(o) - {s}.  Per pair (s, a) the shorter of
-// N(a) and N(o) is walked and each entry searched in the other row, so a hub
-// on either side costs at most the other side's degree; s is the end with
-// the smaller sum over its neighbours a of min(d_a, d_o).  The work is
-// balanced over the whole chip: every pair (e, a) gets its walk length, a
-// scan places the walked entries of all pairs in one index space, and each
-// lane takes entries of that space (a hub pair is spread over many waves).
+// a in N(s) - {o}, b in N(a) & N(o) - {s}.  A pair (e, a) is counted in one
+// of two ways (pair_kind): its row N(a) is walked against a bitmap of N(o)
+// that a workgroup keeps in LDS (k_delta_c4_bits), or the shorter of N(a) and
+// N(o) is walked and each entry searched in the other row (k_delta_c4).  s is
+// the end with the smaller total cost.  The work is balanced over the whole
+// chip: every pair gets its walk length, a scan places the walked entries of
+// all pairs in one index space, and waves or workgroups take ranges of that
+// space (a hub pair is spread over many waves).
 
-// per changed edge: the end to walk from and its number of pairs.  The
-// walk of an end u costs sum_{a in N(u)} min(d_a, d_v); both rows of every
+// A walked entry costs one LDS probe; a search step is a dependent global
+// load.  Measured at scale 22: 9.9 ms for 0.6e9 searched entries (about 15
+// steps each) against 3.5e12 probes a second for the walk, so a search of
+// N(o) in N(a) pays only when N(a) is longer by more than this factor.
+constexpr int64_t C4B_RATIO = 64;
+// An edge whose walks sum to less than this does not earn a bitmap (clearing,
+// filling and the queue cost a workgroup about as much as searching so much).
+constexpr int64_t C4B_MIN = 4096;
+constexpr int C4B_T = 1024;
+constexpr int C4B_SMALL = 16384, C4B_LARGE = 36864;  // 32-bit words of the two bitmaps: 64 and 144 KB
+
+__device__ __forceinline__ int64_t pair_cost(int32_t al, int32_t ol) {
+  return min((int64_t)al, C4B_RATIO * (int64_t)ol);
+}
+// The bitmap of N(o) covers D.c4_ids ids downwards from N(o)'s last one: ids
+// are a degree order, so the ids below that window have few entries.
+__device__ __forceinline__ uint32_t c4b_base(const DeltaArgs& D, uint32_t o) {
+  const uint32_t top = (D.P.col[D.P.off[o] + D.P.len[o] - 1] & GC_ID) + 1u;
+  return top > D.c4_ids ? top - D.c4_ids : 0u;
+}
+// pairs of an edge with a bitmap that are walked against it
+__device__ __forceinline__ bool pair_walked(int32_t al, int32_t ol) { return (int64_t)al <= C4B_RATIO * (int64_t)ol; }
+
+// per changed edge: the end to walk from, whether it earns a bitmap, and its
+// number of pairs.  An end u costs sum_{a in N(u)} pair_cost(d_a, d_v); both rows of every
 // changed edge are cut in pieces of at most TV_CHUNK entries (the touched
 // rows' arrays hold the numbering; they are free again after the degree
 // passes), each wave sums one piece at a time into the edge's two totals
@@ -656,7 +722,7 @@ __global__ void k_delta_c4_plan(DeltaArgs D) {
     const int32_t k0 = (int32_t)((side_v ? pk - nu : pk) * TV_CHUNK), k1 = min(dx, k0 + TV_CHUNK);
     const uint32_t* rx = D.P.col + D.P.off[x];
     int64_t c = 0;
-    for (int32_t q = k0 + l; q < k1; q += 64) c += min((int64_t)D.P.len[rx[q] & GC_ID], (int64_t)other);
+    for (int32_t q = k0 + l; q < k1; q += 64) c += pair_cost(D.P.len[rx[q] & GC_ID], other);
     c = wave_sum64(c);
     if (l == 0 && c) atomicAdd((unsigned long long*)&D.pair_off[2 * i + (side_v ? 1 : 0)], (unsigned long long)c);
   }
@@ -674,12 +740,57 @@ __global__ void k_delta_plan_fin(DeltaArgs D) {
     const unsigned long long K = D.ce[i] & DIR_KEY_MASK;
     const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
     const bool from_u = D.pair_off[2 * i] <= D.pair_off[2 * i + 1];
-    D.c4_side[i] = from_u ? 0 : 1;
-    D.c4_nch[i] = from_u ? D.P.len[u] : D.P.len[v];
+    const int64_t cost = from_u ? D.pair_off[2 * i] : D.pair_off[2 * i + 1];
+    const bool bitmap = cost >= C4B_MIN;
+    const uint32_t s = from_u ? u : v, o = from_u ? v : u;
+    int32_t low = 0;  // N(o) below the window
+    if (bitmap) {
+      const uint32_t base = c4b_base(D, o);
+      if (base) low = lower_bound_id(D.P.col + D.P.off[o], D.P.len[o], base);
+    }
+    D.c4_side[i] = (from_u ? 0 : 1) | (bitmap ? 2 : 0);
+    D.c4_low[i] = low;
+    D.c4_nch[i] = D.P.len[s];
   }
 }
 
-// per pair (e, a): its position and its walk length min(d_a, d_o)
+// The k-th pair (e, b) of an edge with a bitmap of N(o): N(o)'s `low` entries
+// below the window (those in the batch are met again among the others), then
+// its insertions, then its deletions.
+__device__ __forceinline__ void c4_out_pair(const DeltaArgs& D, uint32_t o, int32_t low, int32_t k, uint32_t& b,
+                                            uint32_t& fob) {
+  const int32_t na = D.na[o];
+  if (k < low) {
+    const uint32_t e = D.P.col[D.P.off[o] + k];
+    b = e & GC_ID;
+    fob = nib(e);
+    return;
+  }
+  k -= low;
+  const unsigned long long key = k < na ? D.dirA[D.a_beg[o] + k] : D.dirR[D.r_beg[o] + (k - na)];
+  b = (uint32_t)(key & ((1ull << D.bits) - 1ull));
+  fob = k < na ? 1u : 2u;
+}
+
+// Appends a searched pair (edge i, index j, len entries) of the lanes with
+// `take` to the list (one atomic per wave).
+__device__ __forceinline__ void c4_search_append(const DeltaArgs& D, bool take, int64_t i, int32_t j, int32_t len) {
+  const uint64_t m = __ballot(take);
+  if (!m) return;
+  unsigned long long at = 0;
+  if (lane_id() == 0) at = atomicAdd(&D.dc[DC_SEARCH], (unsigned long long)__popcll(m));
+  const int64_t q = (int64_t)__shfl((long long)at, 0) + __popcll(m & lanemask_lt());
+  if (take && q < D.pair_cap) {
+    D.pair_edge[q] = (int32_t)i;
+    D.pair_idx[q] = j;
+    D.pair_len[q] = len;
+  }
+}
+
+// Per changed edge, a wave: the entries each pair (e, a) walks against the
+// bitmap (0 for the others), in pair order; the searched pairs go to a list
+// that holds nothing else, so that the waves of k_delta_c4 meet no empty
+// pairs.
 __global__ void k_delta_c4_pairs(DeltaArgs D) {
   const int64_t ne = min(ctr(D.dc, DC_EDGES), D.ce_cap);
   const int64_t npairs = D.c4_off[D.ce_cap];
@@ -694,124 +805,157 @@ __global__ void k_delta_c4_pairs(DeltaArgs D) {
   for (int64_t i = w0; i < ne; i += ws) {
     const unsigned long long K = D.ce[i] & DIR_KEY_MASK;
     const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
-    const uint32_t s = D.c4_side[i] ? v : u, o = s == u ? v : u;
+    const uint32_t s = (D.c4_side[i] & 1) ? v : u, o = s == u ? v : u;
     const uint32_t* srow = D.P.col + D.P.off[s];
     const int32_t sl = D.P.len[s], ol = D.P.len[o];
     const int64_t base = D.c4_off[i];
-    for (int32_t k = l; k < sl; k += 64) {
-      const uint32_t a = srow[k] & GC_ID;
+    const bool bitmap = (D.c4_side[i] & 2) != 0;
+    for (int32_t k0 = 0; k0 < sl; k0 += 64) {
+      const int32_t k = k0 + l;
+      const uint32_t a = k < sl ? srow[k] & GC_ID : o;
       const int32_t al = D.P.len[a];
-      const int32_t mn = min(al, ol), mx = max(al, ol);
-      D.pair_edge[base + k] = (int32_t)i;
-      // rows of similar length (the longer at most (log2 of it - 1) / 2
-      // times the shorter, the best split measured) are merged by a wave;
-      // of the others, a shorter N(a) against an N(o) small enough for an
-      // LDS hash table is walked against the table (k_delta_c4_hash), and
-      // the rest walk the shorter row and search the longer, lane by lane
-      const bool merge = a != o && mn > 0 && (int64_t)mx <= (int64_t)mn * ((30 - __clz(max(mx, 1))) / 2);
-      const bool hashed = !merge && a != o && al > 0 && al < ol && ol <= C4H_MAX;
-      D.pair_len[base + k] = a == o || merge || hashed ? 0 : mn;
-      D.pair_hlen[base + k] = hashed ? al : 0;
-      if (merge) D.pair_merge[atomicAdd(&D.dc[DC_MERGE], 1ull)] = (int32_t)(base + k);
+      const bool walked = bitmap && a != o && pair_walked(al, ol);
+      if (k < sl) D.pair_hlen[base + k] = walked ? al : 0;
+      c4_search_append(D, a != o && !walked, i, k, min(al, ol));
+    }
+    if (!bitmap) continue;
+    const int32_t low = D.c4_low[i], out = low + D.na[o] + D.nr[o];  // pairs (e, b)
+    for (int32_t k0 = 0; k0 < out; k0 += 64) {
+      const int32_t k = k0 + l;
+      uint32_t b = s, fob = 0;
+      if (k < out) c4_out_pair(D, o, low, k, b, fob);
+      const bool take = b != s && !(fob != 0 && (k < low || pkey(o, b, D.bits) < K));
+      c4_search_append(D, take, i, sl + k, min(D.P.len[b], sl));
     }
   }
 }
 
+// More searched pairs than the list holds: count again with more.
+__global__ void k_delta_c4_check(DeltaArgs D) {
+  const unsigned long long n = D.dc[DC_SEARCH];
+  if (gtid() == 0 && (int64_t)n > D.pair_cap) {
+    atomicAdd(&D.bstats[BS_RETRY], 1ull);
+    atomicMax(&D.dc[DC_PAIR_NEED], n);
+  }
+}
+
+// largest i in [0, n) with pre[i] <= x, the wave together: 63 samples a round
+__device__ __forceinline__ int64_t wave_upper_bound(const int64_t* __restrict__ pre, int64_t n, int64_t x) {
+  int64_t lo = 0, hi = n;  // pre[lo] <= x, pre[hi] > x (or hi == n)
+  while (hi - lo > 1) {
+    const int64_t st = (hi - lo + 63) / 64;
+    const int64_t at = lo + st * (lane_id() + 1);
+    const int k = __popcll(__ballot(at < hi && pre[min(at, hi - 1)] <= x));
+    hi = min(hi, lo + st * (k + 1));
+    lo = lo + st * k;
+  }
+  return lo;
+}
+
+// A searched pair: the row walked, the row searched, and what a hit needs.
+struct C4Search {
+  int64_t walk;           // first entry of this wave's part of the row walked
+  int64_t row;            // the row searched
+  unsigned long long K;   // key of the changed edge
+  int32_t len;            // entries of the row searched
+  int32_t only;           // > 0: a pair (e, b), |N(o)| of the edge
+  uint32_t s, o, a;       // the path s - a - b - o; the walk runs over b
+  uint32_t meta;          // fe | fsa << 2 | (the row walked is N(a)) << 4
+  int32_t g;
+};
+
+// The searched pairs.  Each wave takes one contiguous range of the index
+// space of their walked entries (equal ranges: balanced by construction),
+// 64 pairs at a time: a lane fetches one pair's record into LDS, then the
+// entries of all of them are dealt over the lanes, each searching its entry
+// in the other row.  Bound by the dependent loads of the searches.
 __global__ __launch_bounds__(TPB) void k_delta_c4(DeltaArgs D) {
+  __shared__ C4Search recs[TPB / 64][64];
   if (D.bstats[BS_RETRY]) return;
-  const int64_t npairs = D.c4_off[D.ce_cap];
-  const int64_t total = D.pair_off[npairs];
+  const int64_t np = ctr(D.dc, DC_SEARCH);
+  if (np == 0) return;
+  const int64_t total = D.pair_off[np];
   const unsigned long long idmask = (1ull << D.bits) - 1ull;
   const int l = lane_id();
-  // each wave takes one contiguous range of whole 64-entry chunks of the
-  // index space (equal ranges: balanced by construction); its lanes walk
-  // entries f = chunk * 64 + lane, so a lane's pair only moves forward and
-  // is found by stepping, and the pair's row data is loaded once per pair
-  const int64_t nchunk = (total + 63) >> 6, nw = gstride() >> 6;
-  const int64_t per = (nchunk + nw - 1) / nw;
-  const int64_t c0 = (gtid() >> 6) * per, c1 = min(nchunk, c0 + per);
+  C4Search* rec = recs[threadIdx.x >> 6];
+  const int64_t nw = gstride() >> 6;
+  const int64_t per = ((total + nw - 1) / nw + 63) / 64 * 64;
+  const int64_t w0 = min(total, (gtid() >> 6) * per), w1 = min(total, w0 + per);
   int64_t acc = 0;
   int cur_g = -1;
-  if (c0 < c1) {
-    // the pair holding the range's first entry: largest p with
-    // pair_off[p] <= f (empty pairs share their offset with the next)
-    const int64_t fs = c0 << 6;
-    int64_t p = 0;
-    {
-      int64_t lo = 0, hi = npairs;
-      while (hi - lo > 1) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (D.pair_off[mid] <= fs) lo = mid; else hi = mid;
-      }
-      p = lo;
-    }
-    int64_t pend = D.pair_off[p + 1], pbeg = D.pair_off[p];
-    bool fresh = true;
-    // the current pair's data
-    unsigned long long K = 0;
-    uint32_t fe = 0, s = 0, o = 0, eaj = 0, a = 0, fsa = 0;
-    const uint32_t* orow = nullptr;
-    const uint32_t* arow = nullptr;
-    int32_t ol = 0, al = 0;
-    int g = 0;
-    for (int64_t c = c0; c < c1; ++c) {
-      const int64_t f = (c << 6) + l;
-      if (f >= total) break;
-      while (pend <= f) {
-        ++p;
-        pbeg = pend;
-        pend = D.pair_off[p + 1];
-        fresh = true;
-      }
-      if (fresh) {
-        fresh = false;
-        const int32_t i = D.pair_edge[p];
+  for (int64_t p = w0 < w1 ? wave_upper_bound(D.pair_off, np, w0) : np; p < np; p += 64) {
+    if (D.pair_off[p] >= w1) break;
+    const int64_t pl = p + l;
+    int32_t n = 0;
+    if (pl < np) {
+      const int64_t hb = D.pair_off[pl], c0 = max(hb, w0), c1 = min(D.pair_off[pl + 1], w1);
+      if (c0 < c1) {
+        n = (int32_t)(c1 - c0);
+        const int64_t i = D.pair_edge[pl];
+        const int32_t j = D.pair_idx[pl];
         const unsigned long long ek = D.ce[i];
-        K = ek & DIR_KEY_MASK;
-        fe = (uint32_t)(ek >> DIR_MASK_SHIFT) & 3u;
-        const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
-        s = D.c4_side[i] ? v : u;
-        o = s == u ? v : u;
-        eaj = D.P.col[D.P.off[s] + (p - D.c4_off[i])];
-        a = eaj & GC_ID;
-        fsa = nib(eaj);
-        orow = D.P.col + D.P.off[o];
-        arow = D.P.col + D.P.off[a];
-        ol = D.P.len[o];
-        al = D.P.len[a];
-        g = D.gid[u];
-      }
-      const int32_t q = (int32_t)(f - pbeg);
-      uint32_t b, fab = 0, fob = 0;
-      bool hit;
-      if (al <= ol) {  // walk N(a), search N(o)
-        const uint32_t eab = arow[q];
-        b = eab & GC_ID;
-        fab = nib(eab);
-        const int32_t x = lower_bound_id(orow, ol, b);
-        hit = x < ol && (orow[x] & GC_ID) == b;
-        if (hit) fob = nib(orow[x]);
-      } else {         // walk N(o), search N(a)
-        const uint32_t eob = orow[q];
-        b = eob & GC_ID;
-        fob = nib(eob);
-        const int32_t x = lower_bound_id(arow, al, b);
-        hit = x < al && (arow[x] & GC_ID) == b;
-        if (hit) fab = nib(arow[x]);
-      }
-      if (hit && b != s) {
-        const bool skip = (fsa && pkey(s, a, D.bits) < K) || (fab && pkey(a, b, D.bits) < K) ||
-                          (fob && pkey(o, b, D.bits) < K);
-        if (!skip) {
-          if (g != cur_g) {
-            if (cur_g >= 0 && acc) atomicAdd(&D.sig[SIG_IDX(cur_g, 1, SG_C4)], (unsigned long long)acc);
-            acc = 0;
-            cur_g = g;
-          }
-          acc += delta_of(fe | fsa | fab | fob);
+        C4Search r;
+        r.K = ek & DIR_KEY_MASK;
+        const uint32_t u = (uint32_t)(r.K >> D.bits), v = (uint32_t)(r.K & idmask);
+        r.s = (D.c4_side[i] & 1) ? v : u;
+        r.o = r.s == u ? v : u;
+        r.only = 0;
+        uint32_t fsa;
+        const int32_t sl = D.P.len[r.s];
+        if (j < sl) {
+          const uint32_t e = D.P.col[D.P.off[r.s] + j];
+          r.a = e & GC_ID;
+          fsa = nib(e);
+        } else {  // a pair (e, b): the same with the ends swapped, through walked a only
+          c4_out_pair(D, r.o, D.c4_low[i], j - sl, r.a, fsa);
+          r.only = D.P.len[r.o];
+          const uint32_t t = r.s;
+          r.s = r.o;
+          r.o = t;
         }
+        const int64_t ao = D.P.off[r.a], oo = D.P.off[r.o];
+        const int32_t al = D.P.len[r.a], ol = D.P.len[r.o];
+        const bool wa = al <= ol;
+        r.walk = (wa ? ao : oo) + (c0 - hb);
+        r.row = wa ? oo : ao;
+        r.len = wa ? ol : al;
+        r.meta = ((uint32_t)(ek >> DIR_MASK_SHIFT) & 3u) | (fsa << 2) | ((wa ? 1u : 0u) << 4);
+        r.g = D.gid[u];
+        rec[l] = r;
       }
     }
+    const int32_t incl = wave_incl_scan32(n), tot = __shfl(incl, 63), excl = incl - n;
+    wave_sync();
+    for (int32_t at = 0; at < tot; at += 64) {
+      const int32_t idx = at + l;
+      int lo = 0, hi = 64;  // the pair of index idx: largest lane with excl <= idx
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        const int mid = (lo + hi) >> 1;
+        if (__shfl(excl, mid) <= idx) lo = mid; else hi = mid;
+      }
+      const int32_t ex = __shfl(excl, lo);
+      if (idx >= tot) continue;
+      const C4Search& r = rec[lo];
+      const uint32_t ew = D.P.col[r.walk + (idx - ex)], b = ew & GC_ID;
+      const uint32_t* row = D.P.col + r.row;
+      const int32_t len = r.len, x = lower_bound_id(row, len, b);
+      if (x >= len) continue;
+      const uint32_t er = row[x];
+      if ((er & GC_ID) != b || b == r.s) continue;
+      const bool wa = (r.meta >> 4) & 1u;
+      const uint32_t fe = r.meta & 3u, fsa = (r.meta >> 2) & 3u, fab = nib(wa ? ew : er), fob = nib(wa ? er : ew);
+      if ((fsa && pkey(r.s, r.a, D.bits) < r.K) || (fab && pkey(r.a, b, D.bits) < r.K) ||
+          (fob && pkey(r.o, b, D.bits) < r.K) || (r.only && !pair_walked(D.P.len[b], r.only)))
+        continue;
+      if (r.g != cur_g) {
+        if (cur_g >= 0 && acc) atomicAdd(&D.sig[SIG_IDX(cur_g, 1, SG_C4)], (unsigned long long)acc);
+        acc = 0;
+        cur_g = r.g;
+      }
+      acc += delta_of(fe | fsa | fab | fob);
+    }
+    wave_sync();
   }
   // one atomic per wave when its lanes hold sums of one graph
   const uint64_t has = __ballot(cur_g >= 0 && acc != 0);
@@ -826,59 +970,21 @@ __global__ __launch_bounds__(TPB) void k_delta_c4(DeltaArgs D) {
   }
 }
 
-// The pairs (e, a) whose rows N(a) and N(o) have similar lengths: one wave
-// per pair merges both rows (wave_window_common); each common b != s closes
-// the path s - a - b - o.
-__global__ __launch_bounds__(TPB) void k_delta_c4_merge(DeltaArgs D) {
-  if (D.bstats[BS_RETRY]) return;
-  const int64_t nm = ctr(D.dc, DC_MERGE);
-  const unsigned long long idmask = (1ull << D.bits) - 1ull;
-  int64_t acc = 0;
-  int cur_g = -1;
-  const int64_t nwv = gstride() >> 6;
-  for (int64_t m = gtid() >> 6; m < nm; m = wave_next(&D.dc[DC_QMERGE], nwv)) {
-    const int64_t p = D.pair_merge[m];
-    const int32_t i = D.pair_edge[p];
-    const unsigned long long ek = D.ce[i];
-    const unsigned long long K = ek & DIR_KEY_MASK;
-    const uint32_t fe = (uint32_t)(ek >> DIR_MASK_SHIFT) & 3u;
-    const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
-    const uint32_t s = D.c4_side[i] ? v : u, o = s == u ? v : u;
-    const uint32_t eaj = D.P.col[D.P.off[s] + (p - D.c4_off[i])], a = eaj & GC_ID;
-    const uint32_t fsa = nib(eaj);
-    const int g = D.gid[u];
-    if (g != cur_g) {
-      // the wave's graph changes: flush per lane (wave-uniform branch)
-      if (cur_g >= 0 && acc) atomicAdd(&D.sig[SIG_IDX(cur_g, 1, SG_C4)], (unsigned long long)acc);
-      acc = 0;
-      cur_g = g;
-    }
-    wave_window_common(D.P.col, D.P.off[a], D.P.len[a], D.P.off[o], D.P.len[o],
-                       [&](uint32_t eab, uint32_t eob) {
-                         const uint32_t b = eab & GC_ID;
-                         if (b == s) return;
-                         const uint32_t fab = nib(eab), fob = nib(eob);
-                         const bool skip = (fsa && pkey(s, a, D.bits) < K) || (fab && pkey(a, b, D.bits) < K) ||
-                                           (fob && pkey(o, b, D.bits) < K);
-                         if (!skip) acc += delta_of(fe | fsa | fab | fob);
-                       });
-  }
-  if (cur_g >= 0) {
-    const int64_t t = wave_sum64(acc);
-    if (lane_id() == 0 && t) atomicAdd(&D.sig[SIG_IDX(cur_g, 1, SG_C4)], (unsigned long long)t);
-  }
+// Walked entries per chunk of a bitmap edge: enough chunks to fill the chip
+// several times over, each long enough to pay for its bitmap (four times
+// |N(o)|, and a floor for the fixed cost of a chunk).
+__device__ __forceinline__ int64_t c4b_chunk(int64_t total, int32_t ol) {
+  const int64_t even = total / 4096;
+  return max(min(max(even, (int64_t)16384), (int64_t)131072), 4 * (int64_t)ol);
 }
 
-// Entries of the walked rows per chunk of hashed pairs: at least
-// C4H_CHUNK_MIN and four times |N(o)|, so that building the table of N(o)
-// costs at most a quarter of a chunk.
-__device__ __forceinline__ int64_t c4h_chunk(int32_t ol) { return max(C4H_CHUNK_MIN, 4 * (int64_t)ol); }
-
-// Chunks of the hashed pairs per changed edge (0 past the edge count, for
+// Chunks of the walked pairs per changed edge (0 past the edge count, for
 // the scan).
 __global__ void k_delta_hitems(DeltaArgs D) {
   const int64_t ne = min(ctr(D.dc, DC_EDGES), D.ce_cap);
-  const bool fits = D.c4_off[D.ce_cap] <= D.pair_cap;  // else the pairs were not listed (count again)
+  const int64_t npairs = D.c4_off[D.ce_cap];
+  const bool fits = npairs <= D.pair_cap;  // else the pairs were not listed (count again)
+  const int64_t total = fits ? D.pair_hoff[npairs] : 0;
   const unsigned long long idmask = (1ull << D.bits) - 1ull;
   for (int64_t i = gtid(); i < D.tcap; i += gstride()) {
     int32_t n = 0;
@@ -887,8 +993,7 @@ __global__ void k_delta_hitems(DeltaArgs D) {
       if (h > 0) {
         const unsigned long long K = D.ce[i] & DIR_KEY_MASK;
         const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
-        const uint32_t o = D.c4_side[i] ? u : v;
-        const int64_t T = c4h_chunk(D.P.len[o]);
+        const int64_t T = c4b_chunk(total, D.P.len[(D.c4_side[i] & 1) ? u : v]);
         n = (int32_t)((h + T - 1) / T);
       }
     }
@@ -896,121 +1001,120 @@ __global__ void k_delta_hitems(DeltaArgs D) {
   }
 }
 
-// The hashed pairs (e, a): each workgroup takes chunks from a queue, builds
-// an LDS hash table of N(o) for the chunk's edge (kept while the next chunk
-// is of the same edge): id, the nibble of (o, b), and whether (o, b) is a
-// changed pair of smaller key than e (such paths are counted from that
-// pair).  Its waves split the chunk's entries in contiguous pieces; a lane
-// steps through the pairs of its piece and probes the table with each entry
-// b of N(a): a hit with b != s closes the path s - a - b - o.
-__global__ __launch_bounds__(C4H_T) void k_delta_c4_hash(DeltaArgs D) {
-  __shared__ uint32_t tab[C4H_SLOTS];
-  __shared__ int64_t item_s;
+// The walked pairs (e, a), e = (s, o).  Each workgroup takes chunks from a
+// queue and holds a bitmap in LDS (kept while the next chunk is of the same
+// edge) of the b in N(o) inside the window whose edge (o, b) is not in the
+// batch.  Its waves split the chunk's entries of the rows N(a) evenly, read
+// them with consecutive lanes and probe one bit per entry: a hit closes the
+// path s - a - b - o.  Hits on entries that are in the batch themselves take
+// the general rule (rare).
+// What bounds it: instruction issue, about 13 per 64 entries, while the
+// bitmap costs little (a chunk is at least four times |N(o)|).  Before, rows
+// of similar length were merged by a wave (about 35 instructions and nine
+// lane exchanges per 64 entries of each row), shorter rows probed an LDS hash
+// table and the rest was searched: 22 ms in all for 2,500 updates at scale 22
+// (7e9 entries walked), 2.1 ms for 1,000 at scale 18 (1.3e8); now 6.3 + 0.3 ms
+// and 0.25 + 0.02 ms.  WORDS = 16384 (ids up to 2^19) lets two workgroups
+// share a CU.
+template <int WORDS>
+__global__ __launch_bounds__(C4B_T, WORDS <= 16384 ? 8 : 4) void k_delta_c4_bits(DeltaArgs D) {
+  __shared__ uint4 bm4[WORDS / 4];
+  __shared__ int64_t item_s, edge_s;
   if (D.bstats[BS_RETRY]) return;
+  uint32_t* bm = (uint32_t*)bm4;
   const int64_t ne = min(ctr(D.dc, DC_EDGES), D.ce_cap);
   if (ne == 0) return;
   const int64_t nitems = D.tv_ioff[ne];
+  const int64_t total = D.pair_hoff[D.c4_off[D.ce_cap]];
   const unsigned long long idmask = (1ull << D.bits) - 1ull;
-  const int32_t l = lane_id(), wv = (int32_t)(threadIdx.x >> 6), nwv = (int32_t)(blockDim.x >> 6);
-  constexpr uint32_t EMPTY = 0xFFFFFFFFu;
+  const int32_t l = lane_id(), wv = (int32_t)(threadIdx.x >> 6);
+  constexpr int32_t NW = C4B_T / 64;
+  const uint32_t ids = D.c4_ids;  // <= WORDS * 32
+  const uint32_t* __restrict__ col = D.P.col;
   int64_t acc = 0;
   int cur_g = -1;
   int64_t cur_i = -1;
   while (true) {
     __syncthreads();
-    if (threadIdx.x == 0) item_s = (int64_t)atomicAdd(&D.dc[DC_QH], 1ull);
-    __syncthreads();
-    const int64_t it = item_s;
-    if (it >= nitems) break;
-    int64_t lo = 0, hi = ne;  // the item's edge: largest i with tv_ioff[i] <= it
-    while (hi - lo > 1) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (D.tv_ioff[mid] <= it) lo = mid; else hi = mid;
+    if (wv == 0) {
+      int64_t it0 = 0;
+      if (l == 0) it0 = (int64_t)atomicAdd(&D.dc[DC_QH], 1ull);
+      it0 = __shfl(it0, 0);
+      const int64_t i0 = it0 < nitems ? wave_upper_bound(D.tv_ioff, ne, it0) : 0;
+      if (l == 0) { item_s = it0; edge_s = i0; }
     }
-    const int64_t i = lo;
+    __syncthreads();
+    const int64_t it = item_s, i = edge_s;
+    if (it >= nitems) break;
     const unsigned long long ek = D.ce[i];
     const unsigned long long K = ek & DIR_KEY_MASK;
     const uint32_t fe = (uint32_t)(ek >> DIR_MASK_SHIFT) & 3u;
     const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
-    const uint32_t s = D.c4_side[i] ? v : u, o = s == u ? v : u;
-    const int32_t ol = D.P.len[o];  // <= C4H_MAX: the edge has hashed pairs
-    int tb = 8;  // table of 2^tb slots: at least 4 |N(o)| where LDS allows
-    while ((1 << tb) < 4 * ol && (1 << tb) < C4H_SLOTS) ++tb;
-    const uint32_t tmask = (1u << tb) - 1u;
-    if (i != cur_i) {
-      for (int32_t k = (int32_t)threadIdx.x; k <= (int32_t)tmask; k += (int32_t)blockDim.x) tab[k] = EMPTY;
-      __syncthreads();
-      const uint32_t* orow = D.P.col + D.P.off[o];
-      for (int32_t k = (int32_t)threadIdx.x; k < ol; k += (int32_t)blockDim.x) {
-        const uint32_t e = orow[k], b = e & GC_ID, f = nib(e);
-        const uint32_t val = b | (f << 28) | ((f && pkey(o, b, D.bits) < K) ? (1u << 30) : 0u);
-        uint32_t h = (b * 2654435761u) >> (32 - tb);
-        while (atomicCAS(&tab[h], EMPTY, val) != EMPTY) h = (h + 1) & tmask;
-      }
-      __syncthreads();
-      cur_i = i;
-    }
+    const uint32_t s = (D.c4_side[i] & 1) ? v : u, o = s == u ? v : u;
+    const int64_t so = D.P.off[s], oo = D.P.off[o];
+    const int32_t ol = D.P.len[o];  // > 0: row o holds s
+    const uint32_t base = c4b_base(D, o);
     const int g = D.gid[u];
     if (g != cur_g) {
       if (cur_g >= 0) add_sig(D, cur_g, SG_C4, acc);
       acc = 0;
       cur_g = g;
     }
-    // the chunk: entries [r0, r1) of the hashed walk index space
+    const int64_t T = c4b_chunk(total, ol);
+    const int64_t ch = it - D.tv_ioff[i];
+    if (i != cur_i) {
+      for (int32_t k = (int32_t)threadIdx.x; k < WORDS / 4; k += C4B_T) bm4[k] = make_uint4(0u, 0u, 0u, 0u);
+      __syncthreads();
+      for (int32_t k0 = wv * 256; k0 < ol; k0 += 4 * C4B_T) {  // four loads in flight per lane
+        uint32_t y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y[q] = col[oo + min(k0 + 64 * q + l, ol - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t x = (y[q] & GC_ID) - base;
+          if (!(y[q] & GC_FLAGS) && x < ids) atomicOr(&bm[x >> 5], 1u << (x & 31u));
+        }
+      }
+      cur_i = i;
+      __syncthreads();
+    }
+    // the chunk: entries [r0, r1) of the walked index space, this wave's
+    // piece of them; 64 pairs at a time, a pair's part of the piece per lane
     const int64_t p0 = D.c4_off[i], p1 = D.c4_off[i + 1];
-    const int64_t T = c4h_chunk(ol);
-    const int64_t r0 = D.pair_hoff[p0] + (it - D.tv_ioff[i]) * T, r1 = min(D.pair_hoff[p1], r0 + T);
-    const int64_t nst = (r1 - r0 + 63) >> 6, per = (nst + nwv - 1) / nwv;
-    const int64_t st0 = wv * per, st1 = min(nst, st0 + per);
-    if (st0 >= st1) continue;
-    // this lane's first pair: largest p with pair_hoff[p] <= f (pairs
-    // walked elsewhere share their offset with the next)
-    int64_t f = r0 + (st0 << 6) + l;
-    int64_t p = p0;
-    {
-      int64_t a0 = p0, a1 = p1;
-      while (a1 - a0 > 1) {
-        const int64_t mid = (a0 + a1) >> 1;
-        if (D.pair_hoff[mid] <= f) a0 = mid; else a1 = mid;
-      }
-      p = a0;
-    }
-    int64_t pbeg = D.pair_hoff[p], pend = D.pair_hoff[p + 1];
-    bool fresh = true;
-    const uint32_t* srow = D.P.col + D.P.off[s];
-    const uint32_t* arow = nullptr;
-    uint32_t a = 0, fsa = 0;
-    bool skip_sa = false;
-    for (int64_t st = st0; st < st1; ++st) {
-      f = r0 + (st << 6) + l;
-      if (f >= r1) break;
-      while (pend <= f) {
-        ++p;
-        pbeg = pend;
-        pend = D.pair_hoff[p + 1];
-        fresh = true;
-      }
-      if (fresh) {
-        fresh = false;
-        const uint32_t eaj = srow[p - p0];
-        a = eaj & GC_ID;
-        fsa = nib(eaj);
-        skip_sa = fsa && pkey(s, a, D.bits) < K;
-        arow = D.P.col + D.P.off[a];
-      }
-      const uint32_t eab = arow[f - pbeg], b = eab & GC_ID;
-      uint32_t h = (b * 2654435761u) >> (32 - tb), sv;
-      while (true) {
-        sv = tab[h];
-        if (sv == EMPTY || (sv & GC_ID) == b) break;
-        h = (h + 1) & tmask;
-      }
-      if (sv != EMPTY && b != s) {
-        const uint32_t fab = nib(eab);
-        if (!(skip_sa || (fab && pkey(a, b, D.bits) < K) || ((sv >> 30) & 1u)))
-          acc += delta_of(fe | fsa | fab | ((sv >> 28) & 3u));
+    const int64_t r0 = D.pair_hoff[p0] + ch * T, r1 = min(D.pair_hoff[p1], r0 + T);
+    const int64_t per = (r1 - r0 + NW - 1) / NW;
+    const int64_t w0 = min(r1, r0 + wv * per), w1 = min(r1, w0 + per);
+    uint32_t clean = 0;  // hits with no other edge of the path in the batch
+    if (w0 < w1) {
+      for (int64_t p = p0 + wave_upper_bound(D.pair_hoff + p0, p1 - p0, w0); p < p1; p += 64) {
+        if (D.pair_hoff[p] >= w1) break;
+        const int64_t pl = p + l;
+        int64_t sb = 0;
+        int32_t sn = 0;
+        uint32_t esa = 0;
+        if (pl < p1) {
+          const int64_t hb = D.pair_hoff[pl], he = D.pair_hoff[pl + 1];
+          const int64_t c0 = max(hb, w0), c1 = min(he, w1);
+          if (c0 < c1) {
+            esa = col[so + (pl - p0)];
+            sb = D.P.off[esa & GC_ID] + (c0 - hb);
+            sn = (int32_t)(c1 - c0);
+          }
+        }
+        wave_rows(col, sb, sn, esa, [&](uint32_t ea, uint32_t y) {
+          const uint32_t x = (y & GC_ID) - base;
+          uint32_t hit = 0;
+          if (x < ids) hit = (bm[x >> 5] >> (x & 31u)) & 1u;
+          if (hit && ((ea | y) & GC_FLAGS)) {  // (s, a) or (a, b) in the batch
+            const uint32_t a = ea & GC_ID, b = y & GC_ID, fsa = nib(ea), fab = nib(y);
+            hit = 0;
+            if (!(fsa && pkey(s, a, D.bits) < K) && !(fab && pkey(a, b, D.bits) < K)) acc += delta_of(fe | fsa | fab);
+          }
+          clean += hit;
+        });
       }
     }
+    acc += (int64_t)clean * delta_of(fe);
   }
   if (cur_g >= 0) add_sig(D, cur_g, SG_C4, acc);
 }
@@ -1062,7 +1166,11 @@ __global__ void k_tv_apply(const int32_t* __restrict__ rlist, const unsigned lon
 }
 
 // ---------------------------------------------------------- launchers
-void launch_delta(const DeltaArgs& D, int slots, hipStream_t s) {
+void launch_delta(const DeltaArgs& D_, int slots, hipStream_t s) {
+  DeltaArgs D = D_;
+  const bool small_bits = D.N <= C4B_SMALL * 32;
+  const uint32_t ids = (small_bits ? C4B_SMALL : C4B_LARGE) * 32;
+  if (D.c4_ids == 0 || D.c4_ids > ids) D.c4_ids = ids;
   fill_u64(D.dc, 0ull, DC_COUNT, s);
   hipLaunchKernelGGL(k_delta_edges, dim3(1024), dim3(TPB), 0, s, D);
   hipLaunchKernelGGL(k_delta_titems, dim3(1024), dim3(TPB), 0, s, D);
@@ -1080,10 +1188,11 @@ void launch_delta(const DeltaArgs& D, int slots, hipStream_t s) {
   hipLaunchKernelGGL(k_delta_c4_plan, dim3(2048), dim3(TPB), 0, s, D);
   hipLaunchKernelGGL(k_delta_plan_fin, dim3(256), dim3(TPB), 0, s, D);
   exclusive_scan_i32_to_i64(D.c4_nch, D.c4_off, D.ce_cap, D.scan_tmp, s);
-  // every pair below the count c4_off[ce_cap] gets both lengths, and only
-  // offsets up to that count are read: no clearing, scans up to the count
+  // every walked and every searched pair below their counts gets a length,
+  // and only offsets up to the counts are read: no clearing, scans up to them
   hipLaunchKernelGGL(k_delta_c4_pairs, dim3(1024), dim3(TPB), 0, s, D);
-  exclusive_scan_i32_to_i64_count(D.pair_len, D.pair_off, D.pair_cap, D.c4_off + D.ce_cap, D.scan_tmp, s);
+  hipLaunchKernelGGL(k_delta_c4_check, dim3(1), dim3(64), 0, s, D);
+  exclusive_scan_i32_to_i64_count(D.pair_len, D.pair_off, D.pair_cap, (const int64_t*)(D.dc + DC_SEARCH), D.scan_tmp, s);
   exclusive_scan_i32_to_i64_count(D.pair_hlen, D.pair_hoff, D.pair_cap, D.c4_off + D.ce_cap, D.scan_tmp, s);
   hipLaunchKernelGGL(k_delta_hitems, dim3(256), dim3(TPB), 0, s, D);
   exclusive_scan_i32_to_i64(D.tv_items, D.tv_ioff, D.tcap, D.scan_tmp, s);
@@ -1093,8 +1202,10 @@ void launch_delta(const DeltaArgs& D, int slots, hipStream_t s) {
   hipLaunchKernelGGL(k_delta_vertex2, dim3(1024), dim3(TPB), 0, s, D);
   hipLaunchKernelGGL(k_delta_tv, dim3(1024), dim3(TPB), 0, s, D, (const unsigned long long*)sorted);
   hipLaunchKernelGGL(k_delta_c4, dim3(4096), dim3(TPB), 0, s, D);
-  hipLaunchKernelGGL(k_delta_c4_merge, dim3(4096), dim3(TPB), 0, s, D);
-  hipLaunchKernelGGL(k_delta_c4_hash, dim3(256), dim3(C4H_T), 0, s, D);
+  if (small_bits)
+    hipLaunchKernelGGL(k_delta_c4_bits<C4B_SMALL>, dim3(512), dim3(C4B_T), 0, s, D);
+  else
+    hipLaunchKernelGGL(k_delta_c4_bits<C4B_LARGE>, dim3(256), dim3(C4B_T), 0, s, D);
 }
 
 void launch_tv_region(int nv, const RegionDev& R, const int32_t* rlist, const unsigned long long* c,

@@ -176,8 +176,8 @@ void launch_combine(int nv, const unsigned long long* sig, long long* state, lon
 
 // capi.cpp: thread-local error text read by gc_last_error()
 // delta.hip: edge-local update of the Sigma terms of a one-batch pass
-enum { DC_EDGES = 0, DC_AFF, DC_AFF_TOTAL, DC_AFF_NEED, DC_SLOT_NEED, DC_QTRI, DC_QC4, DC_PAIR_NEED, DC_MERGE,
-       DC_HS, DC_HITEMS, DC_HEAVY, DC_QK4, DC_QH, DC_QAFF, DC_QMERGE, DC_COUNT };
+enum { DC_EDGES = 0, DC_AFF, DC_AFF_TOTAL, DC_AFF_NEED, DC_SLOT_NEED, DC_QTRI, DC_QC4, DC_PAIR_NEED, DC_SEARCH,
+       DC_HS, DC_HITEMS, DC_HEAVY, DC_QK4, DC_QH, DC_QAFF, DC_COUNT };
 // 4-cliques of changed edges with many common neighbours, spread over the
 // workgroups in chunks: the common neighbours of such edges (with their
 // flags), the edges, and the chunks (fixed capacities; an edge that does not
@@ -188,21 +188,14 @@ constexpr int64_t K4_HS_CAP = 1 << 22;  // stored common neighbours
 constexpr int64_t K4_HE_CAP = 1 << 14;  // split edges
 constexpr int64_t K4_IT_CAP = 1 << 18;  // chunks
 constexpr int32_t TV_CHUNK = 4096;      // entries of a touched row per piece in the edge-local degree passes
-// 4-cycle pairs (e, a) with a shorter N(a) that is not merged, counted
-// against an LDS hash table of N(o): rows N(o) of at most C4H_MAX entries
-// (table of C4H_SLOTS, load <= 1/2); work in chunks of at least
-// C4H_CHUNK_MIN entries of the walked rows and four times |N(o)| (the
-// table build)
-constexpr int C4H_SLOTS = 32768;
-constexpr int32_t C4H_MAX = 16384;
-constexpr int64_t C4H_CHUNK_MIN = 16384;
-constexpr int C4H_T = 1024;
 struct DeltaArgs {
   PoolDev P;                          // union view left by the tombstone merge
   int64_t N;
   int bits;
   const unsigned long long* dirA;     // sorted directed change lists (counts in c)
   const unsigned long long* dirD;
+  const unsigned long long* dirR;     // the deletions again, with a segment per row (r_beg, nr)
+  const int32_t *a_beg, *na, *r_beg, *nr;  // [N] segments of dirA and dirR
   const unsigned long long* c;        // batch counters (C_DIRA, C_DIRD, C_TOUCH)
   const int32_t* touched;             // touched rows
   const int32_t* mark;                // [N] 1 on touched rows
@@ -224,11 +217,13 @@ struct DeltaArgs {
   int64_t slot_cap;
   unsigned long long* dc;             // [DC_COUNT] counters of the stage
   int32_t* c4_nch;                    // [ce_cap] pairs (e, a) per changed edge: degree of the end walked from
-  int32_t* c4_side;                   // [ce_cap] 0: walk from u, 1: from v
+  int32_t* c4_side;                   // [ce_cap] bit 0: walk from v instead of u; bit 1: against a bitmap
+  int32_t* c4_low;                    // [ce_cap] entries of the other end's row below the bitmap's window
+  uint32_t c4_ids;                    // ids a bitmap covers (0 or too many: launch_delta sets the most)
   int64_t* c4_off;                    // [ce_cap + 1] exclusive scan of c4_nch
-  int32_t* pair_edge;                 // [pair_cap] changed edge of each pair
-  int32_t* pair_len;                  // [pair_cap] walk length of each pair (0: merged instead)
-  int32_t* pair_merge;                // [pair_cap] pairs whose rows are merged by a wave (DC_MERGE of them)
+  // searched pairs (DC_SEARCH of them): changed edge, index (below the degree
+  // of the end walked from: pair (e, a), else (e, b)) and entries walked
+  int32_t *pair_edge, *pair_idx, *pair_len;  // [pair_cap]
   uint32_t* k4_s;                     // [K4_HS_CAP] common neighbours of split edges: id | nibble(u, w) << 28 | nibble(v, w) << 30
   int64_t* k4_edge;                   // [K4_HE_CAP][3] split edges: changed edge index, offset in k4_s, count
   int32_t* k4_item;                   // [K4_IT_CAP][2] chunks: split edge (-1: none), chunk index
@@ -236,7 +231,7 @@ struct DeltaArgs {
   int64_t* tv_ioff;                   // [tcap + 1] exclusive scan of tv_items
   int64_t tcap;                       // touched rows the two arrays cover (>= the touched count)
   int64_t* pair_off;                  // [pair_cap + 1] exclusive scan of pair_len
-  int32_t* pair_hlen;                 // [pair_cap] entries of N(a) walked against the hash of N(o) (0: other ways)
+  int32_t* pair_hlen;                 // [pair_cap] entries of N(a) walked against the bitmap of N(o) (0: searched)
   int64_t* pair_hoff;                 // [pair_cap + 1] exclusive scan of pair_hlen
   int64_t pair_cap;
   void* scan_tmp;                     // scan scratch for max(ce_cap, pair_cap) + 1 entries
