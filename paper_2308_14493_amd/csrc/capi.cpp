@@ -84,6 +84,12 @@ int bits_for(int64_t x) {  // smallest b >= 1 with x <= 2^b
   return b;
 }
 
+int64_t pow2_at_least(int64_t x) {
+  int64_t p = 1;
+  while (p < x) p <<= 1;
+  return p;
+}
+
 typedef __int128 i128;
 
 i128 c2w(i128 x) { return x * (x - 1) / 2; }
@@ -148,13 +154,13 @@ int64_t gc_footprint_estimate(int64_t n, int64_t m, double slack, int64_t max_de
   // resident rows (off, len, cap, gid, ext2int, int2ext) and the arena
   b += 28 * N;
   const int64_t used = (int64_t)((1.0 + slack) * (double)E) + 2 * N;
-  b += 4 * std::max<int64_t>(4 * used, used + (1 << 20));
+  b += 8 * std::max<int64_t>(4 * used, used + (1 << 20));  // entries and their triangle counts
   // per-vertex pass arrays and work lists
   b += (10 + L_NUM) * 4 * N;
   // region view of the union (entries grow by a quarter when exceeded) and
   // the merge scratch: rcol, rrow, t, vpos (20 B) + tp (16 B) per entry
   const int64_t e_alloc = E + E / 2 + (1 << 20);
-  b += 36 * e_alloc + 4 * e_alloc;
+  b += 36 * e_alloc + 8 * e_alloc;
   b += 8 * (N + 1) + 16 * N + 4 * GC_NV_MAX * N;  // roff, c4 keys, degrees per version
   b += (int64_t)radix_sort_tmp_bytes(std::max<int64_t>(2 * m, N)) + (int64_t)scan_tmp_bytes(N + 1);
   // hub counters of the large 4-cycle tier and their cursors
@@ -168,14 +174,14 @@ int64_t gc_footprint_estimate(int64_t n, int64_t m, double slack, int64_t max_de
     const int64_t cap = std::min<int64_t>(32767, max_out + max_out / 8 + 16);
     b += 256 * tri_scratch_words64(4, cap) * 8;
   }
-  // triangles per vertex and the edge-local passes' scratch (affected edges
-  // of a batch of 2^18 updates; common neighbours per hub-counter slot)
-  b += 24 * N;
-  b += 2 * 8 * (8 * ((int64_t)1 << 18) + 4096);
-  b += slots * (max_deg + max_deg / 4 + 4096) * 4;
-  // transient arrays of the build (edge keys, directed entries, ranks)
-  b += 64 * m + 24 * N;
-  return b + ((int64_t)64 << 20);
+  // triangles per vertex and the edge-local passes' affected edges (list and
+  // table for a batch of 2^18 updates)
+  b += 16 * N;
+  const int64_t ae = 8 * ((int64_t)1 << 18) + 4096;
+  b += 8 * ae + 12 * pow2_at_least(ae + ae / 2);
+  // the transient arrays of the build (64 bytes per edge) are freed before the
+  // region arrays above, which need more, are allocated
+  return b + ((int64_t)32 << 20);
 }
 
 struct gc_graph {
@@ -197,7 +203,7 @@ struct gc_graph {
   int bits = 1;
 
   // resident graph
-  DevBuf off, len, cap, col, top, gid, ext2int, int2ext;
+  DevBuf off, len, cap, col, tt, top, gid, ext2int, int2ext;
   int64_t arena_cap = 0, arena_top = 0, entries = 0;
 
   // small device state; vout: state after each later version of a pass
@@ -207,16 +213,17 @@ struct gc_graph {
   // batch scratch
   DevBuf bin, keys, keys_alt, dirA, dirA_alt, dirD, dirD_alt, dirR, dirR_alt;
   DevBuf a_beg, na, r_beg, nr, mark, tix;
-  DevBuf touched, dest, newcap, tlen, tpre, scratch, sort_tmp, scan_tmp;
+  DevBuf touched, dest, newcap, tlen, tpre, scratch, scratch_t, sort_tmp, scan_tmp;
 
   // region and counting
   DevBuf roff, rcol, rrow, rlow, dver, t, tp, vpos, level, rlist, rlen, lists;
   DevBuf c4_dense, c4_touch, c4_cur, c4_blk, c4_keys, c4_keys_alt, tri_scratch;
   // triangles at each vertex (kept for the edge-local passes) and the
   // scratch of those passes
-  DevBuf Tv, dTs, sbt, ce, ae, ae_alt, slot_list, dctr, c4_nch, c4_side, c4_low, c4_off, pair_edge, pair_idx, pair_len, pair_off,
-      pair_hlen, pair_hoff, k4_s, k4_edge, k4_item, tv_items, tv_ioff;
-  int64_t ae_cap = 0, slot_cap = 0, pair_cap = 0;
+  DevBuf Tv, dTs, ce, hk, hd, hl, e_ns, e_dt, e_kw, slist, dctr, c4_nch, c4_side, c4_low, c4_off, pair_edge, pair_idx,
+      pair_len, pair_off, pair_hlen, pair_hoff, tv_items, tv_ioff;
+  int64_t ae_cap = 0, pair_cap = 0;
+  uint32_t hmask = 0;                // slots of hk, hd less one
   // largest affected-edge and 4-cycle-pair demand per update seen in an
   // edge-local pass: later passes size their lists for their batch capacity
   // at that rate instead of finding them short and counting again
@@ -319,6 +326,7 @@ struct gc_graph {
     P.len = len.as<int32_t>();
     P.cap = cap.as<int32_t>();
     P.col = col.as<uint32_t>();
+    P.tt = tt.as<uint32_t>();
     P.arena_cap = arena_cap;
     P.arena_top = top.as<unsigned long long>();
     P.gid = gid.as<int32_t>();
@@ -516,7 +524,7 @@ void enqueue_count(gc_graph* G, int nv, int radius, long long* state_d, BatchWor
   if (timed) HIPCHK(hipEventRecord(G->ev[1], s));
   launch_count(nv, A, s, timed ? &G->ev[2] : nullptr);
   if (tv)
-    launch_tv_region(nv, A.R, G->rlist.as<int32_t>(), G->ctr.as<unsigned long long>(), G->dTs.as<unsigned long long>(),
+    launch_tv_region(nv, P, A.R, G->level.as<int32_t>(), radius, G->rlist.as<int32_t>(), G->ctr.as<unsigned long long>(), G->dTs.as<unsigned long long>(),
                      G->Tv.as<long long>(), G->bstats.as<unsigned long long>(), s);
   launch_combine(nv, G->sig.as<unsigned long long>(), state_d, G->vout.as<long long>(), G->k,
                  G->bstats.as<unsigned long long>(), s);
@@ -545,7 +553,7 @@ void enqueue_purge(gc_graph* G, BatchWork& W, int64_t max_touched, int nv) {
   if (G->pass_insert_only)
     launch_purge_insert_only(G->pd(), W, max_touched, G->pass_max_dirA, G->bits, skip, G->stream);
   else
-    launch_purge(G->pd(), W, max_touched, G->bits, 1u << (GC_VSHIFT + nv - 1), skip, G->scan_tmp.p, G->stream);
+    launch_purge(G->pd(), W, max_touched, max_touched, G->bits, 1u << (GC_VSHIFT + nv - 1), skip, G->scan_tmp.p, G->stream);
 }
 
 // After a pass whose results are in the pinned buffer: while a kernel asked
@@ -622,6 +630,7 @@ BatchWork make_work(gc_graph* G, const Staging& S) {
   W.tlen = S.tlen;
   W.tpre = S.tpre;
   W.scratch = G->scratch.as<uint32_t>();
+  W.scratch_t = G->scratch_t.as<uint32_t>();
   return W;
 }
 
@@ -643,7 +652,7 @@ void alloc_vertex_arrays(gc_graph* G) {
   G->ctr.ensure(C_COUNT * sizeof(unsigned long long));
   G->bstats.ensure(BS_COUNT * sizeof(unsigned long long));
   G->top.ensure(sizeof(unsigned long long));
-  for (DevBuf* b : {&G->Tv, &G->dTs, &G->sbt}) {
+  for (DevBuf* b : {&G->Tv, &G->dTs}) {
     b->ensure(N * sizeof(long long));
     fill_u64(b->as<unsigned long long>(), 0ull, N, s);
   }
@@ -655,7 +664,7 @@ void alloc_vertex_arrays(gc_graph* G) {
 void compact(gc_graph* G, int64_t extra) {
   hipStream_t s = G->stream;
   const int64_t N = G->N;
-  DevBuf ncap, noff, ncol;
+  DevBuf ncap, noff, ncol, ntt;
   ncap.ensure(N * sizeof(int32_t));
   noff.ensure((N + 1) * sizeof(int64_t));
   PoolDev P = G->pd();
@@ -668,9 +677,11 @@ void compact(gc_graph* G, int64_t extra) {
   G->sync();
   int64_t capn = std::max<int64_t>(4 * used, used + extra + (1 << 20));
   ncol.ensure((size_t)capn * sizeof(uint32_t));
-  launch_compact(G->pd(), noff.as<int64_t>(), ncol.as<uint32_t>(), s);
+  ntt.ensure((size_t)capn * sizeof(uint32_t));
+  launch_compact(G->pd(), noff.as<int64_t>(), ncol.as<uint32_t>(), ntt.as<uint32_t>(), s);
   G->sync();
   G->col.swap(ncol);
+  G->tt.swap(ntt);
   G->off.swap(noff);
   G->cap.swap(ncap);
   G->arena_cap = capn;
@@ -785,82 +796,89 @@ void build(gc_graph* G, int32_t k, const int64_t* n, const int32_t* const* src, 
     HIPCHK(hipMemcpyAsync(G->gid.p, gid.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, s));
     G->sync();
   }
+  // the build's transient arrays, in one allocation
+  DevBuf tmp;
+  const size_t M1 = (size_t)std::max<int64_t>(M, 1);
+  const size_t sizes[] = {M1 * 4, M1 * 4, (size_t)(k + 1) * 8, (size_t)k * 8, M1 * 8, M1 * 8, M1 * 8, (size_t)N * 4,
+                          (size_t)N * 8, (size_t)N * 8, 2 * M1 * 8, 2 * M1 * 8, (size_t)(N + 1) * 8};
+  char* part[sizeof(sizes) / sizeof(sizes[0])];
+  size_t tmp_bytes = 0;
+  for (size_t b : sizes) tmp_bytes += (b + 255) & ~(size_t)255;
+  tmp.ensure(tmp_bytes);
+  {
+    char* at = tmp.as<char>();
+    for (size_t j = 0; j < sizeof(sizes) / sizeof(sizes[0]); ++j) {
+      part[j] = at;
+      at += (sizes[j] + 255) & ~(size_t)255;
+    }
+  }
+  int32_t *esrc = (int32_t*)part[0], *edst = (int32_t*)part[1], *deg = (int32_t*)part[7];
+  int64_t *seg = (int64_t*)part[2], *gb = (int64_t*)part[3], *rstart = (int64_t*)part[12];
+  unsigned long long *ek = (unsigned long long*)part[4], *ek2 = (unsigned long long*)part[5];
+  unsigned long long *uniq = (unsigned long long*)part[6], *rk = (unsigned long long*)part[8];
+  unsigned long long *rk2 = (unsigned long long*)part[9], *dir = (unsigned long long*)part[10];
+  unsigned long long* dir2 = (unsigned long long*)part[11];
   // upload the edge lists and the segment tables
-  DevBuf esrc, edst, seg, gb;
-  esrc.ensure(std::max<int64_t>(M, 1) * sizeof(int32_t));
-  edst.ensure(std::max<int64_t>(M, 1) * sizeof(int32_t));
   std::vector<int64_t> hseg(k + 1, 0);
   for (int g = 0; g < k; ++g) {
     hseg[g + 1] = hseg[g] + m[g];
     if (m[g]) {
-      HIPCHK(hipMemcpyAsync(esrc.as<int32_t>() + hseg[g], src[g], m[g] * sizeof(int32_t), hipMemcpyHostToDevice, s));
-      HIPCHK(hipMemcpyAsync(edst.as<int32_t>() + hseg[g], dst[g], m[g] * sizeof(int32_t), hipMemcpyHostToDevice, s));
+      HIPCHK(hipMemcpyAsync(esrc + hseg[g], src[g], m[g] * sizeof(int32_t), hipMemcpyHostToDevice, s));
+      HIPCHK(hipMemcpyAsync(edst + hseg[g], dst[g], m[g] * sizeof(int32_t), hipMemcpyHostToDevice, s));
     }
   }
-  seg.ensure((k + 1) * sizeof(int64_t));
-  gb.ensure(k * sizeof(int64_t));
-  HIPCHK(hipMemcpyAsync(seg.p, hseg.data(), (k + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(gb.p, G->gbase.data(), k * sizeof(int64_t), hipMemcpyHostToDevice, s));
+  HIPCHK(hipMemcpyAsync(seg, hseg.data(), (k + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s));
+  HIPCHK(hipMemcpyAsync(gb, G->gbase.data(), k * sizeof(int64_t), hipMemcpyHostToDevice, s));
 
   zero_small(G);
-  DevBuf ek, ek2, uniq, deg;
-  ek.ensure(std::max<int64_t>(M, 1) * 8);
-  ek2.ensure(std::max<int64_t>(M, 1) * 8);
-  uniq.ensure(std::max<int64_t>(M, 1) * 8);
-  deg.ensure(N * sizeof(int32_t));
-  fill_u32(deg.as<uint32_t>(), 0u, N, s);
+  fill_u32((uint32_t*)deg, 0u, N, s);
   G->sort_tmp.ensure(radix_sort_tmp_bytes(std::max<int64_t>(2 * M, N)) + 64);
-  launch_init_keys(esrc.as<int32_t>(), edst.as<int32_t>(), M, seg.as<int64_t>(), gb.as<int64_t>(), k, G->bits,
-                   ek.as<unsigned long long>(), s);
+  launch_init_keys(esrc, edst, M, seg, gb, k, G->bits,
+                   ek, s);
   unsigned long long* sk =
-      radix_sort_u64(ek.as<unsigned long long>(), ek2.as<unsigned long long>(), G->sort_tmp.p, M, nullptr,
+      radix_sort_u64(ek, ek2, G->sort_tmp.p, M, nullptr,
                      2 * G->bits, s);
-  launch_init_unique(sk, M, G->bits, uniq.as<unsigned long long>(), G->ctr.as<unsigned long long>(),
-                     deg.as<int32_t>(), s);
+  launch_init_unique(sk, M, G->bits, uniq, G->ctr.as<unsigned long long>(),
+                     deg, s);
   // rank: (graph, degree, local id)
   G->ext2int.ensure(N * sizeof(int32_t));
   G->int2ext.ensure(N * sizeof(int32_t));
-  DevBuf rk, rk2;
-  rk.ensure(N * 8);
-  rk2.ensure(N * 8);
-  launch_rank(deg.as<int32_t>(), G->gid.as<int32_t>(), gb.as<int64_t>(), N, lbits, gbits + 2 * lbits,
-              rk.as<unsigned long long>(), rk2.as<unsigned long long>(), G->sort_tmp.p, G->ext2int.as<int32_t>(),
+  launch_rank(deg, G->gid.as<int32_t>(), gb, N, lbits, gbits + 2 * lbits,
+              rk, rk2, G->sort_tmp.p, G->ext2int.as<int32_t>(),
               G->int2ext.as<int32_t>(), s);
   // directed entries in internal ids
-  DevBuf dir, dir2;
-  dir.ensure(std::max<int64_t>(2 * M, 1) * 8);
-  dir2.ensure(std::max<int64_t>(2 * M, 1) * 8);
   G->len.ensure(N * sizeof(int32_t));
   fill_u32(G->len.as<uint32_t>(), 0u, N, s);
-  launch_init_dir(uniq.as<unsigned long long>(), M, G->ctr.as<unsigned long long>(), G->bits, G->ext2int.as<int32_t>(),
-                  dir.as<unsigned long long>(), G->len.as<int32_t>(), s);
+  launch_init_dir(uniq, M, G->ctr.as<unsigned long long>(), G->bits, G->ext2int.as<int32_t>(),
+                  dir, G->len.as<int32_t>(), s);
   unsigned long long mu = 0;
   HIPCHK(hipMemcpyAsync(&mu, G->ctr.as<unsigned long long>() + C_DIRA, 8, hipMemcpyDeviceToHost, s));
   G->sync();
   const int64_t nd = 2 * (int64_t)mu;
-  unsigned long long* sd = radix_sort_u64(dir.as<unsigned long long>(), dir2.as<unsigned long long>(), G->sort_tmp.p,
+  unsigned long long* sd = radix_sort_u64(dir, dir2, G->sort_tmp.p,
                                           nd, nullptr, 2 * G->bits, s);
   // rows with slack
   G->cap.ensure(N * sizeof(int32_t));
   G->off.ensure((N + 1) * sizeof(int64_t));
-  DevBuf rstart;
-  rstart.ensure((N + 1) * sizeof(int64_t));
   G->scan_tmp.ensure(scan_tmp_bytes(N + 1) + 64);
   PoolDev P = G->pd();
   launch_caps(P, G->opt.slack, s);
-  exclusive_scan_i32_to_i64(P.len, rstart.as<int64_t>(), N, G->scan_tmp.p, s);
+  exclusive_scan_i32_to_i64(P.len, rstart, N, G->scan_tmp.p, s);
   exclusive_scan_i32_to_i64(P.cap, P.off, N, G->scan_tmp.p, s);
   int64_t used = 0;
   HIPCHK(hipMemcpyAsync(&used, P.off + N, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   G->sync();
   G->arena_cap = std::max<int64_t>(4 * used, used + (1 << 20));
   G->col.ensure((size_t)G->arena_cap * sizeof(uint32_t));
+  G->tt.ensure((size_t)G->arena_cap * sizeof(uint32_t));
   G->arena_top = used;
   HIPCHK(hipMemcpyAsync(G->top.p, &G->arena_top, sizeof(int64_t), hipMemcpyHostToDevice, s));
   P = G->pd();
-  launch_init_csr(P, sd, nd, G->ctr.as<unsigned long long>(), G->bits, rstart.as<int64_t>(), G->opt.slack,
+  launch_init_csr(P, sd, nd, G->ctr.as<unsigned long long>(), G->bits, rstart, G->opt.slack,
                   G->scan_tmp.p, GC_F_NEW, s);
-  // the fill kernel reads the number of edges from ctr[C_DIRA]
+  // the fill kernel reads the number of edges from ctr[C_DIRA]; the
+  // transient arrays go before the region arrays come
+  tmp.release();
   // count: whole graph, version b empty
   fill_u64((unsigned long long*)G->state.p, 0ull, (int64_t)k * ST_STRIDE, s);
   zero_small(G);
@@ -869,6 +887,7 @@ void build(gc_graph* G, int32_t k, const int64_t* n, const int32_t* const* src, 
   // the merge's copy of the touched rows, as large as the region view, so
   // that a batch can be applied without growing it
   G->scratch.ensure(std::max<int64_t>(G->e_alloc, 1) * 4);
+  G->scratch_t.ensure(std::max<int64_t>(G->e_alloc, 1) * 4);
   // sort and scan temporaries for batches up to the allocation-free limit
   // (2^18 insertions and 2^18 deletions: 2^20 touched rows at most)
   G->sort_tmp.ensure(radix_sort_tmp_bytes(std::max<int64_t>(std::max<int64_t>(2 * M, N), 1 << 20)) + 64);
@@ -952,12 +971,6 @@ void check_batch(const gc_batch_desc& b, int64_t n, int which, const uint8_t* de
             (long long)i, (long long)n);
 }
 
-int64_t pow2_at_least(int64_t x) {
-  int64_t p = 1;
-  while (p < x) p <<= 1;
-  return p;
-}
-
 // Host-side sizes of one pass.  Array layouts and grids use the capacities
 // (powers of two), so passes whose batches fall in the same capacity class
 // enqueue the same work and can replay one captured graph.
@@ -993,16 +1006,16 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
   D.dd = G->dver.as<int32_t>();
   D.Tv = G->Tv.as<long long>();
   D.dT = G->dTs.as<unsigned long long>();
-  D.sbt = G->sbt.as<unsigned long long>();
   D.ce = G->ce.as<unsigned long long>();
   D.ce_cap = (int64_t)(G->ce.cap / 8);
-  D.ae = G->ae.as<unsigned long long>();
-  D.ae_alt = G->ae_alt.as<unsigned long long>();
+  D.e_ns = G->e_ns.as<int32_t>();
+  D.e_dt = G->e_dt.as<int32_t>();
+  D.e_kw = G->e_kw.as<int64_t>();
+  D.hk = G->hk.as<unsigned long long>();
+  D.hd = G->hd.as<int32_t>();
+  D.hmask = G->hmask;
+  D.hl = G->hl.as<unsigned long long>();
   D.ae_cap = G->ae_cap;
-  D.sort_tmp = G->sort_tmp.p;
-  D.slot_mark = G->c4_dense.as<unsigned long long>();
-  D.slot_list = G->slot_list.as<uint32_t>();
-  D.slot_cap = G->slot_cap;
   D.dc = G->dctr.as<unsigned long long>();
   D.c4_nch = G->c4_nch.as<int32_t>();
   D.c4_side = G->c4_side.as<int32_t>();
@@ -1012,9 +1025,7 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
   D.pair_edge = G->pair_edge.as<int32_t>();
   D.pair_idx = G->pair_idx.as<int32_t>();
   D.pair_len = G->pair_len.as<int32_t>();
-  D.k4_s = G->k4_s.as<uint32_t>();
-  D.k4_edge = G->k4_edge.as<int64_t>();
-  D.k4_item = G->k4_item.as<int32_t>();
+  D.slist = G->slist.as<uint32_t>();
   D.tv_items = G->tv_items.as<int32_t>();
   D.tv_ioff = G->tv_ioff.as<int64_t>();
   D.tcap = 2 * (int64_t)(G->ce.cap / 8);
@@ -1028,37 +1039,38 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
 
 // Buffers of an edge-local pass for batches of capacity cap_t (allocates:
 // never called during stream capture).
-void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t slot_need, int64_t pair_need = 0) {
+void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t pair_need) {
   const int64_t ce_cap = std::max<int64_t>(cap_t, 64);
   G->ce.ensure(ce_cap * 8);
-  G->c4_nch.ensure(G->ce.cap / 8 * 4);
-  G->c4_side.ensure(G->ce.cap / 8 * 4);
-  G->c4_low.ensure(G->ce.cap / 8 * 4);
-  G->c4_off.ensure((G->ce.cap / 8 + 1) * 8);
+  const int64_t ce = (int64_t)(G->ce.cap / 8);
+  for (DevBuf* b : {&G->c4_nch, &G->c4_side, &G->c4_low, &G->e_ns, &G->e_dt}) b->ensure(ce * 4);
+  G->e_kw.ensure(ce * 8);
+  G->c4_off.ensure((ce + 1) * 8);
   G->pair_cap = std::max<int64_t>(G->pair_cap, std::max<int64_t>(pair_need, 64 * cap_t + 4096));
-  G->pair_edge.ensure(G->pair_cap * 4);
-  G->pair_idx.ensure(G->pair_cap * 4);
-  G->pair_len.ensure(G->pair_cap * 4);
-  G->pair_hlen.ensure(G->pair_cap * 4);
-  G->pair_hoff.ensure((G->pair_cap + 1) * 8);
-  G->k4_s.ensure(K4_HS_CAP * 4);
-  G->k4_edge.ensure(K4_HE_CAP * 3 * 8);
-  G->k4_item.ensure(K4_IT_CAP * 2 * 4);
+  for (DevBuf* b : {&G->pair_edge, &G->pair_idx, &G->pair_len, &G->pair_hlen}) b->ensure(2 * G->pair_cap * 4);
+  for (DevBuf* b : {&G->pair_off, &G->pair_hoff}) b->ensure((2 * G->pair_cap + 1) * 8);
+  G->slist.ensure(G->pair_cap * 4);
   // touched rows: at most both ends of every change
-  G->tv_items.ensure(2 * (G->ce.cap / 8) * 4);
-  G->tv_ioff.ensure((2 * (G->ce.cap / 8) + 1) * 8);
-  G->pair_off.ensure((G->pair_cap + 1) * 8);
-  G->scan_tmp.ensure(scan_tmp_bytes(std::max<int64_t>(2 * (G->ce.cap / 8), G->pair_cap) + 1) + 64);
+  G->tv_items.ensure(2 * ce * 4);
+  G->tv_ioff.ensure((2 * ce + 1) * 8);
+  G->scan_tmp.ensure(scan_tmp_bytes(std::max<int64_t>(2 * ce, 2 * G->pair_cap) + 1) + 64);
+  // affected edges: the list, and a table at most two thirds full (free
+  // between passes)
   G->ae_cap = std::max<int64_t>(G->ae_cap, std::max<int64_t>(ae_need, 8 * cap_t + 4096));
-  G->ae.ensure(G->ae_cap * 8);
-  G->ae_alt.ensure(G->ae_cap * 8);
-  G->sort_tmp.ensure(radix_sort_tmp_bytes(G->ae_cap) + 64);
-  G->slot_cap = std::max<int64_t>(G->slot_cap, std::max<int64_t>(slot_need, 4096));
-  G->slot_list.ensure((size_t)std::max(1, G->c4_slots) * G->slot_cap * 4);
+  G->hl.ensure(G->ae_cap * 8);
+  const int64_t slots = pow2_at_least(G->ae_cap + G->ae_cap / 2);
+  if (slots > (int64_t)G->hmask + 1 || !G->hk.p) {
+    G->hmask = 0;
+    G->hk.ensure(slots * 8);
+    G->hd.ensure(slots * 4);
+    G->hmask = (uint32_t)(slots - 1);
+    fill_u64(G->hk.as<unsigned long long>(), 0ull, slots, G->stream);
+    fill_u32(G->hd.as<uint32_t>(), 0u, slots, G->stream);
+  }
 }
 
-// After an edge-local pass whose affected-edge list or common-neighbour slot
-// was too small (the combine and the purge then changed nothing): grow them
+// After an edge-local pass whose affected-edge table or pair lists
+// were too small (the combine and the purge then changed nothing): grow them
 // from the sizes the kernels asked for and run the stage again.
 int settle_delta(gc_graph* G, const PassPlan& L, BatchWork& W);
 
@@ -1180,7 +1192,7 @@ void enqueue_pass(gc_graph* G, const PassPlan& L, BatchIn& B, BatchWork& W, cons
   if (!ins_only) launch_flag_rows(P, W, 2 * L.cap_d, G->bits, bst, s);
   if (L.delta) {
     if (timed) HIPCHK(hipEventRecord(G->ev[1], s));
-    launch_delta(make_delta_args(G, W), G->c4_slots, s);
+    launch_delta(make_delta_args(G, W), s);
     if (timed)
       for (int e = 2; e <= 7; ++e) HIPCHK(hipEventRecord(G->ev[e], s));
     launch_combine(2, G->sig.as<unsigned long long>(), G->state.as<long long>(), G->vout.as<long long>(), G->k, bst, s);
@@ -1205,11 +1217,14 @@ int settle_delta(gc_graph* G, const PassPlan& L, BatchWork& W) {
     const double tot = (double)std::max<int64_t>(L.total, 1);
     G->ae_per_update = std::max(G->ae_per_update, (double)dc[DC_AFF_NEED] / tot);
     G->pair_per_update = std::max(G->pair_per_update, (double)dc[DC_PAIR_NEED] / tot);
+    // what the stopped attempt left in the tables goes, then they may grow
+    fill_u64(G->hk.as<unsigned long long>(), 0ull, (int64_t)G->hmask + 1, s);
+    fill_u32(G->hd.as<uint32_t>(), 0u, (int64_t)G->hmask + 1, s);
+    fill_u64(G->dTs.as<unsigned long long>(), 0ull, G->N, s);
     size_delta(G, L.cap_t, (int64_t)dc[DC_AFF_NEED] + (int64_t)dc[DC_AFF_NEED] / 4,
-               (int64_t)dc[DC_SLOT_NEED] + (int64_t)dc[DC_SLOT_NEED] / 4,
                (int64_t)dc[DC_PAIR_NEED] + (int64_t)dc[DC_PAIR_NEED] / 4);
     reset_count_stage(G);
-    launch_delta(make_delta_args(G, W), G->c4_slots, s);
+    launch_delta(make_delta_args(G, W), s);
     launch_combine(2, G->sig.as<unsigned long long>(), G->state.as<long long>(), G->vout.as<long long>(), G->k,
                    G->bstats.as<unsigned long long>(), s);
     enqueue_purge(G, W, L.max_touched, 2);
@@ -1227,7 +1242,7 @@ std::vector<uint64_t> pass_signature(gc_graph* G, const PassPlan& L, const Count
                              (uint64_t)A.c4_dense_min, (uint64_t)A.c4_win, (uint64_t)A.c4_narrow_max, (uint64_t)A.c4_ref,
                              (uint64_t)A.c4_maxlow, (uint64_t)A.slots, (uint64_t)A.tri_cap, (uint64_t)A.e_max,
                              (uint64_t)G->arena_cap, (uint64_t)L.in_bytes, (uint64_t)G->k, (uint64_t)G->N,
-                             (uint64_t)G->bits, (uint64_t)L.delta, (uint64_t)G->ae_cap, (uint64_t)G->slot_cap,
+                             (uint64_t)G->bits, (uint64_t)L.delta, (uint64_t)G->ae_cap, (uint64_t)G->hmask,
                              (uint64_t)G->ce.cap, (uint64_t)G->pair_cap, (uint64_t)(L.ndl == 0),
                              (uint64_t)G->tiers_now[0], (uint64_t)G->tiers_now[1], (uint64_t)G->tiers_now[2]};
   const DevBuf* bufs[] = {&G->off, &G->len, &G->cap, &G->col, &G->top, &G->gid, &G->ext2int, &G->state, &G->vout,
@@ -1237,8 +1252,9 @@ std::vector<uint64_t> pass_signature(gc_graph* G, const PassPlan& L, const Count
                           &G->sort_tmp, &G->scan_tmp, &G->roff, &G->rcol, &G->rrow, &G->rlow, &G->dver, &G->t,
                           &G->tp, &G->vpos, &G->level, &G->rlist, &G->rlen, &G->lists, &G->c4_dense, &G->c4_touch,
                           &G->c4_cur, &G->c4_blk, &G->c4_keys, &G->c4_keys_alt, &G->tri_scratch, &G->Tv, &G->dTs,
-                          &G->sbt, &G->ce, &G->ae, &G->ae_alt, &G->slot_list, &G->dctr, &G->c4_nch, &G->c4_side,
-                          &G->c4_low, &G->c4_off, &G->pair_edge, &G->pair_idx, &G->pair_len, &G->pair_off, &G->dead_d, &G->pair_hlen, &G->pair_hoff, &G->k4_s, &G->k4_edge, &G->k4_item, &G->tv_items,
+                          &G->ce, &G->hk, &G->hd, &G->hl, &G->e_ns, &G->e_dt, &G->e_kw, &G->slist, &G->dctr,
+                          &G->c4_nch, &G->c4_side, &G->c4_low, &G->c4_off, &G->pair_edge, &G->pair_idx, &G->pair_len,
+                          &G->pair_off, &G->pair_hlen, &G->pair_hoff, &G->tt, &G->scratch_t, &G->dead_d, &G->tv_items,
                           &G->tv_ioff};
   for (const DevBuf* b : bufs) v.push_back((uint64_t)(uintptr_t)b->p);
   v.push_back((uint64_t)(uintptr_t)G->pin);
@@ -1331,19 +1347,16 @@ void apply(gc_graph* G, const gc_batch_desc* b, int nb, bool dev, bool seq, int6
   G->tlen.ensure(L.max_touched * 4);
   G->tpre.ensure((L.max_touched + 1) * 8);
   G->scratch.ensure(std::max<int64_t>(L.union_bound, 1) * 4);
+  G->scratch_t.ensure(std::max<int64_t>(L.union_bound, 1) * 4);
   G->sort_tmp.ensure(radix_sort_tmp_bytes(std::max<int64_t>(std::max(L.cap_t, 2 * std::max(L.cap_i, L.cap_d)), G->N)) +
                      64);
   G->scan_tmp.ensure(scan_tmp_bytes(std::max<int64_t>(L.max_touched, G->N) + 1) + 64);
   size_count_scratch(G, L.nv, L.union_bound);
   if (L.delta) {
     // at the demand per update seen so far (within 2^26 entries a list: a
-    // larger demand is met by the retry, which sizes for the batch at hand);
-    // a common-neighbour slot holds the shorter row of a changed edge, at
-    // most about the largest lower degree counted (ids follow the degree
-    // order, so a hub's neighbours are nearly all below it)
+    // larger demand is met by the retry, which sizes for the batch at hand)
     const double lim = (double)(1ll << 26);
     size_delta(G, L.cap_t, (int64_t)std::min(lim, 1.25 * G->ae_per_update * (double)L.cap_t),
-               std::min<int64_t>(1ll << 26, G->seen_maxlow + G->seen_maxlow / 4 + 64),
                (int64_t)std::min(lim, 1.25 * G->pair_per_update * (double)L.cap_t));
   }
   // arena reserve: enough for every touched row to move
@@ -1637,7 +1650,8 @@ void apply_noalloc(gc_graph* G, const int32_t* iu, const int32_t* iv, int64_t n_
   const int64_t arena_need = (int64_t)((1.0 + G->opt.slack) * (double)L.union_bound) + 8 * L.max_touched + 1024;
   const char* short_of = G->sort_tmp.cap < sort_need                                          ? "sort temporaries"
                          : G->scan_tmp.cap < scan_need                                        ? "scan temporaries"
-                         : G->scratch.cap < (size_t)std::max<int64_t>(L.union_bound, 4) * 4 ? "merge scratch"
+                         : std::min(G->scratch.cap, G->scratch_t.cap) < (size_t)std::max<int64_t>(L.union_bound, 4) * 4
+                             ? "merge scratch"
                          : count_scratch_short(G, 2, L.union_bound)                           ? count_scratch_short(G, 2, L.union_bound)
                          : G->arena_cap - G->arena_top < arena_need                           ? "resident rows"
                                                                                               : nullptr;
@@ -1676,7 +1690,7 @@ void apply_noalloc(gc_graph* G, const int32_t* iu, const int32_t* iv, int64_t n_
       // counting needs more scratch: undo the merge, keep the graph as it was
       unsigned long long* bst = G->bstats.as<unsigned long long>();
       fill_u64(bst + BS_RETRY, 0ull, 1, s);
-      launch_purge(G->pd(), W, L.max_touched, G->bits, 0u, bst + BS_RETRY, G->scan_tmp.p, s, true);
+      launch_purge(G->pd(), W, L.max_touched, L.max_touched, G->bits, 0u, bst + BS_RETRY, G->scan_tmp.p, s, true);
       G->sync();
       G->arena_top = (int64_t)*G->out_top();
       G->in_pass = false;

@@ -70,7 +70,7 @@ enum {
   BS_TRI_GLOBAL,  // vertices counted by the global-scratch triangle tier
   BS_TRI_REBUILD, // vertices whose version-specific edges overflowed the exception list
   BS_TRI_E,       // adjacency entries the triangle tiers read: N+(u) and the lists N+(v) probed
-  BS_K4_SPLIT,    // changed edges whose edge-local 4-cliques were split into chunks
+  BS_K4_SPLIT,    // changed edges whose edge-local 4-cliques were spread over workgroups in chunks
   BS_COUNT
 };
 
@@ -80,6 +80,7 @@ struct PoolDev {
   int32_t* len;        // [N]
   int32_t* cap;        // [N]
   uint32_t* col;       // [arena_cap]
+  uint32_t* tt;        // [arena_cap] triangles through the edge, at the entry in the row of its smaller end
   int64_t arena_cap;
   unsigned long long* arena_top;  // bump pointer (device scalar)
   int32_t* gid;        // [N] graph of each internal vertex
@@ -157,6 +158,32 @@ __device__ __forceinline__ int64_t upper_bound_i64(const int64_t* pre, int64_t n
   while (hi - lo > 1) {
     int64_t mid = (lo + hi) >> 1;
     if (pre[mid] <= x) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// The same by an exponential search from i0 (pre[i0] <= x), for indexes that
+// lie close by.
+__device__ __forceinline__ int64_t upper_bound_from(const int64_t* __restrict__ pre, int64_t n, int64_t i0, int64_t x) {
+  int64_t lo = i0, step = 1;
+  while (lo + step < n && pre[lo + step] <= x) { lo += step; step <<= 1; }
+  int64_t hi = lo + step < n ? lo + step : n;  // pre[hi] > x or hi == n
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (pre[mid] <= x) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// The same for one x per wave, the lanes together: 64 samples a round.
+__device__ __forceinline__ int64_t wave_upper_bound(const int64_t* __restrict__ pre, int64_t n, int64_t x) {
+  int64_t lo = 0, hi = n;  // pre[lo] <= x, pre[hi] > x (or hi == n)
+  while (hi - lo > 1) {
+    const int64_t st = (hi - lo + 63) / 64;
+    const int64_t at = lo + st * (lane_id() + 1);
+    const int k = __popcll(__ballot(at < hi && pre[at < hi ? at : hi - 1] <= x));
+    hi = hi < lo + st * (k + 1) ? hi : lo + st * (k + 1);
+    lo = lo + st * k;
   }
   return lo;
 }

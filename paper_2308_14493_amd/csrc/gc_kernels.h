@@ -67,7 +67,8 @@ struct BatchWork {
   int32_t* a_beg; int32_t* na; int32_t* r_beg; int32_t* nr; int32_t* mark; int32_t* tix;  // [N]
   int32_t* touched;            // [max_touched]
   int64_t* dest; int32_t* newcap; int32_t* tlen; int64_t* tpre;  // [max_touched (+1)]
-  uint32_t* scratch;           // copy of the touched rows
+  uint32_t* scratch;           // copy of the touched rows (col)
+  uint32_t* scratch_t;         // and of their tt
 };
 
 // graph.hip
@@ -88,10 +89,11 @@ void launch_merge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int
 void launch_flag_rows(const PoolDev& P, const BatchWork& W, int64_t max_dirD, int bits, unsigned long long* bstats,
                       hipStream_t s);
 // removes the entries carrying `fin` (absent from the last version), clears
-// all flags; does nothing while *skip != 0.  undo: removes the entries new
+// all flags (rows that lose nothing: in place, max_dir bounds the
+// flagged entries); does nothing while *skip != 0.  undo: removes the entries new
 // in the pass instead (GC_F_NEW, listed in W.dirA), which restores the graph
 // as it was before a one-batch pass whose counting did not complete
-void launch_purge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int bits, uint32_t fin,
+void launch_purge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int64_t max_dir, int bits, uint32_t fin,
                   const unsigned long long* skip, void* scan_tmp, hipStream_t s, bool undo = false);
 // the purge of a pass without deletions: the flags of the new entries are
 // cleared in place (max_dirA bounds their count)
@@ -119,7 +121,7 @@ void launch_init_csr(const PoolDev& P, const unsigned long long* dir, int64_t ma
                      int64_t* rstart, float slack, void* scan_tmp, uint32_t flag, hipStream_t s);
 void launch_caps(const PoolDev& P, float slack, hipStream_t s);  // P.cap <- len + slack
 void launch_all_flags(const PoolDev& P, uint32_t set, uint32_t keep, hipStream_t s);
-void launch_compact(const PoolDev& P, int64_t* noff, uint32_t* ncol, hipStream_t s);
+void launch_compact(const PoolDev& P, int64_t* noff, uint32_t* ncol, uint32_t* ntt, hipStream_t s);
 void launch_upper_count(const PoolDev& P, int32_t* cnt, hipStream_t s);
 // rows of k vertices of a single graph (external ids): lengths, then the
 // edges (x, neighbour) in external ids at the exclusive prefix pre
@@ -176,17 +178,17 @@ void launch_combine(int nv, const unsigned long long* sig, long long* state, lon
 
 // capi.cpp: thread-local error text read by gc_last_error()
 // delta.hip: edge-local update of the Sigma terms of a one-batch pass
-enum { DC_EDGES = 0, DC_AFF, DC_AFF_TOTAL, DC_AFF_NEED, DC_SLOT_NEED, DC_QTRI, DC_QC4, DC_PAIR_NEED, DC_SEARCH,
-       DC_HS, DC_HITEMS, DC_HEAVY, DC_QK4, DC_QH, DC_QAFF, DC_COUNT };
-// 4-cliques of changed edges with many common neighbours, spread over the
-// workgroups in chunks: the common neighbours of such edges (with their
-// flags), the edges, and the chunks (fixed capacities; an edge that does not
-// fit is counted in place)
-constexpr int K4_HEAVY_MIN = 256;       // common neighbours from which an edge is split
-constexpr int K4_CHUNK = 64;            // common neighbours per chunk
-constexpr int64_t K4_HS_CAP = 1 << 22;  // stored common neighbours
-constexpr int64_t K4_HE_CAP = 1 << 14;  // split edges
-constexpr int64_t K4_IT_CAP = 1 << 18;  // chunks
+enum {
+  DC_EDGES = 0,  // changed pairs
+  DC_AFF,        // affected edges listed
+  DC_AFF_INST,   // moves of t of an affected edge (at least as many)
+  DC_AFF_FULL,   // the table of the affected edges was too full
+  DC_AFF_NEED, DC_PAIR_NEED,
+  DC_SEARCH,     // searched pairs
+  DC_WALK,       // walk lengths (twice the pairs)
+  DC_QH,         // queue of the walked chunks
+  DC_COUNT
+};
 constexpr int32_t TV_CHUNK = 4096;      // entries of a touched row per piece in the edge-local degree passes
 struct DeltaArgs {
   PoolDev P;                          // union view left by the tombstone merge
@@ -204,17 +206,18 @@ struct DeltaArgs {
   unsigned long long* bstats;         // BS_RETRY when a buffer below is too small
   int32_t* dd;                        // [N][2] degrees before / after of the touched rows
   long long* Tv;                      // [N] triangles at each vertex (moved to the graph after the batch)
-  unsigned long long* dT;             // [N] scratch, zero between passes: twice the change of T(v)
-  unsigned long long* sbt;            // [N] scratch, zero between passes: t before of affected edges at v
+  unsigned long long* dT;             // [N] scratch, zero between passes: the change of T(v)
   unsigned long long* ce;             // changed pairs (u < v) | nibble << 60
   int64_t ce_cap;
-  unsigned long long* ae;             // affected edge keys and their sort buffer
-  unsigned long long* ae_alt;
+  int32_t *e_ns, *e_dt;               // [ce_cap] per changed pair: common neighbours, change of t
+  int64_t* e_kw;                      // [ce_cap] and the entries of the common neighbours' rows
+  // affected edges: a hash table of resident positions + 1 (0: free; all free
+  // between passes) with the change of t, and the slots taken (slot | an end << 32)
+  unsigned long long* hk;             // [hmask + 1]
+  int32_t* hd;                        // [hmask + 1]
+  uint32_t hmask;
+  unsigned long long* hl;             // [ae_cap]
   int64_t ae_cap;
-  void* sort_tmp;                     // radix sort scratch for ae_cap keys
-  unsigned long long* slot_mark;      // [slots][N] dense marks, zero between uses
-  uint32_t* slot_list;                // [slots][slot_cap] common neighbours of a changed edge
-  int64_t slot_cap;
   unsigned long long* dc;             // [DC_COUNT] counters of the stage
   int32_t* c4_nch;                    // [ce_cap] pairs (e, a) per changed edge: degree of the end walked from
   int32_t* c4_side;                   // [ce_cap] bit 0: walk from v instead of u; bit 1: against a bitmap
@@ -223,25 +226,25 @@ struct DeltaArgs {
   int64_t* c4_off;                    // [ce_cap + 1] exclusive scan of c4_nch
   // searched pairs (DC_SEARCH of them): changed edge, index (below the degree
   // of the end walked from: pair (e, a), else (e, b)) and entries walked
-  int32_t *pair_edge, *pair_idx, *pair_len;  // [pair_cap]
-  uint32_t* k4_s;                     // [K4_HS_CAP] common neighbours of split edges: id | nibble(u, w) << 28 | nibble(v, w) << 30
-  int64_t* k4_edge;                   // [K4_HE_CAP][3] split edges: changed edge index, offset in k4_s, count
-  int32_t* k4_item;                   // [K4_IT_CAP][2] chunks: split edge (-1: none), chunk index
+  int32_t *pair_edge, *pair_idx, *pair_len;  // [2 pair_cap]
+  uint32_t* slist;                    // [pair_cap] S(e) at c4_off of e: id | nibble(s, w) << 28 | nibble(o, w) << 30
   int32_t* tv_items;                  // [tcap] pieces of each touched row (rows split in TV_CHUNK entries)
   int64_t* tv_ioff;                   // [tcap + 1] exclusive scan of tv_items
   int64_t tcap;                       // touched rows the two arrays cover (>= the touched count)
-  int64_t* pair_off;                  // [pair_cap + 1] exclusive scan of pair_len
-  int32_t* pair_hlen;                 // [pair_cap] entries of N(a) walked against the bitmap of N(o) (0: searched)
-  int64_t* pair_hoff;                 // [pair_cap + 1] exclusive scan of pair_hlen
+  int64_t* pair_off;                  // [2 pair_cap + 1] exclusive scan of pair_len
+  // entries walked against a bitmap: of N(a) per pair (e, a), then of the row
+  // of each member of the lists S(e) (same places)
+  int32_t* pair_hlen;                 // [2 pair_cap]
+  int64_t* pair_hoff;                 // [2 pair_cap + 1] exclusive scan of pair_hlen
   int64_t pair_cap;
-  void* scan_tmp;                     // scan scratch for max(ce_cap, pair_cap) + 1 entries
+  void* scan_tmp;                     // scan scratch for max(ce_cap, 2 pair_cap) + 1 entries
 };
-// launches the delta stage with `slots` workgroups for the per-edge kernels
-void launch_delta(const DeltaArgs& D, int slots, hipStream_t s);
-// T(v) of the region vertices after a region pass (t of the last version
-// minus t of version 0); dT zero before and after
-void launch_tv_region(int nv, const RegionDev& R, const int32_t* rlist, const unsigned long long* c,
-                      unsigned long long* dT, long long* Tv, unsigned long long* bstats, hipStream_t s);
+void launch_delta(const DeltaArgs& D, hipStream_t s);
+// T(v) of the region vertices and the resident t of its edges after a region
+// pass (t of the last version minus t of version 0); dT zero before and after
+void launch_tv_region(int nv, const PoolDev& P, const RegionDev& R, const int32_t* level, int32_t radius,
+                      const int32_t* rlist, const unsigned long long* c, unsigned long long* dT, long long* Tv,
+                      unsigned long long* bstats, hipStream_t s);
 
 void gc_set_error(const char* msg);
 // device bytes a single-graph handle reaches (capi.cpp); used by the server's admission

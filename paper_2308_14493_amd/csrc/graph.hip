@@ -164,7 +164,7 @@ __global__ void k_plan_rows(PoolDev P, const int32_t* __restrict__ touched, cons
     const int32_t r = touched[i];
     const int32_t add = na[r];
     const int32_t L = P.len[r];
-    tlen[i] = L;  // copied to scratch for the merge and again for the purge
+    tlen[i] = add ? L : 0;  // rows that grow are copied to scratch
     if (add == 0) { dest[i] = P.off[r]; newcap[i] = P.cap[r]; continue; }
     const int32_t nl = L + add;
     if (nl <= P.cap[r]) { dest[i] = P.off[r]; newcap[i] = P.cap[r]; continue; }
@@ -181,20 +181,37 @@ __global__ void k_plan_rows(PoolDev P, const int32_t* __restrict__ touched, cons
   }
 }
 
+// Entries [0, total) of the rows copied to scratch, 256 consecutive ones per
+// wave at a time (64 while that leaves waves idle), their first row found by
+// the wave, the others close by; f(index, touched row).  A binary search over
+// all touched rows per entry took 1.0 ms for a copy at scale 22 (40,000
+// updates).
+template <class F>
+__device__ __forceinline__ void copied_entries(const int64_t* __restrict__ tpre, int64_t nt, F f) {
+  const int64_t total = tpre[nt];
+  const int64_t per = total > gwaves() * 64 ? 256 : 64;
+  for (int64_t b0 = gwave() * per; b0 < total; b0 += gwaves() * per) {
+    int64_t t = wave_upper_bound(tpre, nt, b0);
+    for (int64_t i = b0 + lane_id(); i < total && i < b0 + per; i += 64) {
+      t = upper_bound_from(tpre, nt, t, i);
+      f(i, t);
+    }
+  }
+}
+
 // Flat copy of the touched rows into scratch (positions from tpre); skipped
 // while *skip != 0 (skip may be null).
 __global__ void k_copy_rows(PoolDev P, const int32_t* __restrict__ touched, const unsigned long long* c,
                             const int64_t* __restrict__ tpre, uint32_t* __restrict__ scratch,
-                            const unsigned long long* skip) {
+                            uint32_t* __restrict__ scratch_t, const unsigned long long* skip) {
   if (skip && *skip) return;
   const int64_t nt = ctr(c, C_TOUCH);
   if (nt == 0) return;
-  const int64_t total = tpre[nt];
-  for (int64_t i = gtid(); i < total; i += gstride()) {
-    const int64_t t = upper_bound_i64(tpre, nt, i);
-    const int32_t r = touched[t];
-    scratch[i] = P.col[P.off[r] + (i - tpre[t])];
-  }
+  copied_entries(tpre, nt, [&](int64_t i, int64_t t) {
+    const int64_t at = P.off[touched[t]] + (i - tpre[t]);
+    scratch[i] = P.col[at];
+    scratch_t[i] = P.tt[at];
+  });
 }
 
 // Merge: old entries shift right by the insertions before them; insertions
@@ -202,18 +219,16 @@ __global__ void k_copy_rows(PoolDev P, const int32_t* __restrict__ touched, cons
 // absence mask (at least F_NEW: absent before the pass).
 __global__ void k_merge_old(PoolDev P, const int32_t* __restrict__ touched, const unsigned long long* c,
                             const int64_t* __restrict__ tpre, const uint32_t* __restrict__ scratch,
-                            const unsigned long long* __restrict__ dirA, int bits,
-                            const int32_t* __restrict__ a_beg, const int32_t* __restrict__ na,
+                            const uint32_t* __restrict__ scratch_t, const unsigned long long* __restrict__ dirA,
+                            int bits, const int32_t* __restrict__ a_beg, const int32_t* __restrict__ na,
                             const int64_t* __restrict__ dest) {
   const int64_t nt = ctr(c, C_TOUCH);
   if (nt == 0) return;
-  const int64_t total = tpre[nt];
   const uint64_t idmask = (1ull << bits) - 1ull;
-  for (int64_t i = gtid(); i < total; i += gstride()) {
-    const int64_t t = upper_bound_i64(tpre, nt, i);
+  copied_entries(tpre, nt, [&](int64_t i, int64_t t) {
     const int32_t r = touched[t];
     const int32_t cntA = na[r];
-    if (cntA == 0 || dest[t] < 0) continue;
+    if (dest[t] < 0) return;
     const int64_t k = i - tpre[t];
     const uint32_t x = scratch[i];
     const uint32_t id = x & GC_ID;
@@ -221,7 +236,8 @@ __global__ void k_merge_old(PoolDev P, const int32_t* __restrict__ touched, cons
     int32_t lo = 0, hi = cntA;
     while (lo < hi) { int32_t mid = (lo + hi) >> 1; if ((uint32_t)(A[mid] & idmask) < id) lo = mid + 1; else hi = mid; }
     P.col[dest[t] + k + lo] = x;
-  }
+    P.tt[dest[t] + k + lo] = scratch_t[i];
+  });
 }
 
 __global__ void k_merge_new(PoolDev P, const unsigned long long* c, const unsigned long long* __restrict__ dirA,
@@ -241,6 +257,7 @@ __global__ void k_merge_new(PoolDev P, const unsigned long long* c, const unsign
     const int32_t L = (int32_t)(tpre[t + 1] - tpre[t]);
     int32_t p = lower_bound_id(old, L, id);
     P.col[dest[t] + q + p] = id | fl;
+    P.tt[dest[t] + q + p] = 0u;
   }
 }
 
@@ -277,38 +294,56 @@ __global__ void k_flag_rows(PoolDev P, const unsigned long long* c, const unsign
 // Remove the entries absent from the last version and clear every flag in
 // the touched rows (from a scratch copy of the union rows); reset the per-row
 // batch arrays.
+// Rows that lose entries are copied and compacted (nrem of them per row); the
+// others only lose their flags, in place (k_clear_flags).
 __global__ void k_touched_len(PoolDev P, const int32_t* __restrict__ touched, const unsigned long long* c,
-                              int64_t max_touched, int32_t* __restrict__ tlen, const unsigned long long* skip) {
+                              int64_t max_touched, const int32_t* __restrict__ nrem, int32_t* __restrict__ tlen,
+                              const unsigned long long* skip) {
   if (*skip) return;
   const int64_t nt = ctr(c, C_TOUCH);
-  for (int64_t i = gtid(); i < max_touched; i += gstride()) tlen[i] = i < nt ? P.len[touched[i]] : 0;
+  for (int64_t i = gtid(); i < max_touched; i += gstride())
+    tlen[i] = i < nt && nrem[touched[i]] ? P.len[touched[i]] : 0;
 }
 
 __global__ void k_purge_rows(PoolDev P, const int32_t* __restrict__ touched, const unsigned long long* c,
                              const int64_t* __restrict__ tpre, const uint32_t* __restrict__ scratch,
-                             const unsigned long long* __restrict__ dirR, int bits, uint32_t fin,
-                             const int32_t* __restrict__ r_beg, const int32_t* __restrict__ nr,
-                             const unsigned long long* skip) {
+                             const uint32_t* __restrict__ scratch_t, const unsigned long long* __restrict__ dirR,
+                             int bits, uint32_t fin, const int32_t* __restrict__ r_beg,
+                             const int32_t* __restrict__ nr, const unsigned long long* skip) {
   if (*skip) return;
   const int64_t nt = ctr(c, C_TOUCH);
   if (nt == 0) return;
-  const int64_t total = tpre[nt];
   const uint64_t idmask = (1ull << bits) - 1ull;
-  for (int64_t i = gtid(); i < total; i += gstride()) {
-    const int64_t t = upper_bound_i64(tpre, nt, i);
+  copied_entries(tpre, nt, [&](int64_t i, int64_t t) {
     const int32_t r = touched[t];
     const uint32_t x = scratch[i];
-    if (x & fin) continue;
+    if (x & fin) return;
     const int64_t k = i - tpre[t];
-    const int32_t cntD = nr[r];
-    int32_t lo = 0;
-    if (cntD) {
-      const unsigned long long* D = dirR + r_beg[r];
-      const uint32_t id = x & GC_ID;
-      int32_t hi = cntD;
-      while (lo < hi) { int32_t mid = (lo + hi) >> 1; if ((uint32_t)(D[mid] & idmask) < id) lo = mid + 1; else hi = mid; }
-    }
-    P.col[P.off[r] + k - lo] = x & GC_ID;
+    const unsigned long long* D = dirR + r_beg[r];
+    const uint32_t id = x & GC_ID;
+    int32_t lo = 0, hi = nr[r];
+    while (lo < hi) { int32_t mid = (lo + hi) >> 1; if ((uint32_t)(D[mid] & idmask) < id) lo = mid + 1; else hi = mid; }
+    const int64_t at = P.off[r] + k - lo;
+    P.col[at] = id;
+    P.tt[at] = scratch_t[i];
+  });
+}
+
+// Flags of the entries in the batch (lists dirA and dirD), in the rows that
+// lose nothing.
+__global__ void k_clear_flags(PoolDev P, const unsigned long long* __restrict__ dirA,
+                              const unsigned long long* __restrict__ dirD, const unsigned long long* c, int bits,
+                              const int32_t* __restrict__ nrem, const unsigned long long* skip) {
+  if (*skip) return;
+  const int64_t na = ctr(c, C_DIRA), n = na + ctr(c, C_DIRD);
+  const uint64_t idmask = (1ull << bits) - 1ull;
+  for (int64_t i = gtid(); i < n; i += gstride()) {
+    const unsigned long long key = (i < na ? dirA[i] : dirD[i - na]) & DIR_KEY_MASK;
+    const uint32_t r = (uint32_t)(key >> bits), id = (uint32_t)(key & idmask);
+    if (nrem[r]) continue;
+    uint32_t* row = P.col + P.off[r];
+    const int32_t p = lower_bound_id(row, P.len[r], id);
+    if (p < P.len[r] && (row[p] & GC_ID) == id) row[p] = id;
   }
 }
 
@@ -817,7 +852,9 @@ __global__ void k_init_fill(PoolDev P, const unsigned long long* __restrict__ di
   const uint64_t idmask = (1ull << bits) - 1ull;
   for (int64_t i = gtid(); i < n; i += gstride()) {
     const uint32_t r = (uint32_t)(dir[i] >> bits);
-    P.col[P.off[r] + (i - rstart[r])] = (uint32_t)(dir[i] & idmask) | flag;
+    const int64_t at = P.off[r] + (i - rstart[r]);
+    P.col[at] = (uint32_t)(dir[i] & idmask) | flag;
+    P.tt[at] = 0u;
   }
 }
 
@@ -835,12 +872,15 @@ __global__ void k_all_flags(PoolDev P, uint32_t set, uint32_t keep) {
 }
 
 // compaction: copy rows into a fresh arena with new offsets
-__global__ void k_compact_copy(PoolDev P, const int64_t* __restrict__ noff, uint32_t* __restrict__ ncol) {
+__global__ void k_compact_copy(PoolDev P, const int64_t* __restrict__ noff, uint32_t* __restrict__ ncol,
+                               uint32_t* __restrict__ ntt) {
   for (int64_t v = gwave(); v < P.N; v += gwaves()) {
-    const uint32_t* row = P.col + P.off[v];
-    uint32_t* out = ncol + noff[v];
+    const int64_t from = P.off[v], to = noff[v];
     const int32_t L = P.len[v];
-    for (int32_t k = lane_id(); k < L; k += 64) out[k] = row[k];
+    for (int32_t k = lane_id(); k < L; k += 64) {
+      ncol[to + k] = P.col[from + k];
+      ntt[to + k] = P.tt[from + k];
+    }
   }
 }
 
@@ -946,9 +986,9 @@ void launch_merge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int
   exclusive_scan_i32_to_i64(W.tlen, W.tpre, max_touched, scan_tmp, s);
   const unsigned g = 4096;
   hipLaunchKernelGGL(k_copy_rows, dim3(g), dim3(TPB), 0, s, P, W.touched, W.c, W.tpre, W.scratch,
-                     (const unsigned long long*)nullptr);
-  hipLaunchKernelGGL(k_merge_old, dim3(g), dim3(TPB), 0, s, P, W.touched, W.c, W.tpre, W.scratch, W.dirA, bits,
-                     W.a_beg, W.na, W.dest);
+                     W.scratch_t, (const unsigned long long*)nullptr);
+  hipLaunchKernelGGL(k_merge_old, dim3(g), dim3(TPB), 0, s, P, W.touched, W.c, W.tpre, W.scratch,
+                     W.scratch_t, W.dirA, bits, W.a_beg, W.na, W.dest);
   if (max_dirA)
     hipLaunchKernelGGL(k_merge_new, dim3(grid_for(max_dirA)), dim3(TPB), 0, s, P, W.c, W.dirA, bits, W.a_beg, W.tix,
                        W.tpre, W.scratch, W.dest);
@@ -962,7 +1002,7 @@ void launch_flag_rows(const PoolDev& P, const BatchWork& W, int64_t max_dirD, in
   hipLaunchKernelGGL(k_flag_rows, dim3(grid_for(max_dirD)), dim3(TPB), 0, s, P, W.c, W.dirD, bits, bstats);
 }
 
-void launch_purge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int bits, uint32_t fin,
+void launch_purge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int64_t max_dir, int bits, uint32_t fin,
                   const unsigned long long* skip, void* scan_tmp, hipStream_t s, bool undo) {
   if (max_touched == 0) return;
   // undo: keep version 0 instead of the last version (remove the new
@@ -974,11 +1014,12 @@ void launch_purge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int
   // lengths of the union rows, then a copy, then the compaction (the scan of
   // stale lengths under skip is harmless: nothing reads it)
   hipLaunchKernelGGL(k_touched_len, dim3(grid_for(max_touched)), dim3(TPB), 0, s, P, W.touched, W.c, max_touched,
-                     W.tlen, skip);
+                     rm_n, W.tlen, skip);
   exclusive_scan_i32_to_i64(W.tlen, W.tpre, max_touched, scan_tmp, s);
-  hipLaunchKernelGGL(k_copy_rows, dim3(4096), dim3(TPB), 0, s, P, W.touched, W.c, W.tpre, W.scratch, skip);
-  hipLaunchKernelGGL(k_purge_rows, dim3(4096), dim3(TPB), 0, s, P, W.touched, W.c, W.tpre, W.scratch, rm, bits,
-                     fin, rm_beg, rm_n, skip);
+  hipLaunchKernelGGL(k_copy_rows, dim3(4096), dim3(TPB), 0, s, P, W.touched, W.c, W.tpre, W.scratch, W.scratch_t, skip);
+  hipLaunchKernelGGL(k_purge_rows, dim3(4096), dim3(TPB), 0, s, P, W.touched, W.c, W.tpre, W.scratch, W.scratch_t, rm,
+                     bits, fin, rm_beg, rm_n, skip);
+  hipLaunchKernelGGL(k_clear_flags, dim3(grid_for(max_dir)), dim3(TPB), 0, s, P, W.dirA, W.dirD, W.c, bits, rm_n, skip);
   hipLaunchKernelGGL(k_purge_commit, dim3(grid_for(max_touched)), dim3(TPB), 0, s, P, W.touched, W.c, W.a_beg, W.na,
                      W.r_beg, W.nr, W.mark, W.tix, rm_n, skip);
 }
@@ -986,25 +1027,12 @@ void launch_purge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int
 // Purge of a pass without deletions (Alg. 1's insert-only batches): nothing
 // leaves the rows, so the new entries (listed in dirA) only lose their flags
 // in place; no row is copied or compacted.
-__global__ void k_clear_new(PoolDev P, const unsigned long long* __restrict__ dirA, const unsigned long long* c,
-                            int bits, const unsigned long long* skip) {
-  if (*skip) return;
-  const int64_t n = ctr(c, C_DIRA);
-  const uint64_t idmask = (1ull << bits) - 1ull;
-  for (int64_t i = gtid(); i < n; i += gstride()) {
-    const unsigned long long key = dirA[i] & DIR_KEY_MASK;
-    const uint32_t r = (uint32_t)(key >> bits), id = (uint32_t)(key & idmask);
-    uint32_t* row = P.col + P.off[r];
-    const int32_t p = lower_bound_id(row, P.len[r], id);
-    if (p < P.len[r] && (row[p] & GC_ID) == id) row[p] = id;
-  }
-}
-
 void launch_purge_insert_only(const PoolDev& P, const BatchWork& W, int64_t max_touched, int64_t max_dirA, int bits,
                               const unsigned long long* skip, hipStream_t s) {
   if (max_touched == 0) return;
   if (max_dirA > 0)
-    hipLaunchKernelGGL(k_clear_new, dim3(grid_for(max_dirA)), dim3(TPB), 0, s, P, W.dirA, W.c, bits, skip);
+    hipLaunchKernelGGL(k_clear_flags, dim3(grid_for(max_dirA)), dim3(TPB), 0, s, P, W.dirA, W.dirD, W.c, bits,
+                       (const int32_t*)W.nr, skip);
   hipLaunchKernelGGL(k_purge_commit, dim3(grid_for(max_touched)), dim3(TPB), 0, s, P, W.touched, W.c, W.a_beg, W.na,
                      W.r_beg, W.nr, W.mark, W.tix, (const int32_t*)W.nr, skip);
 }
@@ -1087,8 +1115,8 @@ void launch_caps(const PoolDev& P, float slack, hipStream_t s) {
 void launch_all_flags(const PoolDev& P, uint32_t set, uint32_t keep, hipStream_t s) {
   hipLaunchKernelGGL(k_all_flags, dim3(4096), dim3(TPB), 0, s, P, set, keep);
 }
-void launch_compact(const PoolDev& P, int64_t* noff, uint32_t* ncol, hipStream_t s) {
-  hipLaunchKernelGGL(k_compact_copy, dim3(4096), dim3(TPB), 0, s, P, noff, ncol);
+void launch_compact(const PoolDev& P, int64_t* noff, uint32_t* ncol, uint32_t* ntt, hipStream_t s) {
+  hipLaunchKernelGGL(k_compact_copy, dim3(4096), dim3(TPB), 0, s, P, noff, ncol, ntt);
 }
 void launch_upper_count(const PoolDev& P, int32_t* cnt, hipStream_t s) {
   hipLaunchKernelGGL(k_upper_count, dim3(4096), dim3(TPB), 0, s, P, cnt);
