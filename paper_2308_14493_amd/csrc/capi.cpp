@@ -211,7 +211,7 @@ struct gc_graph {
   std::vector<long long> hstate;
 
   // batch scratch
-  DevBuf bin, keys, keys_alt, dirA, dirA_alt, dirD, dirD_alt, dirR, dirR_alt;
+  DevBuf bin, keys, keys_alt, dirA, dirA_alt, dirD, dirR, dirR_alt;
   DevBuf a_beg, na, r_beg, nr, mark, tix;
   DevBuf touched, dest, newcap, tlen, tpre, scratch, scratch_t, sort_tmp, scan_tmp;
 
@@ -366,9 +366,8 @@ struct gc_graph {
 namespace {
 
 void zero_small(gc_graph* G) {
-  fill_u64(G->ctr.as<unsigned long long>(), 0ull, C_COUNT, G->stream);
-  fill_u64(G->bstats.as<unsigned long long>(), 0ull, BS_COUNT, G->stream);
-  fill_u64(G->sig.as<unsigned long long>(), 0ull, (int64_t)G->k * GC_NV_MAX * SG_N, G->stream);
+  zero3_u64(G->ctr.as<unsigned long long>(), C_COUNT, G->bstats.as<unsigned long long>(), BS_COUNT,
+            G->sig.as<unsigned long long>(), (int64_t)G->k * GC_NV_MAX * SG_N, G->stream);
 }
 
 // Before a second attempt of the counting stage: its counters, statistics
@@ -530,15 +529,30 @@ void enqueue_count(gc_graph* G, int nv, int radius, long long* state_d, BatchWor
                  G->bstats.as<unsigned long long>(), s);
 }
 
-// Results of a pass into the pinned buffer (enqueue only).
+// Results of a pass into the pinned buffer (enqueue only): one kernel that
+// writes host memory instead of five copies.
+__global__ void k_readback(const unsigned long long* ctr, const unsigned long long* bst, const long long* state,
+                           const long long* vout, const unsigned long long* top, int64_t st,
+                           unsigned long long* out) {
+  const int64_t n = C_COUNT + BS_COUNT + (1 + (GC_NV_MAX - 1)) * st + 1;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    int64_t j = i;
+    unsigned long long v;
+    if (j < C_COUNT) v = ctr[j];
+    else if ((j -= C_COUNT) < BS_COUNT) v = bst[j];
+    else if ((j -= BS_COUNT) < st) v = (unsigned long long)state[j];
+    else if ((j -= st) < (GC_NV_MAX - 1) * st) v = (unsigned long long)vout[j];
+    else v = *top;
+    out[i] = v;
+  }
+}
+
 void enqueue_readback(gc_graph* G, const long long* state_d) {
-  hipStream_t s = G->stream;
-  const size_t st = (size_t)G->k * ST_STRIDE * 8;
-  HIPCHK(hipMemcpyAsync(G->out_ctr(), G->ctr.p, C_COUNT * 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(G->out_bst(), G->bstats.p, BS_COUNT * 8, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(G->out_state(), state_d, st, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(G->out_vout(), G->vout.p, (GC_NV_MAX - 1) * st, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(G->out_top(), G->top.p, 8, hipMemcpyDeviceToHost, s));
+  const int64_t st = (int64_t)G->k * ST_STRIDE;
+  const int64_t n = C_COUNT + BS_COUNT + GC_NV_MAX * st + 1;
+  hipLaunchKernelGGL(k_readback, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256), 0, G->stream,
+                     G->ctr.as<unsigned long long>(), G->bstats.as<unsigned long long>(), state_d,
+                     G->vout.as<long long>(), G->top.as<unsigned long long>(), st, G->out_ctr());
 }
 
 void note_maxima(gc_graph* G) {
@@ -585,7 +599,7 @@ int settle_retries(gc_graph* G, int nv, int radius, long long* state_d, BatchWor
 struct Staging {
   void* bin = nullptr;
   unsigned long long *keys = nullptr, *keys_alt = nullptr, *dirA = nullptr, *dirA_alt = nullptr;
-  unsigned long long *dirD = nullptr, *dirD_alt = nullptr, *dirR = nullptr, *dirR_alt = nullptr;
+  unsigned long long *dirD = nullptr, *dirR = nullptr, *dirR_alt = nullptr;
   int32_t* touched = nullptr;
   int64_t* dest = nullptr;
   int32_t* newcap = nullptr;
@@ -601,7 +615,6 @@ Staging handle_staging(gc_graph* G) {
   S.dirA = G->dirA.as<unsigned long long>();
   S.dirA_alt = G->dirA_alt.as<unsigned long long>();
   S.dirD = G->dirD.as<unsigned long long>();
-  S.dirD_alt = G->dirD_alt.as<unsigned long long>();
   S.dirR = G->dirR.as<unsigned long long>();
   S.dirR_alt = G->dirR_alt.as<unsigned long long>();
   S.touched = G->touched.as<int32_t>();
@@ -1173,21 +1186,15 @@ void enqueue_pass(gc_graph* G, const PassPlan& L, BatchIn& B, BatchWork& W, cons
   }
   unsigned long long* sA = radix_sort_u64(S.dirA, S.dirA_alt, G->sort_tmp.p, 2 * L.cap_i, ctr + C_DIRA, 2 * G->bits, s);
   // a pass without deletions (insert-only batches, Alg. 1) has empty flag and
-  // removal lists: their sorts, marks and flag kernels are skipped
+  // removal lists: the sort of the second and the flag kernel are skipped
+  // (the flag list is in no order: nothing needs it sorted)
   const bool ins_only = L.ndl == 0;
-  unsigned long long* sD = ins_only ? W.dirD
-                                    : radix_sort_u64(S.dirD, S.dirD_alt, G->sort_tmp.p, 2 * L.cap_d, ctr + C_DIRD,
-                                                     2 * G->bits, s);
   unsigned long long* sR = ins_only ? W.dirR
                                     : radix_sort_u64(S.dirR, S.dirR_alt, G->sort_tmp.p, 2 * L.cap_d, ctr + C_DIRR,
                                                      2 * G->bits, s);
-  if (sA != W.dirA || sD != W.dirD || sR != W.dirR) raise(GC_EDEVICE, "sorted merge lists not where expected");
+  if (sA != W.dirA || sR != W.dirR) raise(GC_EDEVICE, "sorted merge lists not where expected");
   G->in_pass = true;  // from here on the resident graph holds the union view until the purge
-  launch_mark_rows(sA, 2 * L.cap_i, ctr, C_DIRA, G->bits, W.a_beg, W.na, W.mark, W.touched, W.tix, s);
-  if (!ins_only) {
-    launch_mark_rows(sD, 2 * L.cap_d, ctr, C_DIRD, G->bits, nullptr, nullptr, W.mark, W.touched, W.tix, s);
-    launch_mark_rows(sR, 2 * L.cap_d, ctr, C_DIRR, G->bits, W.r_beg, W.nr, W.mark, W.touched, W.tix, s);
-  }
+  launch_mark_rows(W, 2 * L.cap_i + (ins_only ? 0 : 4 * L.cap_d), G->bits, s);
   launch_merge(P, W, L.max_touched, 2 * L.cap_i, G->bits, G->opt.slack, bst, G->scan_tmp.p, s);
   if (!ins_only) launch_flag_rows(P, W, 2 * L.cap_d, G->bits, bst, s);
   if (L.delta) {
@@ -1247,7 +1254,7 @@ std::vector<uint64_t> pass_signature(gc_graph* G, const PassPlan& L, const Count
                              (uint64_t)G->tiers_now[0], (uint64_t)G->tiers_now[1], (uint64_t)G->tiers_now[2]};
   const DevBuf* bufs[] = {&G->off, &G->len, &G->cap, &G->col, &G->top, &G->gid, &G->ext2int, &G->state, &G->vout,
                           &G->sig, &G->ctr, &G->bstats, &G->bin, &G->keys, &G->keys_alt, &G->dirA, &G->dirA_alt,
-                          &G->dirD, &G->dirD_alt, &G->dirR, &G->dirR_alt, &G->a_beg, &G->na, &G->r_beg, &G->nr,
+                          &G->dirD, &G->dirR, &G->dirR_alt, &G->a_beg, &G->na, &G->r_beg, &G->nr,
                           &G->mark, &G->tix, &G->touched, &G->dest, &G->newcap, &G->tlen, &G->tpre, &G->scratch,
                           &G->sort_tmp, &G->scan_tmp, &G->roff, &G->rcol, &G->rrow, &G->rlow, &G->dver, &G->t,
                           &G->tp, &G->vpos, &G->level, &G->rlist, &G->rlen, &G->lists, &G->c4_dense, &G->c4_touch,
@@ -1340,7 +1347,7 @@ void apply(gc_graph* G, const gc_batch_desc* b, int nb, bool dev, bool seq, int6
   G->keys.ensure(L.cap_t * 8);
   G->keys_alt.ensure(L.cap_t * 8);
   for (DevBuf* d : {&G->dirA, &G->dirA_alt}) d->ensure(2 * L.cap_i * 8);
-  for (DevBuf* d : {&G->dirD, &G->dirD_alt, &G->dirR, &G->dirR_alt}) d->ensure(2 * L.cap_d * 8);
+  for (DevBuf* d : {&G->dirD, &G->dirR, &G->dirR_alt}) d->ensure(2 * L.cap_d * 8);
   G->touched.ensure(L.max_touched * 4);
   G->dest.ensure(L.max_touched * 8);
   G->newcap.ensure(L.max_touched * 4);
@@ -1409,7 +1416,6 @@ void apply(gc_graph* G, const gc_batch_desc* b, int nb, bool dev, bool seq, int6
   const Staging S = handle_staging(G);
   BatchWork W = make_work(G, S);
   W.dirA = radix_sort_result(S.dirA, S.dirA_alt, 2 * L.cap_i, 2 * G->bits);
-  W.dirD = radix_sort_result(S.dirD, S.dirD_alt, 2 * L.cap_d, 2 * G->bits);
   W.dirR = radix_sort_result(S.dirR, S.dirR_alt, 2 * L.cap_d, 2 * G->bits);
 
   const bool use_graph = G->opt.graphs && !dev && !timed_run;
@@ -1580,7 +1586,7 @@ size_t carve_staging(char* base, int64_t cap_i, int64_t cap_d, size_t table_byte
   S->dirA = (unsigned long long*)take(2 * cap_i * 8);
   S->dirA_alt = (unsigned long long*)take(2 * cap_i * 8);
   S->dirD = (unsigned long long*)take(2 * cap_d * 8);
-  S->dirD_alt = (unsigned long long*)take(2 * cap_d * 8);
+  take(2 * cap_d * 8);  // unused: keeps the documented limit as it is
   S->dirR = (unsigned long long*)take(2 * cap_d * 8);
   S->dirR_alt = (unsigned long long*)take(2 * cap_d * 8);
   S->touched = (int32_t*)take(mt * 4);
@@ -1678,7 +1684,6 @@ void apply_noalloc(gc_graph* G, const int32_t* iu, const int32_t* iv, int64_t n_
   B.iu = iu; B.iv = iv; B.du = du; B.dv = dv;
   BatchWork W = make_work(G, S);
   W.dirA = radix_sort_result(S.dirA, S.dirA_alt, 2 * L.cap_i, 2 * G->bits);
-  W.dirD = radix_sort_result(S.dirD, S.dirD_alt, 2 * L.cap_d, 2 * G->bits);
   W.dirR = radix_sort_result(S.dirR, S.dirR_alt, 2 * L.cap_d, 2 * G->bits);
   G->pass_insert_only = L.ndl == 0;
   G->pass_max_dirA = 2 * L.cap_i;

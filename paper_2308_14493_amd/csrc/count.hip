@@ -1463,10 +1463,11 @@ __global__ void k_c4_blkmax(const int64_t* __restrict__ roff, int64_t N, int32_t
   }
 }
 
-// hubs of the large tier in decreasing order of wedge work
+// hubs of the large tier in decreasing order of wedge work (roughly: the
+// order only starts the long ones first)
 __global__ void k_c4_order(const unsigned long long* sorted, const unsigned long long* c, int32_t* list) {
   const int64_t n = (int64_t)c[C_LIST0 + L_C4_L];
-  for (int64_t i = gtid(); i < n; i += gstride()) list[i] = (int32_t)(sorted[i] & 0xFFFFFFFFull);
+  for (int64_t i = gtid(); i < n; i += gstride()) list[i] = (int32_t)(sorted[i] >> 8);
 }
 
 // --------------------------------------------------------------- combine
@@ -1557,7 +1558,7 @@ void launch_count_t(const CountArgs& A, hipStream_t s, hipEvent_t* ev) {
   hipLaunchKernelGGL(k_c4_mid<NV>, dim3(cap_grid(N, 4096)), dim3(256), 0, s, A);
   if (ev) (void)hipEventRecord(ev[4], s);
   // order the hubs by decreasing wedge work (keys written by the per-vertex pass)
-  unsigned long long* sk = radix_sort_u64(A.c4_keys, A.c4_keys_alt, A.sort_tmp, N, A.c + C_LIST0 + L_C4_L, 64, s);
+  unsigned long long* sk = radix_sort_u64(A.c4_keys, A.c4_keys_alt, A.sort_tmp, N, A.c + C_LIST0 + L_C4_L, 8, s);
   hipLaunchKernelGGL(k_c4_order, dim3(cap_grid((N + 255) / 256, 1024)), dim3(256), 0, s, sk, A.c,
                      (int32_t*)(A.lists + L_C4_L * A.list_stride));
   fill_u32((uint32_t*)A.c4_blk, 0u, N / C4_BLK + 2, s);

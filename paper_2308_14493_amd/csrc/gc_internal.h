@@ -217,6 +217,9 @@ void exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, void* tmp, h
 // fill helpers (kernels, capturable)
 void fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 void fill_u64(unsigned long long* p, unsigned long long v, int64_t n, hipStream_t s);
+// three arrays cleared by one launch
+void zero3_u64(unsigned long long* a, int64_t na, unsigned long long* b, int64_t nb, unsigned long long* c, int64_t nc,
+               hipStream_t s);
 // p[i] = v for i < min(mult * (*count), max_n), count on the device
 void fill_u64_count(unsigned long long* p, unsigned long long v, const unsigned long long* count, int64_t mult,
                     int64_t max_n, hipStream_t s);

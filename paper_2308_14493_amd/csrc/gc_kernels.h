@@ -60,9 +60,9 @@ struct BatchIn {
 
 struct BatchWork {
   unsigned long long* c;       // counters
-  unsigned long long* dirA;    // sorted directed entry keys (see DIR_MASK_SHIFT)
-  unsigned long long* dirD;
-  unsigned long long* dirR;
+  unsigned long long* dirA;    // directed entry keys (see DIR_MASK_SHIFT), sorted
+  unsigned long long* dirD;    // in any order
+  unsigned long long* dirR;    // sorted
   // per row: segment of dirA (a_beg, na) and of dirR (r_beg, nr)
   int32_t* a_beg; int32_t* na; int32_t* r_beg; int32_t* nr; int32_t* mark; int32_t* tix;  // [N]
   int32_t* touched;            // [max_touched]
@@ -81,9 +81,8 @@ void launch_ingest_keys(const PoolDev& P, const BatchIn& B, int bits, unsigned l
 void launch_ingest_classify(const PoolDev& P, const unsigned long long* keys, int64_t cap_total, int bits, int nb,
                             int nv, unsigned long long* dirA, unsigned long long* dirD, unsigned long long* dirR,
                             unsigned long long* c, unsigned long long* bstats, hipStream_t s);
-// beg/cnt may be null (rows are then only marked as touched)
-void launch_mark_rows(const unsigned long long* dir, int64_t max_n, unsigned long long* c, int which, int bits,
-                      int32_t* beg, int32_t* cnt, int32_t* mark, int32_t* touched, int32_t* tix, hipStream_t s);
+// max_n bounds the entries of dirA, dirD and dirR together
+void launch_mark_rows(const BatchWork& W, int64_t max_n, int bits, hipStream_t s);
 void launch_merge(const PoolDev& P, const BatchWork& W, int64_t max_touched, int64_t max_dirA, int bits, float slack,
                   unsigned long long* bstats, void* scan_tmp, hipStream_t s);
 void launch_flag_rows(const PoolDev& P, const BatchWork& W, int64_t max_dirD, int bits, unsigned long long* bstats,
@@ -194,7 +193,7 @@ struct DeltaArgs {
   PoolDev P;                          // union view left by the tombstone merge
   int64_t N;
   int bits;
-  const unsigned long long* dirA;     // sorted directed change lists (counts in c)
+  const unsigned long long* dirA;     // directed change lists, dirA sorted (counts in c)
   const unsigned long long* dirD;
   const unsigned long long* dirR;     // the deletions again, with a segment per row (r_beg, nr)
   const int32_t *a_beg, *na, *r_beg, *nr;  // [N] segments of dirA and dirR

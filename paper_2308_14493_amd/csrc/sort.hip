@@ -1,11 +1,12 @@
 // Device primitives: LSD radix sort of u64 keys, exclusive scans, fills.
 //
-// Radix sort: 8-bit digits, tiles of 4096 keys per 256-thread block.
-//   hist    : per-tile digit histogram -> hist[digit * nblk + blk]
-//   scan    : digit-major exclusive scan of hist (per-digit row scan, then
-//             a scan of the 256 row totals)
-//   scatter : stable rank inside the tile (16 rounds of 256 consecutive keys;
+// Radix sort: 8-bit digits, tiles of 4096 keys per 1024-thread block.
+//   hist    : per-tile digit histogram
+//   scatter : stable rank inside the tile (4 rounds of 1024 consecutive keys;
 //             rank within a wave by 8 ballots, across waves through LDS)
+// Up to RS_DIRECT tiles the scatter sums the tile histograms it needs itself
+// (two launches a digit; a launch costs more than reading a few dozen KB);
+// beyond, a digit-major scan of the histograms runs in between.
 // Counts may live on the device so that the whole sort is capturable with a
 // size known only to earlier kernels; tiles beyond the count exit at once,
 // and the histogram scans read only the tiles that hold keys.
@@ -13,12 +14,15 @@
 // (k_rs_small).
 #include "gc_internal.h"
 
+#include <algorithm>
+
 namespace {
 
-constexpr int RS_THREADS = 256;
-constexpr int RS_ROUNDS = 16;
+constexpr int RS_THREADS = 1024;
+constexpr int RS_ROUNDS = 4;
 constexpr int RS_TILE = RS_THREADS * RS_ROUNDS;
 constexpr int RS_WAVES = RS_THREADS / 64;
+constexpr int64_t RS_DIRECT = 96;  // tiles
 
 __device__ __forceinline__ int64_t rs_count(int64_t max_count, const unsigned long long* d_count) {
   if (!d_count) return max_count;
@@ -28,25 +32,40 @@ __device__ __forceinline__ int64_t rs_count(int64_t max_count, const unsigned lo
 
 __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const unsigned long long* __restrict__ keys,
                                                        int64_t max_count, const unsigned long long* d_count,
-                                                       int shift, uint32_t* __restrict__ hist, int64_t nblk) {
+                                                       int shift, uint32_t* __restrict__ hist, int64_t nblk,
+                                                       bool direct) {
   __shared__ uint32_t h[256];
   const int64_t count = rs_count(max_count, d_count);
   const int64_t blk = blockIdx.x;
   const int64_t base = blk * RS_TILE;
   if (base >= count) return;  // tiles past the count are not scanned (uniform per block)
-  h[threadIdx.x] = 0;
+  if (threadIdx.x < 256) h[threadIdx.x] = 0;
   __syncthreads();
+#pragma unroll
   for (int r = 0; r < RS_ROUNDS; ++r) {
     int64_t i = base + r * RS_THREADS + threadIdx.x;
     if (i < count) atomicAdd(&h[(keys[i] >> shift) & 255u], 1u);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * nblk + blk] = h[threadIdx.x];
+  // tile-major for the scatter's own sums, digit-major for the scans
+  if (threadIdx.x < 256)
+    hist[direct ? blk * 256 + threadIdx.x : (int64_t)threadIdx.x * nblk + blk] = h[threadIdx.x];
 }
 
 // tiles holding keys: the histogram rows are read only that far
 __device__ __forceinline__ int64_t rs_tiles(int64_t max_count, const unsigned long long* d_count) {
   return (rs_count(max_count, d_count) + RS_TILE - 1) / RS_TILE;
+}
+
+// exclusive scan of 256 values by one wave, four per lane (out may be in)
+__device__ __forceinline__ void rs_scan256(const uint32_t* in, uint32_t* out) {
+  const int l = lane_id();
+  uint32_t c[4], t = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) { c[k] = in[4 * l + k]; t += c[k]; }
+  uint32_t before = (uint32_t)wave_incl_scan32((int32_t)t) - t;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) { out[4 * l + k] = before; before += c[k]; }
 }
 
 // One block per digit: exclusive scan of that digit's row; row total out.
@@ -83,10 +102,7 @@ __global__ __launch_bounds__(256) void k_rs_addtotals(uint32_t* __restrict__ his
   __shared__ uint32_t pre[256];
   const int64_t nt = rs_tiles(max_count, d_count);
   if (nt == 0) return;  // uniform
-  if (threadIdx.x == 0) {
-    uint32_t s = 0;
-    for (int d = 0; d < 256; ++d) { pre[d] = s; s += totals[d]; }
-  }
+  if (threadIdx.x < 64) rs_scan256(totals, pre);
   __syncthreads();
   const int64_t total = nt * 256;  // digit d, tile b < nt: hist[d * nblk + b]
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
@@ -96,47 +112,89 @@ __global__ __launch_bounds__(256) void k_rs_addtotals(uint32_t* __restrict__ his
   }
 }
 
+// One round of a stable counting pass over consecutive keys, one per thread
+// of WAVES waves: the position of this thread's key among the keys placed so
+// far plus off[digit]; run[digit] moves on by the round's keys.  wcnt must be
+// zero on entry and is zero on return; all threads call it.
+template <int WAVES>
+__device__ __forceinline__ uint32_t rs_round(bool valid, uint32_t d, const uint32_t* off, uint32_t* run,
+                                             uint32_t (*wcnt)[256]) {
+  const int tid = threadIdx.x, w = tid >> 6;
+  uint64_t same = __ballot(valid);
+#pragma unroll
+  for (int b = 0; b < 8; ++b) {
+    const uint64_t bb = __ballot((d >> b) & 1u);
+    same &= ((d >> b) & 1u) ? bb : ~bb;
+  }
+  const uint32_t wrank = (uint32_t)__popcll(same & lanemask_lt());
+  if (valid && wrank == 0) wcnt[w][d] = (uint32_t)__popcll(same);
+  __syncthreads();
+  if (tid < 256) {  // digit tid: the waves' counts become their first positions
+    uint32_t at = run[tid];
+#pragma unroll
+    for (int k = 0; k < WAVES; ++k) { const uint32_t c = wcnt[k][tid]; wcnt[k][tid] = at; at += c; }
+    run[tid] = at;
+  }
+  __syncthreads();
+  const uint32_t pos = valid ? off[d] + wcnt[w][d] + wrank : 0u;
+  __syncthreads();
+  for (int k = tid; k < WAVES * 256; k += WAVES * 64) (&wcnt[0][0])[k] = 0u;
+  __syncthreads();
+  return pos;
+}
+
 __global__ __launch_bounds__(RS_THREADS) void k_rs_scatter(const unsigned long long* __restrict__ keys,
                                                           unsigned long long* __restrict__ out,
                                                           int64_t max_count, const unsigned long long* d_count,
                                                           int shift, const uint32_t* __restrict__ hist,
-                                                          int64_t nblk) {
+                                                          int64_t nblk, bool direct) {
   __shared__ uint32_t base_off[256];
   __shared__ uint32_t run[256];
   __shared__ uint32_t wcnt[RS_WAVES][256];
+  __shared__ uint32_t part[2][RS_THREADS];
   const int64_t count = rs_count(max_count, d_count);
   const int64_t blk = blockIdx.x;
   const int64_t tbase = blk * RS_TILE;
   if (tbase >= count) return;  // uniform per block
-  const int tid = threadIdx.x, w = tid >> 6;
-  base_off[tid] = hist[(int64_t)tid * nblk + blk];
-  run[tid] = 0;
-  for (int k = 0; k < RS_WAVES; ++k) wcnt[k][tid] = 0;
+  const int tid = threadIdx.x;
+  for (int k = tid; k < RS_WAVES * 256; k += RS_THREADS) (&wcnt[0][0])[k] = 0u;
+  if (direct) {
+    // digit tid % 256 over every fourth tile: all its keys, and those of earlier tiles
+    const int64_t nt = (count + RS_TILE - 1) / RS_TILE;
+    uint32_t all = 0, before = 0;
+#pragma unroll 8
+    for (int64_t b = tid >> 8; b < nt; b += RS_THREADS / 256) {
+      const uint32_t c = hist[b * 256 + (tid & 255)];
+      all += c;
+      before += b < blk ? c : 0u;
+    }
+    part[0][tid] = all;
+    part[1][tid] = before;
+    __syncthreads();
+    if (tid < 256) {
+#pragma unroll
+      for (int k = 256; k < RS_THREADS; k += 256) { all += part[0][tid + k]; before += part[1][tid + k]; }
+      base_off[tid] = all;
+      run[tid] = before;
+    }
+    __syncthreads();
+    if (tid < 64) rs_scan256(base_off, base_off);
+  } else if (tid < 256) {
+    base_off[tid] = hist[(int64_t)tid * nblk + blk];
+    run[tid] = 0;
+  }
   __syncthreads();
+  unsigned long long key[RS_ROUNDS];
+#pragma unroll
   for (int r = 0; r < RS_ROUNDS; ++r) {
     const int64_t i = tbase + r * RS_THREADS + tid;
-    const bool valid = i < count;
-    unsigned long long key = valid ? keys[i] : 0ull;
-    const uint32_t d = (uint32_t)(key >> shift) & 255u;
-    uint64_t same = __ballot(valid);
-    for (int b = 0; b < 8; ++b) {
-      uint64_t bb = __ballot((d >> b) & 1u);
-      same &= ((d >> b) & 1u) ? bb : ~bb;
-    }
-    const uint32_t wrank = (uint32_t)__popcll(same & lanemask_lt());
-    const bool leader = valid && (same & lanemask_lt()) == 0;
-    if (leader) wcnt[w][d] = (uint32_t)__popcll(same);
-    __syncthreads();
-    if (valid) {
-      uint32_t before = run[d];
-      for (int k = 0; k < w; ++k) before += wcnt[k][d];
-      out[base_off[d] + before + wrank] = key;
-    }
-    __syncthreads();
-    uint32_t add = 0;
-    for (int k = 0; k < RS_WAVES; ++k) { add += wcnt[k][tid]; wcnt[k][tid] = 0; }
-    run[tid] += add;
-    __syncthreads();
+    key[r] = i < count ? keys[i] : 0ull;
+  }
+#pragma unroll
+  for (int r = 0; r < RS_ROUNDS; ++r) {
+    const bool valid = tbase + r * RS_THREADS + tid < count;
+    const uint32_t pos = rs_round<RS_WAVES>(valid, (uint32_t)(key[r] >> shift) & 255u, base_off, run, wcnt);
+    if (valid) out[pos] = key[r];
   }
 }
 
@@ -159,7 +217,7 @@ __global__ __launch_bounds__(RSS_T) void k_rs_small(const unsigned long long* ke
   __shared__ uint32_t run[256];
   __shared__ uint32_t wcnt[RSS_WAVES][256];
   const int32_t count = (int32_t)rs_count(max_count, d_count);  // <= max_count <= RSS_MAX
-  const int tid = threadIdx.x, w = tid >> 6, l = lane_id();
+  const int tid = threadIdx.x, w = tid >> 6;
   for (int32_t i = tid; i < count; i += RSS_T) buf[0][i] = keys[i];
   for (int k = tid; k < RSS_WAVES * 256; k += RSS_T) (&wcnt[0][0])[k] = 0u;
   int cur = 0;
@@ -170,43 +228,18 @@ __global__ __launch_bounds__(RSS_T) void k_rs_small(const unsigned long long* ke
     __syncthreads();
     for (int32_t i = tid; i < count; i += RSS_T) atomicAdd(&hist[(uint32_t)(src[i] >> shift) & 255u], 1u);
     __syncthreads();
-    if (w == 0) {  // exclusive scan of the 256 digit counts, four per lane
-      uint32_t c[4], t = 0;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) { c[k] = hist[4 * l + k]; t += c[k]; }
-      uint32_t before = (uint32_t)wave_incl_scan32((int32_t)t) - t;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) { hist[4 * l + k] = before; before += c[k]; }
-    }
+    if (w == 0) rs_scan256(hist, hist);
     __syncthreads();
     for (int32_t r0 = 0; r0 < count; r0 += RSS_T) {
       const int32_t i = r0 + tid;
       const bool valid = i < count;
       const unsigned long long key = valid ? src[i] : 0ull;
-      const uint32_t d = (uint32_t)(key >> shift) & 255u;
-      uint64_t same = __ballot(valid);
-      for (int b = 0; b < 8; ++b) {
-        const uint64_t bb = __ballot((d >> b) & 1u);
-        same &= ((d >> b) & 1u) ? bb : ~bb;
-      }
-      const uint32_t wrank = (uint32_t)__popcll(same & lanemask_lt());
-      if (valid && (same & lanemask_lt()) == 0) wcnt[w][d] = (uint32_t)__popcll(same);
-      __syncthreads();
-      if (valid) {
-        uint32_t before = hist[d] + run[d];
-        for (int k = 0; k < w; ++k) before += wcnt[k][d];
-        dst[before + wrank] = key;
-      }
-      __syncthreads();
-      if (tid < 256) {
-        uint32_t add = 0;
-        for (int k = 0; k < RSS_WAVES; ++k) { add += wcnt[k][tid]; wcnt[k][tid] = 0u; }
-        run[tid] += add;
-      }
-      __syncthreads();
+      const uint32_t pos = rs_round<RSS_WAVES>(valid, (uint32_t)(key >> shift) & 255u, hist, run, wcnt);
+      if (valid) dst[pos] = key;
     }
     cur ^= 1;
   }
+  __syncthreads();
   for (int32_t i = tid; i < count; i += RSS_T) out[i] = buf[cur][i];
 }
 
@@ -301,6 +334,48 @@ __global__ __launch_bounds__(SC_THREADS) void k_scan_down(const TIn* __restrict_
   }
 }
 
+// The whole scan in one block, tile after tile: one launch instead of three
+// where the capacity is a few tiles (4 us against 3 x 3 to 4 us).
+constexpr int SO_ITEMS = 8;
+constexpr int64_t SO_MAX = 4 * SC_THREADS * SO_ITEMS;
+
+template <class TIn>
+__global__ __launch_bounds__(SC_THREADS) void k_scan_one(const TIn* __restrict__ in, int64_t n, const int64_t* d_n,
+                                                         int64_t* __restrict__ out) {
+  __shared__ int64_t ws[2][SC_THREADS / 64];
+  const int64_t nn = scan_count(n, d_n);
+  const int w = threadIdx.x >> 6;
+  int64_t carry = 0;
+  int ph = 0;
+  for (int64_t b0 = 0; b0 < nn; b0 += SC_THREADS * SO_ITEMS, ph ^= 1) {
+    const int64_t base = b0 + (int64_t)threadIdx.x * SO_ITEMS;
+    int64_t v[SO_ITEMS], s = 0;
+#pragma unroll
+    for (int k = 0; k < SO_ITEMS; ++k) {
+      v[k] = base + k < nn ? (int64_t)in[base + k] : 0;
+      s += v[k];
+    }
+    const int64_t inc = wave_incl_scan64(s);
+    if (lane_id() == 63) ws[ph][w] = inc;
+    __syncthreads();  // ws of the other phase is read no more once all are here
+    int64_t run = carry + inc - s;
+#pragma unroll
+    for (int k = 0; k < SC_THREADS / 64; ++k) {
+      run += k < w ? ws[ph][k] : 0;
+      carry += ws[ph][k];
+    }
+#pragma unroll
+    for (int k = 0; k < SO_ITEMS; ++k) {
+      if (base + k < nn) out[base + k] = run;
+      run += v[k];
+    }
+  }
+  if (threadIdx.x == 0) {
+    out[n] = carry;
+    if (nn < n) out[nn] = carry;
+  }
+}
+
 __global__ void k_fill_u32(uint32_t* p, uint32_t v, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
@@ -324,6 +399,10 @@ inline int64_t rs_nblk(int64_t max_count) { return (max_count + RS_TILE - 1) / R
 
 template <class TIn>
 void scan_impl(const TIn* in, int64_t* out, int64_t n, void* tmp, hipStream_t s, const int64_t* d_n = nullptr) {
+  if (n <= SO_MAX) {
+    hipLaunchKernelGGL(k_scan_one<TIn>, dim3(1), dim3(SC_THREADS), 0, s, in, n, d_n, out);
+    return;
+  }
   int64_t nb = (n + SC_TILE - 1) / SC_TILE;
   if (nb == 0) nb = 1;
   int64_t* bsum = (int64_t*)tmp;
@@ -354,15 +433,18 @@ unsigned long long* radix_sort_u64(unsigned long long* keys, unsigned long long*
   uint32_t* totals = hist + nblk * 256;
   unsigned long long* src = keys;
   unsigned long long* dst = alt;
+  const bool direct = nblk <= RS_DIRECT;
   for (int shift = 0; shift < bits; shift += 8) {
     hipLaunchKernelGGL(k_rs_hist, dim3((unsigned)nblk), dim3(RS_THREADS), 0, s, src, max_count, d_count,
-                       shift, hist, nblk);
-    hipLaunchKernelGGL(k_rs_rowscan, dim3(256), dim3(1024), 0, s, hist, nblk, totals, max_count, d_count);
-    unsigned g = (unsigned)((nblk * 256 + 255) / 256);
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL(k_rs_addtotals, dim3(g), dim3(256), 0, s, hist, nblk, totals, max_count, d_count);
+                       shift, hist, nblk, direct);
+    if (!direct) {
+      hipLaunchKernelGGL(k_rs_rowscan, dim3(256), dim3(1024), 0, s, hist, nblk, totals, max_count, d_count);
+      unsigned g = (unsigned)((nblk * 256 + 255) / 256);
+      if (g > 4096) g = 4096;
+      hipLaunchKernelGGL(k_rs_addtotals, dim3(g), dim3(256), 0, s, hist, nblk, totals, max_count, d_count);
+    }
     hipLaunchKernelGGL(k_rs_scatter, dim3((unsigned)nblk), dim3(RS_THREADS), 0, s, src, dst, max_count,
-                       d_count, shift, hist, nblk);
+                       d_count, shift, hist, nblk, direct);
     unsigned long long* t = src; src = dst; dst = t;
   }
   return src;
@@ -392,6 +474,17 @@ void fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s) {
   int64_t g = (n + 255) / 256;
   if (g > 8192) g = 8192;
   hipLaunchKernelGGL(k_fill_u32, dim3((unsigned)g), dim3(256), 0, s, p, v, n);
+}
+__global__ void k_zero3(unsigned long long* a, int64_t na, unsigned long long* b, int64_t nb, unsigned long long* c,
+                        int64_t nc) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < na + nb + nc;
+       i += (int64_t)gridDim.x * blockDim.x)
+    *(i < na ? a + i : (i < na + nb ? b + (i - na) : c + (i - na - nb))) = 0ull;
+}
+void zero3_u64(unsigned long long* a, int64_t na, unsigned long long* b, int64_t nb, unsigned long long* c, int64_t nc,
+               hipStream_t s) {
+  const int64_t g = std::min<int64_t>((na + nb + nc + 255) / 256, 1024);
+  hipLaunchKernelGGL(k_zero3, dim3((unsigned)std::max<int64_t>(g, 1)), dim3(256), 0, s, a, na, b, nb, c, nc);
 }
 void fill_u64(unsigned long long* p, unsigned long long v, int64_t n, hipStream_t s) {
   if (n <= 0) return;
