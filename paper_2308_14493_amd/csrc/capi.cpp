@@ -271,9 +271,6 @@ struct gc_graph {
   std::vector<double> tune_ms, tune_wedges;
   int tune_next = 0;
   int64_t dense_min_best = 256;
-  // rows at least this long go through a whole wave in the per-vertex pass
-  // (GC_DEG_WAVE_ROW overrides it: tests lower it to reach that path)
-  int32_t deg_wave_row = 1 << 16;
   // ids covered by the bitmaps of the edge-local 4-cycles, 0: the most
   // (GC_DELTA_BITS lowers it: tests reach the ids below the window)
   int32_t delta_bits = 0;
@@ -515,11 +512,12 @@ void enqueue_count(gc_graph* G, int nv, int radius, long long* state_d, BatchWor
   hipStream_t s = G->stream;
   PoolDev P = G->pd();
   launch_region(P, W, radius, G->level.as<int32_t>(), G->rlist.as<int32_t>(), G->rlen.as<int32_t>(), s);
-  launch_region_fill(P, A.R, W, radius, G->level.as<int32_t>(), G->rlist.as<int32_t>(), G->rlen.as<int32_t>(),
-                     G->scan_tmp.p, s);
+  // the hub keys' sort buffer holds the wedge sums until the keys are sorted
+  launch_region_fill(nv, P, A.R, W, radius, G->level.as<int32_t>(), G->rlist.as<int32_t>(), G->rlen.as<int32_t>(),
+                     A.c4_keys_alt, G->scan_tmp.p, s);
   launch_degrees(nv, A.R, G->gid.as<int32_t>(), G->rlist.as<int32_t>(), G->ctr.as<unsigned long long>(),
                  G->sig.as<unsigned long long>(), G->lists.as<int32_t>(), G->N, G->tiers_now[0], G->tiers_now[1], G->tiers_now[2],
-                 G->deg_wave_row, G->bstats.as<unsigned long long>(), G->c4_keys.as<unsigned long long>(), s);
+                 G->bstats.as<unsigned long long>(), G->c4_keys.as<unsigned long long>(), A.c4_keys_alt, s);
   if (timed) HIPCHK(hipEventRecord(G->ev[1], s));
   launch_count(nv, A, s, timed ? &G->ev[2] : nullptr);
   if (tv)
@@ -733,7 +731,6 @@ void* noalloc_scratch_ptr(int device) {
 
 void setup_handle(gc_graph* G, const gc_options* opt) {
   if (opt) G->opt = *opt; else gc_options_default(&G->opt);
-  if (const char* e = std::getenv("GC_DEG_WAVE_ROW")) G->deg_wave_row = std::max(1, std::min(1 << 16, std::atoi(e)));
   if (const char* e = std::getenv("GC_DELTA_BITS")) G->delta_bits = std::max(0, std::atoi(e));
   if (const char* e = std::getenv("GC_RETRY_LIMIT")) G->retry_limit = std::max(0, std::min(8, std::atoi(e)));
   if (G->opt.radius < 0 || G->opt.radius > 4) raise(GC_EINVAL, "radius must be in [0, 4]");

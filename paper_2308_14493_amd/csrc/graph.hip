@@ -460,12 +460,37 @@ __global__ void k_level_end(unsigned long long* cc, int lvl) {
   if (gtid() == 0) cc[C_LVL0 + lvl + 1] = cc[C_RLIST];
 }
 
-// Whole-graph region: every vertex with a non-empty row.
-__global__ void k_all_rows(PoolDev P, int32_t* __restrict__ rlist, unsigned long long* __restrict__ cc) {
-  const int64_t lim = (P.N + 63) / 64 * 64;  // whole waves take part in the appends
-  for (int64_t v = gtid(); v < lim; v += gstride()) {
-    const bool take = v < P.N && P.len[v] > 0;
-    wave_append(take, (int32_t)v, rlist, cc);
+// Whole-graph region: every vertex with a non-empty row, in id order within
+// a workgroup's 1024 (one atomic for all of them).
+__global__ __launch_bounds__(TPB) void k_all_rows(PoolDev P, int32_t* __restrict__ rlist,
+                                                  unsigned long long* __restrict__ cc) {
+  __shared__ uint32_t cnt[TPB / 64];
+  __shared__ unsigned long long base_s;
+  const int w = threadIdx.x >> 6, l = lane_id();
+  for (int64_t v0 = (int64_t)blockIdx.x * 1024; v0 < P.N; v0 += (int64_t)gridDim.x * 1024) {
+    uint64_t m[4];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {  // wave w: ids v0 + 256 w + 64 k + lane
+      const int64_t v = v0 + 256 * w + 64 * k + l;
+      m[k] = __ballot(v < P.N && P.len[v] > 0);
+      mine += (uint32_t)__popcll(m[k]);
+    }
+    if (l == 0) cnt[w] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t t = 0;
+      for (int k = 0; k < TPB / 64; ++k) { const uint32_t c = cnt[k]; cnt[k] = t; t += c; }
+      base_s = t ? atomicAdd(&cc[C_RLIST], (unsigned long long)t) : 0ull;
+    }
+    __syncthreads();
+    unsigned long long at = base_s + cnt[w];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if ((m[k] >> l) & 1ull) rlist[at + __popcll(m[k] & lanemask_lt())] = (int32_t)(v0 + 256 * w + 64 * k + l);
+      at += __popcll(m[k]);
+    }
+    __syncthreads();
   }
 }
 
@@ -485,19 +510,42 @@ __global__ void k_region_len(PoolDev P, const int32_t* __restrict__ rlist, const
   }
 }
 
+// Rows inside the radius are whole: their entries are copied by position, so
+// that a hub's row is spread over the chip (a wave per row took 86 us at
+// scale 18, most of it the longest row).  Entries of other rows are left.
+__global__ void k_region_copy(PoolDev P, RegionDev R, const int32_t* __restrict__ level, int32_t radius,
+                              const unsigned long long* cc) {
+  const int64_t total = ctr(cc, C_ER);
+  for (int64_t b0 = gwave() * 256; b0 < total; b0 += gwaves() * 256) {
+    int64_t v = wave_upper_bound(R.roff, P.N, b0);
+    for (int64_t p = b0 + lane_id(); p < total && p < b0 + 256; p += 64) {
+      v = upper_bound_from(R.roff, P.N, v, p);
+      if (radius >= 0 && level[v] >= radius) continue;
+      R.rcol[p] = P.col[P.off[v] + (p - R.roff[v])];
+      R.rrow[p] = (int32_t)v;
+    }
+  }
+}
+
+// The outermost rows: the entries whose other end is in the region.  Every
+// region vertex: its sums of the entry pass cleared.
 __global__ void k_region_fill(PoolDev P, RegionDev R, const int32_t* __restrict__ rlist, const unsigned long long* cc,
-                              const int32_t* __restrict__ level, int32_t radius) {
+                              const int32_t* __restrict__ level, int32_t radius, int nv,
+                              unsigned long long* __restrict__ wsum) {
   const int64_t n = ctr(cc, C_RLIST);
+  for (int64_t i = gtid(); i < n; i += gstride()) {
+    const int64_t v = rlist[i];
+    for (int x = 0; x < nv; ++x) R.d[v * nv + x] = 0;
+    wsum[v] = 0ull;
+  }
+  if (radius < 0) return;
   for (int64_t i = gwave(); i < n; i += gwaves()) {
     const int32_t v = rlist[i];
+    if (level[v] < radius) continue;
     const int32_t L = P.len[v];
     const uint32_t* row = P.col + P.off[v];
     uint32_t* out = R.rcol + R.roff[v];
     int32_t* orow = R.rrow + R.roff[v];
-    if (radius < 0 || level[v] < radius) {
-      for (int32_t k = lane_id(); k < L; k += 64) { out[k] = row[k]; orow[k] = v; }
-      continue;
-    }
     int32_t base = 0;
     for (int32_t k0 = 0; k0 < L; k0 += 64) {
       const int32_t k = k0 + lane_id();
@@ -572,20 +620,6 @@ __device__ __forceinline__ void flush_decisions(DegDecision& d, unsigned long lo
   d = DegDecision();
 }
 
-// Segment of entry idx of a wave's concatenated lists: the last lane s whose
-// exclusive prefix excl(s) is <= idx (excl nondecreasing over the lanes,
-// excl(0) = 0, idx below the total).  All lanes must call it.
-__device__ __forceinline__ int wave_segment(int32_t excl, int32_t idx) {
-  int lo = 0, hi = 64;
-#pragma unroll
-  for (int st = 0; st < 6; ++st) {
-    const int mid = (lo + hi) >> 1;
-    if (__shfl(excl, mid) <= idx) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ int64_t wave_max64(int64_t v) {
   for (int o = 32; o > 0; o >>= 1) {
     const int64_t t = __shfl_xor(v, o);
@@ -601,27 +635,59 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// A wave takes a group of 64 region vertices at a time, one per lane: the
-// rows of the shorter ones are concatenated and dealt over the lanes (a
-// segment search per step), so the lanes' searches for v in the rows of its
-// lower neighbours overlap instead of one vertex's chain of loads at a time;
-// the per-vertex sums meet in LDS, one slot per lane.  Rows of at least
-// wave_row (<= 65536) entries are walked by the whole wave, one at a time.
+// Entry pass of the region: per lower entry (v, w), w < v, the position of v
+// in row w, which is the number of wedges (v, w, .) below v through it (kept
+// for the 4-cycle kernels as the starting cursor in row w) and their sum per
+// v; per entry absent from a version, the count that v's degree lacks there.
+// One lane per entry, whatever the row: a wave that held 64 whole rows waited
+// for its longest (0.72 ms at scale 18, now 0.1; 9.5 ms at scale 22, now
+// 5.3).  Consecutive entries share a row, so its sums cost one atomic per
+// wave.  Bound by the dependent loads of the searches.
+template <int NV>
+__global__ __launch_bounds__(TPB) void k_entries(RegionDev R, const unsigned long long* cc,
+                                                 unsigned long long* __restrict__ wsum) {
+  const int64_t total = ctr(cc, C_ER);
+  const int l = lane_id();
+  for (int64_t b0 = gwave() * 64; b0 < total; b0 += gwaves() * 64) {
+    const int64_t p = b0 + l;
+    const bool in = p < total;
+    const int32_t v = in ? R.rrow[p] : -1;
+    const uint32_t x = in ? R.rcol[p] : 0u, w = x & GC_ID;
+    int32_t pos = 0;
+    if (in && w < (uint32_t)v) {
+      const int64_t wb = R.roff[w];
+      pos = lower_bound_from_end(R.rcol + wb, (int32_t)(R.roff[w + 1] - wb), (uint32_t)v);
+      R.vpos[p] = pos;
+    }
+    // the lanes of one row: from the last row start at or below the lane
+    const int32_t before = __shfl_up(v, 1), after = __shfl_down(v, 1);
+    const uint64_t heads = __ballot(l == 0 || before != v);
+    const uint64_t upto = lanemask_lt() | (1ull << l);
+    const int head = 63 - __clzll((long long)(heads & upto));
+    const bool tail = in && (l == 63 || after != v);
+    const int64_t incl = wave_incl_scan64((int64_t)pos);
+    const int64_t sum = incl - __shfl(incl - pos, head);
+    if (tail && sum) atomicAdd(&wsum[v], (unsigned long long)sum);
+    const uint64_t seg = upto & ~((1ull << head) - 1ull);
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const uint64_t m = __ballot(in && ((x >> (GC_VSHIFT + q)) & 1u));
+      if (m && tail) {
+        const int c = __popcll(m & seg);
+        if (c) atomicAdd(&R.d[(int64_t)v * NV + q], c);
+      }
+    }
+  }
+}
+
+// The region vertices, a lane each, from the sums of the entry pass.
 template <int NV>
 __global__ __launch_bounds__(TPB) void k_degrees(RegionDev R, const int32_t* __restrict__ gid, const int32_t* __restrict__ rlist,
                           unsigned long long* __restrict__ cc, unsigned long long* __restrict__ sig,
                           int32_t* __restrict__ lists, int64_t list_stride, int32_t tri_small, int32_t c4_small,
-                          int32_t c4_mid, int32_t wave_row, unsigned long long* __restrict__ bstats,
-                          unsigned long long* __restrict__ c4_keys) {
-  __shared__ uint32_t sdv[TPB / 64][NV][64];          // degree per version
-  __shared__ uint32_t slow[TPB / 64][64];             // lower entries
-  __shared__ unsigned long long sws[TPB / 64][64];    // wedge bound
+                          int32_t c4_mid, unsigned long long* __restrict__ bstats,
+                          unsigned long long* __restrict__ c4_keys, const unsigned long long* __restrict__ wsum_) {
   const int l = lane_id(), wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int x = 0; x < NV; ++x) sdv[wv][x][l] = 0u;
-  slow[wv][l] = 0u;
-  sws[wv][l] = 0ull;
-  wave_sync();
   const int64_t n = ctr(cc, C_RLIST);
   int cur_g = -1;  // graph of the running sums s1, w2, d1 (lane 0)
   int64_t s1[NV], w2[NV], d1[NV];
@@ -632,69 +698,23 @@ __global__ __launch_bounds__(TPB) void k_degrees(RegionDev R, const int32_t* __r
   int32_t maxdp = 0, maxlow = 0;
   int64_t maxw = 0;
   DegDecision dec;
-  // group c holds the region vertices c, c + C, c + 2C, ... (C groups): one
-  // from each 64th of the list, so the high-degree vertices (ids follow the
-  // degree order) are spread over the groups
   const int64_t C = (n + 63) / 64;
   for (int64_t c = gwave(); c < C; c += gwaves()) {
-    const int64_t i = c + (int64_t)l * C;
-    int32_t v = -1, L = 0;
-    int64_t b = 0;
+    const int64_t i = c * 64 + l;
+    int32_t v = -1, L = 0, low = 0;
+    int32_t dv[NV];
+    int64_t wsum = 0;
+#pragma unroll
+    for (int x = 0; x < NV; ++x) dv[x] = 0;
     if (i < n) {
       v = rlist[i];
-      b = R.roff[v];
+      const int64_t b = R.roff[v];
       L = (int32_t)(R.roff[v + 1] - b);
-    }
-    // entry at region position p of the row of lane s (vertex vs)
-    auto entry = [&](int s, int32_t vs, int64_t p) {
-      const uint32_t x = R.rcol[p];
-      const uint32_t pm = vpresent<NV>(x);
+      low = lower_bound_id(R.rcol + b, L, (uint32_t)v);
+      wsum = (int64_t)wsum_[v];
 #pragma unroll
-      for (int q = 0; q < NV; ++q)
-        if ((pm >> q) & 1u) atomicAdd(&sdv[wv][q][s], 1u);
-      const uint32_t w = x & GC_ID;
-      if (w < (uint32_t)vs) {
-        // wedges (vs, w, .) below vs: entries of row w smaller than vs (kept
-        // for the 4-cycle kernels as the starting cursor in row w)
-        atomicAdd(&slow[wv][s], 1u);
-        const int64_t wb = R.roff[w];
-        const int32_t pos = lower_bound_from_end(R.rcol + wb, (int32_t)(R.roff[w + 1] - wb), (uint32_t)vs);
-        R.vpos[p] = pos;
-        if (pos) atomicAdd(&sws[wv][s], (unsigned long long)pos);
-      }
-    };
-    {
-      const int32_t ss = L < wave_row ? L : 0;  // total < 64 * 65536
-      const int32_t incl = wave_incl_scan32(ss);
-      const int32_t tot = __shfl(incl, 63);
-      const int32_t excl = incl - ss;
-      for (int32_t base = 0; base < tot; base += 64) {
-        const int32_t idx = base + l;
-        const int s = wave_segment(excl, idx);
-        const int32_t vs = __shfl(v, s);
-        const int64_t bs = __shfl(b, s);
-        const int32_t es = __shfl(excl, s);
-        if (idx < tot) entry(s, vs, bs + (idx - es));
-      }
+      for (int x = 0; x < NV; ++x) dv[x] = L - R.d[(int64_t)v * NV + x];
     }
-    for (uint64_t lm = __ballot(L >= wave_row); lm; lm &= lm - 1) {
-      const int s = __builtin_ctzll(lm);
-      const int32_t vs = __shfl(v, s), Ls = __shfl(L, s);
-      const int64_t bs = __shfl(b, s);
-      for (int32_t k = l; k < Ls; k += 64) entry(s, vs, bs + k);
-    }
-    wave_sync();
-    int32_t dv[NV];
-#pragma unroll
-    for (int x = 0; x < NV; ++x) {
-      dv[x] = (int32_t)sdv[wv][x][l];
-      sdv[wv][x][l] = 0u;
-    }
-    const int32_t low = (int32_t)slow[wv][l];
-    const int64_t wsum = (int64_t)sws[wv][l];
-    slow[wv][l] = 0u;
-    sws[wv][l] = 0ull;
-    wave_sync();
     const bool has = v >= 0;
     if (has) {
       if constexpr (NV == 2) {
@@ -1088,7 +1108,7 @@ void launch_region(const PoolDev& P, const BatchWork& W, int radius, int32_t* le
   const int64_t N = P.N;
   fill_u32((uint32_t*)rlen, 0u, N, s);
   if (radius < 0) {
-    hipLaunchKernelGGL(k_all_rows, dim3(grid_for(N)), dim3(TPB), 0, s, P, rlist, W.c);
+    hipLaunchKernelGGL(k_all_rows, dim3(grid_for(N, 1024)), dim3(TPB), 0, s, P, rlist, W.c);
     hipLaunchKernelGGL(k_region_len, dim3(4096), dim3(TPB), 0, s, P, rlist, W.c, level, -1, rlen);
     return;
   }
@@ -1101,25 +1121,30 @@ void launch_region(const PoolDev& P, const BatchWork& W, int radius, int32_t* le
   hipLaunchKernelGGL(k_region_len, dim3(4096), dim3(TPB), 0, s, P, rlist, W.c, level, radius, rlen);
 }
 
-void launch_region_fill(const PoolDev& P, const RegionDev& R, const BatchWork& W, int radius, const int32_t* level,
-                        const int32_t* rlist, const int32_t* rlen, void* scan_tmp, hipStream_t s) {
+void launch_region_fill(int nv, const PoolDev& P, const RegionDev& R, const BatchWork& W, int radius,
+                        const int32_t* level, const int32_t* rlist, const int32_t* rlen, unsigned long long* wsum,
+                        void* scan_tmp, hipStream_t s) {
   exclusive_scan_i32_to_i64(rlen, R.roff, P.N, scan_tmp, s);
   hipLaunchKernelGGL(k_region_total, dim3(1), dim3(64), 0, s, R.roff, P.N, W.c);
-  hipLaunchKernelGGL(k_region_fill, dim3(4096), dim3(TPB), 0, s, P, R, rlist, W.c, level, radius);
+  hipLaunchKernelGGL(k_region_copy, dim3(4096), dim3(TPB), 0, s, P, R, level, radius, (const unsigned long long*)W.c);
+  hipLaunchKernelGGL(k_region_fill, dim3(4096), dim3(TPB), 0, s, P, R, rlist, W.c, level, radius, nv, wsum);
 }
 
 void launch_degrees(int nv, const RegionDev& R, const int32_t* gid, const int32_t* rlist, unsigned long long* c,
                     unsigned long long* sig, int32_t* lists, int64_t list_stride, int32_t tri_small, int32_t c4_small,
-                    int32_t c4_mid, int32_t wave_row, unsigned long long* bstats, unsigned long long* c4_keys,
+                    int32_t c4_mid, unsigned long long* bstats, unsigned long long* c4_keys, unsigned long long* wsum,
                     hipStream_t s) {
-  // at least 1024 vertices (list_stride = N bounds the region) per workgroup
-  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (list_stride + 1023) / 1024));
-  if (nv == 2)
+  // list_stride = N bounds the region's vertices
+  const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (list_stride + 255) / 256));
+  if (nv == 2) {
+    hipLaunchKernelGGL(k_entries<2>, dim3(8192), dim3(TPB), 0, s, R, (const unsigned long long*)c, wsum);
     hipLaunchKernelGGL(k_degrees<2>, dim3(grid), dim3(TPB), 0, s, R, gid, rlist, c, sig, lists, list_stride,
-                       tri_small, c4_small, c4_mid, wave_row, bstats, c4_keys);
-  else
+                       tri_small, c4_small, c4_mid, bstats, c4_keys, (const unsigned long long*)wsum);
+  } else {
+    hipLaunchKernelGGL(k_entries<4>, dim3(8192), dim3(TPB), 0, s, R, (const unsigned long long*)c, wsum);
     hipLaunchKernelGGL(k_degrees<4>, dim3(grid), dim3(TPB), 0, s, R, gid, rlist, c, sig, lists, list_stride,
-                       tri_small, c4_small, c4_mid, wave_row, bstats, c4_keys);
+                       tri_small, c4_small, c4_mid, bstats, c4_keys, (const unsigned long long*)wsum);
+  }
 }
 
 // ---------------------------------------------------------------- build
