@@ -1066,18 +1066,9 @@ struct C4Smem {
   unsigned long long win[C4W_WIN];
   C4Chunk C;
   int64_t item;
+  int64_t cut[2];
   int32_t nt;
 };
-
-// first p in [0, c) with id(row[p]) >= lo, rows sorted, id(row[c-1]) < v
-__device__ __forceinline__ int32_t gallop_down(const uint32_t* row, int32_t c, uint32_t lo) {
-  if (c == 0 || (row[c - 1] & GC_ID) < lo) return c;
-  int32_t k = 1;
-  while (c - 1 - k >= 0 && (row[c - 1 - k] & GC_ID) >= lo) k <<= 1;
-  const int32_t a = c - 1 - k > 0 ? c - 1 - k : 0;   // row[a] < lo or a == 0
-  const int32_t z = c - 1 - (k >> 1);                 // row[z] >= lo
-  return a + lower_bound_id(row + a, z - a + 1, lo);
-}
 
 // block maximum (all threads call; result valid in every thread)
 __device__ __forceinline__ int32_t block_max32(C4Chunk& C, int32_t x) {
@@ -1107,7 +1098,7 @@ __device__ __forceinline__ void block_sum2(C4Chunk& C, long long& x, long long& 
 // Thread q takes u_q: short slices (the common case: u_q has few entries in
 // the id range) are walked by their own thread, long ones by their whole
 // wave, one at a time (wave_walk).
-constexpr int32_t C4W_SHORT = 128;  // entries a thread walks itself before the gallop
+constexpr int32_t C4W_LANE = 128;  // entries a thread walks itself
 
 template <class P0, class P1, class F>
 __device__ __forceinline__ void c4_block_walk(const RegionDev& R, int64_t rb, int32_t nlow, const int64_t* urow,
@@ -1123,7 +1114,7 @@ __device__ __forceinline__ void c4_block_walk(const RegionDev& R, int64_t rb, in
     if (p1 > p0) {
       sb = urow[q] + p0;
       fl = R.rcol[rb + q] & GC_FLAGS;
-      if (p1 - p0 <= C4W_SHORT) {
+      if (p1 - p0 <= C4W_LANE) {
         const int32_t len = p1 - p0;
         for (int32_t k = 0; k < len; k += 4) {  // four loads in flight
           uint32_t y[4];
@@ -1143,88 +1134,188 @@ __device__ __forceinline__ void c4_block_walk(const RegionDev& R, int64_t rb, in
   __syncthreads();
 }
 
-// One window of ids [lo, ...) of hub v: every lower neighbour u_q walks its
-// row backwards from its cursor while the ids stay >= lo and leaves the
+// sum over each group of LANES (4 or 16) consecutive lanes
+template <int LANES>
+__device__ __forceinline__ int32_t lanes_sum(int32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true);  // quad_perm [1, 0, 3, 2]
+  x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true);  // quad_perm [2, 3, 0, 1]
+  if constexpr (LANES == 16) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x124, 0xF, 0xF, true);  // row_ror:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x128, 0xF, 0xF, true);  // row_ror:8
+  }
+  return x;
+}
+
+// One window of ids [lo, lo + wsz) of hub v: every lower neighbour u_q walks
+// its row backwards from its cursor while the ids stay >= lo and leaves the
 // cursor at the first position below the window, so the slice is read once
-// and no search precedes it.  The thread reads up to C4W_SHORT entries itself,
-// four at a time; the rest of a longer slice is delimited by a gallop and
-// walked by the whole wave.  wtot += entries walked, rest += entries left
-// below the window (per thread).
-template <class F>
-__device__ __forceinline__ void c4_window_walk(const RegionDev& R, int64_t rb, int32_t nlow, const int64_t* urow,
-                                               int32_t* ucur, uint32_t lo, F f, long long& wtot, long long& rest) {
-  const int t = threadIdx.x;
-  for (int32_t c0 = 0; c0 < nlow; c0 += C4W_T) {
-    const int32_t q = c0 + t;
-    int64_t sb = 0;
-    int32_t sl = 0;
-    uint32_t fl = 0;
-    if (q < nlow) {
-      const int32_t c = ucur[q];
-      int32_t k = c;  // positions [k, c) are walked
-      if (c > 0) {
-        const int64_t base = urow[q];
-        const uint32_t* row = R.rcol + base;
-        fl = R.rcol[rb + q] & GC_FLAGS;
-        const int32_t a0 = (int32_t)(base & 3);  // row start within its 16-byte group
-        bool open = true;
-        while (open && c - k < C4W_SHORT) {
-          // one 16-byte load: the aligned group of four entries holding
-          // position k - 1.  Its positions in [0, k) with ids >= lo are a
-          // run ending at k - 1 (rows are sorted), so each entry is tested
-          // on its own; the walk goes on while the whole group was taken.
-          const int32_t top = k - 1;
-          const int32_t g = ((top + a0) & ~3) - a0;  // position of the group's first entry (>= -3)
-          const uint4 g4 = *(const uint4*)(row + g);
-          const uint32_t y[4] = {g4.x, g4.y, g4.z, g4.w};
-          int32_t took = 0;
+// and no search precedes it.  wc: the window's counters (FW bits each), cf:
+// the flags of an entry that counts there; slow(take, id, flags of both
+// entries) gets the others.  wtot += entries walked, rest += entries left below
+// the window (per thread).
+//
+// An entry y counts in the window exactly when y - (lo | cf) is below wsz as
+// an unsigned number: one subtract and one compare test the range and the
+// flags, entries past the cursor included (their ids are lo + wsz or more).
+// What bounds it is the latency of the rows' loads: 144 KB of counters leave
+// one workgroup per CU.  So the lanes read adjacent aligned 16-byte groups of
+// a row, four lanes a row for its first C4W_SHORT entries, then 16 lanes a
+// row, and each step's groups are loaded one step ahead.  (A lane per row for
+// 128 entries, then a gallop and the whole wave, took 100.5 ms at scale 22;
+// this 86, at 3.5 TB/s of lines from beyond the L2s for 1.6e11 bytes of
+// entries.  Unrolling the slow path costs more than it gives: beyond 128
+// registers the walk spills.)
+constexpr int32_t C4W_SHORT = 64;
+
+// one more in the counter of FW bits at offset o (FW = 0: 2^sh of them a word)
+template <int FW>
+__device__ __forceinline__ void window_add(uint32_t* wc, uint32_t o, int sh = 0) {
+  if constexpr (FW == 0) { atomicAdd(&wc[o >> sh], 1u << ((o << (5 - sh)) & 31u)); return; }
+  if constexpr (FW == 8) atomicAdd(&wc[o >> 2], 1u << ((o << 3) & 31u));
+  else if constexpr (FW == 16) atomicAdd(&wc[o >> 1], 1u << ((o << 4) & 31u));
+  else atomicAdd(&wc[o], 1u);
+}
+
+// LANES lanes walk the row at R.rcol + base (cursor k, flags of its own entry
+// fl) for at most `steps` steps of 4 LANES entries; k moves to the first
+// position not taken.  True while the row has more entries in the window.
+// The same base, k, fl on the lanes of a group; all lanes of the wave call it.
+template <int LANES, int FW, class S>
+__device__ __forceinline__ bool window_row(const uint32_t* __restrict__ rcol, int64_t base, int32_t& k, uint32_t fl,
+                                           bool open, int32_t steps, uint32_t lo, uint32_t wsz, uint32_t cf,
+                                           uint32_t* wc, int sh, S& slow) {
+  const int32_t gl = (int32_t)threadIdx.x & (LANES - 1);
+  const uint32_t lob = lo | cf;
+  const uint32_t* row = rcol + base;
+  const int32_t a0 = (int32_t)(base & 3);  // row start within its 16-byte group
+  // first entry of the topmost group: the one holding position k - 1; this
+  // lane's group is the gl-th below it
+  int32_t g0 = ((k - 1 + a0) & ~3) - a0, top = k - 1;
+  uint4 y = make_uint4(cf, cf, cf, cf);
+  if (open && g0 - 4 * gl > -4) y = *(const uint4*)(row + (g0 - 4 * gl));
+  for (int32_t step = 0; step < steps && __ballot(open); ++step) {
+    const int32_t g = g0 - 4 * gl;
+    const bool mine = open && g > -4;
+    uint4 yn = make_uint4(cf, cf, cf, cf);  // the next step's, if this one is taken whole
+    if (open && g - 4 * LANES > -4) yn = *(const uint4*)(row + (g - 4 * LANES));
+    const bool odd = mine && (((y.x ^ cf) | (y.y ^ cf) | (y.z ^ cf) | (y.w ^ cf) | (fl ^ cf)) & GC_FLAGS) != 0u;
+    int32_t took = 0;
+    if (__ballot(odd) == 0ull) {
+      uint32_t o[4] = {y.x - lob, y.y - lob, y.z - lob, y.w - lob};
+      if (step == 0) {  // entries past the cursor may be another row's
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const uint32_t id = y[u] & GC_ID;
-            const bool ok = g + u >= 0 && g + u <= top && id >= lo;
-            took += ok ? 1 : 0;
-            if (ok) f(id, fl | (y[u] & GC_FLAGS));
-          }
-          open = g > 0 && took == top + 1 - g;
-          k -= took;
-        }
-        if (open) {  // more than C4W_SHORT entries in the window
-          const int32_t p0 = gallop_down(row, k, lo);
-          sb = base + p0;
-          sl = k - p0;
-          k = p0;
-        }
-        ucur[q] = k;
+        for (int u = 0; u < 4; ++u) o[u] = g + u > top ? 0xFFFFFFFFu : o[u];
       }
+      if (__ballot(g < 0)) {  // and those before the row's start
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[u] = g + u < 0 ? 0xFFFFFFFFu : o[u];
+      }
+      if (mine) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (o[u] < wsz) {
+            window_add<FW>(wc, o[u], sh);
+            ++took;
+          }
+      }
+    } else {  // entries in the batch somewhere in the step
+#pragma unroll 1
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t e = u == 0 ? y.x : (u == 1 ? y.y : (u == 2 ? y.z : y.w)), id = e & GC_ID;
+        const uint32_t f = fl | (e & GC_FLAGS);
+        const bool in = mine && g + u >= 0 && g + u <= top && id >= lo;
+        if (in) {
+          ++took;
+          if (f == cf) window_add<FW>(wc, id - lo, sh);
+        }
+        slow(in && f != cf, id, f);
+      }
+    }
+    took = lanes_sum<LANES>(took);
+    // entries the groups hold of [0, top]: all taken, and more below?
+    const int32_t low = g0 - 4 * (LANES - 1);
+    if (open) {
+      k = top + 1 - took;
+      open = low > 0 && k == low;
+      top = low - 1;
+      g0 = low - 4;
+    }
+    y = yn;
+  }
+  return open;
+}
+
+template <int FW, class S>
+__device__ __forceinline__ void c4_window_walk(const RegionDev& R, int64_t rb, int32_t nlow, const int64_t* urow,
+                                               int32_t* ucur, uint32_t lo, uint32_t wsz, uint32_t cf, uint32_t* wc,
+                                               int sh, S slow, long long& wtot, long long& rest) {
+  const int32_t l = lane_id();
+  for (int32_t c0 = 0; c0 < nlow; c0 += C4W_T / 4) {
+    const int32_t q = c0 + ((int32_t)threadIdx.x >> 2);
+    uint32_t fl = cf;
+    int32_t c = 0, k = 0;  // positions [k, c) are walked
+    int64_t base = 0;
+    if (q < nlow) {
+      c = k = ucur[q];
+      base = urow[q];
+      fl = R.rcol[rb + q] & GC_FLAGS;
+    }
+    const bool open = window_row<4, FW>(R.rcol, base, k, fl, k > 0, C4W_SHORT / 16, lo, wsz, cf, wc, sh, slow);
+    // rows that go on: four at a time, 16 lanes each
+    for (uint64_t m = __ballot(open && (l & 3) == 0); m;) {
+      int src = -1;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int at = m ? __builtin_ctzll(m) : -1;
+        m &= m - 1;  // (0 stays 0)
+        if ((l >> 4) == r) src = at;
+      }
+      const int from = max(src, 0);
+      const int64_t b2 = __shfl(base, from);
+      int32_t k2 = __shfl(k, from);
+      const uint32_t f2 = (uint32_t)__shfl((int32_t)fl, from);
+      (void)window_row<16, FW>(R.rcol, b2, k2, f2, src >= 0, 1 << 30, lo, wsz, cf, wc, sh, slow);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {  // the cursor goes back to the row's quad
+        const int to = __shfl(src, 16 * r);
+        const int32_t kr = __shfl(k2, 16 * r);
+        if (to >= 0 && (l >> 2) == (to >> 2)) k = kr;
+      }
+    }
+    if ((l & 3) == 0 && q < nlow) {
+      ucur[q] = k;
       wtot += c - k;
       rest += k;
     }
-    if (__ballot(sl > 0))  // slices this long run to hundreds of entries: eight loads in flight per lane
-      wave_walk<8>(R.rcol, sb, sl, fl, [&](int, int64_t, uint32_t fs, uint32_t y) { f(y & GC_ID, fs | (y & GC_FLAGS)); });
   }
 }
 
 // Pair sums of one 16-byte piece of single-field window counters of FB bits:
-// s += c(c - 1) for every counter c, with no branch on zero counters.
+// s += c(c - 1) for every counter c, with no branch on zero counters.  The
+// scan of a window is as long as a few thousand wedges' walk, and there are
+// 40 windows per million wedges at scale 22: sums of squares and of counters
+// by dot products (a word of four 8-bit counters in two instructions).
 template <int FB>
 __device__ __forceinline__ void window_pairs(const uint4 q, uint64_t& s) {
   const uint32_t wv[4] = {q.x, q.y, q.z, q.w};
+  if constexpr (FB == 8) {
+    uint32_t sq = 0, sm = 0;  // at most 16 x 255^2
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    if constexpr (FB == 8) {
-      uint32_t p = 0;  // four products < 2^16 each
+    for (int k = 0; k < 4; ++k) {
+      sq = __builtin_amdgcn_udot4(wv[k], wv[k], sq, false);
+      sm = __builtin_amdgcn_udot4(wv[k], 0x01010101u, sm, false);
+    }
+    s += sq - sm;
+  } else {
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        const uint32_t a = (wv[k] >> (8 * b)) & 0xFFu;
-        p += a * (a - 1u);
+    for (int k = 0; k < 4; ++k) {
+      if constexpr (FB == 16) {
+        const uint32_t a = wv[k] & 0xFFFFu, b = wv[k] >> 16;
+        s += (uint64_t)(a * (a - 1u));  // < 2^32 for a < 2^16, and 0 for a = 0
+        s += (uint64_t)(b * (b - 1u));
+      } else {
+        s += (uint64_t)wv[k] * (uint64_t)(wv[k] - 1u);
       }
-      s += p;
-    } else if constexpr (FB == 16) {
-      const uint32_t a = wv[k] & 0xFFFFu, b = wv[k] >> 16;
-      s += (uint64_t)(a * (a - 1u));  // < 2^32 for a < 2^16, and 0 for a = 0
-      s += (uint64_t)(b * (b - 1u));
-    } else {
-      s += (uint64_t)wv[k] * (uint64_t)(wv[k] - 1u);
     }
   }
 }
@@ -1247,7 +1338,8 @@ __device__ __forceinline__ void window_pairs(const uint4 q, uint64_t& s) {
 // global counters are clear on entry and on return (each pass clears what it
 // read).
 template <int NV, int NF, int FBW>
-__device__ void c4_hub(const CountArgs& A, C4Smem& S, int32_t v, int vsh, int64_t (&acc)[NV], int64_t& tail_) {
+__device__ void c4_hub(const CountArgs& A, C4Smem& S, int32_t v, int64_t top, int64_t bot, int vsh,
+                       int64_t (&acc)[NV], int64_t& tail_) {
   using TFd = Fields<NF, 64 / NF>;
   constexpr int IPW = 32 / FBW;  // ids per 32-bit window word
   const RegionDev& R = A.R;
@@ -1270,24 +1362,32 @@ __device__ void c4_hub(const CountArgs& A, C4Smem& S, int32_t v, int vsh, int64_
   };
   if (t == 0) S.nt = 0;
   for (int32_t q = t; q < nlow; q += C4W_T) {
-    urow[q] = R.roff[R.rcol[rb + q] & GC_ID];
-    ucur[q] = R.vpos[rb + q];
+    const int64_t ub = R.roff[R.rcol[rb + q] & GC_ID];
+    int32_t c = R.vpos[rb + q];
+    if (top < v) c = lower_bound_id(R.rcol + ub, c, (uint32_t)top);
+    urow[q] = ub;
+    ucur[q] = c;
   }
   __syncthreads();
-  int64_t hi = v;
-  while (hi > 0) {
+  int64_t hi = top;
+  while (hi > bot) {
     int64_t wsz = ws;
     sh = FBW == 16 ? 1 : 0;
     fw = FBW;
     if constexpr (FBW == 16) {
-      // 8-bit fields over twice the ids when no row there is longer than 255
-      const int64_t lo8 = hi - 2 * ws > 0 ? hi - 2 * ws : 0;
-      const int64_t b0 = lo8 >> C4_BLK_LOG, b1 = (hi - 1) >> C4_BLK_LOG;
-      int32_t m = 0;
-      for (int64_t b = b0 + t; b <= b1; b += C4W_T) m = max(m, A.c4_blk[b]);
-      if (block_max32(S.C, m) <= 255) { sh = 2; fw = 8; wsz = 2 * ws; }
+      // 8-bit fields over twice the ids when c(v, w) <= 255: v has no more
+      // lower neighbours, or no row there is longer
+      int32_t m = nlow;
+      if (nlow > 255) {
+        const int64_t lo8 = hi - 2 * ws > bot ? hi - 2 * ws : bot;
+        const int64_t b0 = lo8 >> C4_BLK_LOG, b1 = (hi - 1) >> C4_BLK_LOG;
+        m = 0;
+        for (int64_t b = b0 + t; b <= b1; b += C4W_T) m = max(m, A.c4_blk[b]);
+        m = block_max32(S.C, m);
+      }
+      if (m <= 255) { sh = 2; fw = 8; wsz = 2 * ws; }
     }
-    const uint32_t lo = (uint32_t)(hi - wsz > 0 ? hi - wsz : 0);
+    const uint32_t lo = (uint32_t)(hi - wsz > bot ? hi - wsz : bot);
     const int32_t wcap = (int32_t)(hi - lo);  // list capacity: ids of the window (<= N)
     if (t == 0) {
       atomicAdd(&A.bstats[BS_C4_SEARCH], (unsigned long long)nlow);
@@ -1295,27 +1395,35 @@ __device__ void c4_hub(const CountArgs& A, C4Smem& S, int32_t v, int vsh, int64_
     }
     long long wtot = 0, rest = 0;
     // the window walk with the field layout as constants (8-bit fields, or FBW)
-    auto walk = [&](auto fwc) {
-      constexpr int FW = decltype(fwc)::value;
-      constexpr int SH = FW == 8 ? 2 : (FW == 16 ? 1 : 0);
-      constexpr uint32_t IM = (1u << SH) - 1u;
-      c4_window_walk(R, rb, nlow, urow, ucur, lo,
-                     [&](uint32_t wid, uint32_t fl) {
-                       const uint32_t sub = (vpresent<NV>(fl) >> vsh) & fmask;
-                       const uint32_t o = wid - lo;
-                       if (sub == ref) {
-                         atomicAdd(&wc[o >> SH], 1u << (FW * (o & IM)));
-                       } else if (sub) {  // present in some versions only
-                         // no wait for the global atomic: the id is listed once per
-                         // exception wedge (while the list is shorter than the window)
-                         atomicAdd(&cnt[wid], (unsigned long long)TFd::spread(sub));
-                         const int32_t p = atomicAdd(&S.nt, 1);
-                         if (p < wcap) touch[p] = (int32_t)wid;
-                       }
-                     },
-                     wtot, rest);
+    // wedges with an entry in the batch, on the lanes with `take` (all lanes call it)
+    auto other = [&](bool take, uint32_t wid, uint32_t fl) {
+      const uint32_t sub = (vpresent<NV>(fl) >> vsh) & fmask;
+      if (take && sub == ref) {
+        const uint32_t o = wid - lo;
+        window_add<0>(wc, o, sh);
+      }
+      const bool some = take && sub != 0u && sub != ref;  // present in some versions only
+      const uint64_t m = __ballot(some);
+      if (!m) return;
+      // no wait for the global atomic: the id is listed once per
+      // exception wedge (while the list is shorter than the window)
+      int32_t at = 0;
+      if (lane_id() == 0) at = atomicAdd(&S.nt, (int32_t)__popcll(m));
+      at = rdl32(at, 0) + (int32_t)__popcll(m & lanemask_lt());
+      if (some) {
+        atomicAdd(&cnt[wid], (unsigned long long)TFd::spread(sub));
+        if (at < wcap) touch[at] = (int32_t)wid;
+      }
     };
-    if (fw == 8) walk(std::integral_constant<int, 8>{});
+    // flags of the wedges the window counts (versions outside this walk's
+    // differing send an entry through other(), which counts it all the same)
+    const uint32_t cf = ((~ref & fmask) << vsh) << GC_VSHIFT;
+    auto walk = [&](auto fwc) {
+      c4_window_walk<decltype(fwc)::value>(R, rb, nlow, urow, ucur, lo, (uint32_t)wcap, cf, wc, sh, other, wtot, rest);
+    };
+    // (four versions: one copy of the walk for either width, to stay within the registers)
+    if constexpr (NV == 4) walk(std::integral_constant<int, 0>{});
+    else if (fw == 8) walk(std::integral_constant<int, 8>{});
     else walk(std::integral_constant<int, FBW>{});
     block_sum2(S.C, wtot, rest);  // also orders the window's counter updates before the passes below
     if (const int32_t nt = S.nt) {  // the window's exceptions
@@ -1350,7 +1458,8 @@ __device__ void c4_hub(const CountArgs& A, C4Smem& S, int32_t v, int vsh, int64_
     {
       uint4* w4 = (uint4*)S.win;
       uint64_t s2 = 0;
-      for (int qi = t; qi < A.c4_win / 2; qi += C4W_T) {
+      const int nq = min(((wcap >> sh) + 4) >> 2, A.c4_win / 2);  // 16-byte pieces that hold the window's ids
+      for (int qi = t; qi < nq; qi += C4W_T) {
         const uint4 q = w4[qi];
         w4[qi] = make_uint4(0u, 0u, 0u, 0u);
         if (fw == 8) window_pairs<8>(q, s2);
@@ -1363,7 +1472,7 @@ __device__ void c4_hub(const CountArgs& A, C4Smem& S, int32_t v, int vsh, int64_
     __syncthreads();
     hi = lo;
     if (rest == 0) break;
-    if (wtot < A.c4_dense_min) {
+    if (wtot < A.c4_dense_min && bot == 0) {  // (a range above others is dense throughout)
       // sparse from here down: every remaining wedge in global memory
       const int32_t tcap = (int32_t)lo;  // list capacity: the ids below the windows (<= N)
       c4_block_walk(R, rb, nlow, urow, [&](int32_t) { return 0; }, [&](int32_t q) { return ucur[q]; },
@@ -1406,8 +1515,7 @@ template <int NV>
 __global__ __launch_bounds__(C4W_T) void k_c4_large(CountArgs A, unsigned long long* qhead) {
   __shared__ C4Smem S;
   const RegionDev& R = A.R;
-  const int64_t n = (int64_t)A.c[C_LIST0 + L_C4_L];
-  const int32_t* list = A.lists + L_C4_L * A.list_stride;
+  const int64_t n = (int64_t)A.c[C_C4I];
   const int t = threadIdx.x;
   int cur_g = -1;
   int64_t acc[NV];
@@ -1420,24 +1528,48 @@ __global__ __launch_bounds__(C4W_T) void k_c4_large(CountArgs A, unsigned long l
     __syncthreads();
     const int64_t item = S.item;
     if (item >= n) break;
-    const int32_t v = list[item];
+    const unsigned long long e = A.c4_keys_alt[item];
+    const int32_t v = (int32_t)(uint32_t)e;
     const int g = A.gid[v];
     if (g != cur_g) { if (cur_g >= 0) flushv<NV>(A.sig, cur_g, SG_C4, acc); cur_g = g; }
     if (R.rlow[v] > A.c4_maxlow) {  // cursor scratch too small: the host counts again with more
       if (t == 0) atomicAdd(&A.bstats[BS_RETRY], 1ull);
       continue;
     }
+    // the item's ids [bot, top): all below v, or one of `cut` ranges that hold
+    // about equal shares of the graph's entries below v
+    const int part = (int)(e >> 32) & 0xFF, cut = (int)(e >> 40);
+    int64_t top = v, bot = 0;
+    if (cut > 1) {
+      if (t < 64) {  // the graph's first vertex, then the two cuts
+        int64_t lo = 0, hi = v;  // gid[hi] == g
+        while (hi > lo) {
+          const int64_t st = (hi - lo + 63) / 64, at = min(lo + st * lane_id(), hi);
+          const int k = __popcll(__ballot(A.gid[at] < g));  // samples before the graph
+          hi = min(hi, lo + st * k);
+          lo = k ? min(lo + st * (k - 1) + 1, hi) : lo;
+        }
+        const int64_t r0 = R.roff[hi], all = R.roff[v] - r0;
+        const int64_t x = part == 0 ? v : wave_upper_bound(R.roff, v, r0 + all / cut * (cut - part));
+        const int64_t y = part == cut - 1 ? 0 : wave_upper_bound(R.roff, v, r0 + all / cut * (cut - part - 1));
+        if (lane_id() == 0) { S.cut[0] = x; S.cut[1] = y; }
+      }
+      __syncthreads();
+      top = S.cut[0];
+      bot = S.cut[1];
+    }
+    if (top <= bot) continue;
     // c(v, w) <= nlow: 16-bit fields suffice up to 65535 lower neighbours
     const bool narrow = R.rlow[v] <= A.c4_narrow_max;
     if constexpr (NV == 2) {
-      if (narrow) c4_hub<2, 2, 16>(A, S, v, 0, acc, tail_);
-      else c4_hub<2, 2, 32>(A, S, v, 0, acc, tail_);
+      if (narrow) c4_hub<2, 2, 16>(A, S, v, top, bot, 0, acc, tail_);
+      else c4_hub<2, 2, 32>(A, S, v, top, bot, 0, acc, tail_);
     } else {
       if (narrow) {
-        c4_hub<4, 4, 16>(A, S, v, 0, acc, tail_);
+        c4_hub<4, 4, 16>(A, S, v, top, bot, 0, acc, tail_);
       } else {
-        c4_hub<4, 2, 32>(A, S, v, 0, acc, tail_);
-        c4_hub<4, 2, 32>(A, S, v, 2, acc, tail_);
+        c4_hub<4, 2, 32>(A, S, v, top, bot, 0, acc, tail_);
+        c4_hub<4, 2, 32>(A, S, v, top, bot, 2, acc, tail_);
       }
     }
   }
@@ -1463,11 +1595,49 @@ __global__ void k_c4_blkmax(const int64_t* __restrict__ roff, int64_t N, int32_t
   }
 }
 
-// hubs of the large tier in decreasing order of wedge work (roughly: the
-// order only starts the long ones first)
-__global__ void k_c4_order(const unsigned long long* sorted, const unsigned long long* c, int32_t* list) {
-  const int64_t n = (int64_t)c[C_LIST0 + L_C4_L];
-  for (int64_t i = gtid(); i < n; i += gstride()) list[i] = (int32_t)(sorted[i] >> 8);
+// Items of the large tier: a hub, or one of the id ranges a large hub is cut
+// into (the opposite vertices of different ranges are counted apart), in
+// decreasing order of wedge work: the workgroups then walk hubs of about the
+// same size through the same windows at the same time, and find the rows in
+// the shared cache (in loose order the count at scale 22 took 115 ms instead
+// of 90).  One workgroup walks about 1.5e9 wedges a second, so a hub with
+// more than 1/1024 of all wedges sets the time of a small graph's count.
+constexpr int64_t C4_ITEMS = 1024;        // pieces the whole work is cut to
+constexpr int64_t C4_ITEM_MIN = 65536;    // wedges that pay for a range's cursor searches
+constexpr int64_t C4_CUT_MAX = 32;        // ranges per hub
+
+__global__ __launch_bounds__(1024) void k_c4_items(const unsigned long long* sorted, unsigned long long* cc,
+                                                   const unsigned long long* bstats, int64_t N,
+                                                   unsigned long long* items) {
+  __shared__ int32_t ws[2][16];
+  const int64_t n = (int64_t)cc[C_LIST0 + L_C4_L];
+  const int64_t target = max((int64_t)bstats[BS_C4_L] / C4_ITEMS, C4_ITEM_MIN);
+  const int64_t most = max((int64_t)1, min(C4_CUT_MAX, N / max(n, (int64_t)1)));  // the list holds N items
+  const int l = lane_id(), w = threadIdx.x >> 6;
+  int64_t base = 0;
+  int ph = 0;
+  for (int64_t b0 = 0; b0 < n; b0 += 1024, ph ^= 1) {
+    int32_t cut = 0;
+    unsigned long long v = 0;
+    if (b0 + threadIdx.x < n) {
+      const unsigned long long key = sorted[b0 + threadIdx.x];
+      v = key >> 16;
+      const int q = 65535 - (int)(key & 65535ull), e = q >> 11;  // work: (2048 + q % 2048) 2^(e - 11)
+      const int64_t work = ((int64_t)(2048 + (q & 2047)) << e) >> 11;
+      cut = (int32_t)max((int64_t)1, min(most, (work + target - 1) / target));
+    }
+    const int32_t incl = wave_incl_scan32(cut);
+    if (l == 63) ws[ph][w] = incl;
+    __syncthreads();  // the other phase's sums are read no more once all are here
+    int64_t at = base + incl - cut;
+    for (int k = 0; k < 16; ++k) {
+      at += k < w ? ws[ph][k] : 0;
+      base += ws[ph][k];
+    }
+    for (int32_t k = 0; k < cut; ++k)
+      items[at + k] = v | ((unsigned long long)k << 32) | ((unsigned long long)cut << 40);
+  }
+  if (threadIdx.x == 0) cc[C_C4I] = (unsigned long long)base;
 }
 
 // --------------------------------------------------------------- combine
@@ -1558,9 +1728,10 @@ void launch_count_t(const CountArgs& A, hipStream_t s, hipEvent_t* ev) {
   hipLaunchKernelGGL(k_c4_mid<NV>, dim3(cap_grid(N, 4096)), dim3(256), 0, s, A);
   if (ev) (void)hipEventRecord(ev[4], s);
   // order the hubs by decreasing wedge work (keys written by the per-vertex pass)
-  unsigned long long* sk = radix_sort_u64(A.c4_keys, A.c4_keys_alt, A.sort_tmp, N, A.c + C_LIST0 + L_C4_L, 8, s);
-  hipLaunchKernelGGL(k_c4_order, dim3(cap_grid((N + 255) / 256, 1024)), dim3(256), 0, s, sk, A.c,
-                     (int32_t*)(A.lists + L_C4_L * A.list_stride));
+  unsigned long long* sk = radix_sort_u64(A.c4_keys, A.c4_keys_alt, A.sort_tmp, N, A.c + C_LIST0 + L_C4_L, 16, s);
+  // two digits: the keys are back where they were written, the other buffer takes the items
+  hipLaunchKernelGGL(k_c4_items, dim3(1), dim3(1024), 0, s, (const unsigned long long*)sk, (unsigned long long*)A.c,
+                     (const unsigned long long*)A.bstats, N, A.c4_keys_alt);
   fill_u32((uint32_t*)A.c4_blk, 0u, N / C4_BLK + 2, s);
   hipLaunchKernelGGL(k_c4_blkmax, dim3(cap_grid((N + 1023) / 1024, 4096)), dim3(256), 0, s, A.R.roff, N, A.c4_blk);
   hipLaunchKernelGGL(k_c4_large<NV>, dim3(cap_grid(N, (unsigned)A.slots)), dim3(C4W_T), 0, s, A,

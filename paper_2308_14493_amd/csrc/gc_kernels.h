@@ -20,6 +20,7 @@ enum {
   C_QTRI,                  // C_QTRI + k: queue head of list L_TRI_1 + k (k < 6)
   C_QTS = C_QTRI + 6,      // queue heads of the small triangle tier and of the mid 4-cycle tier
   C_QC4M,
+  C_C4I,                   // items of the large 4-cycle tier
   C_COUNT
 };
 // Work lists: triangles by out-degree (<= 64 one wave per vertex, then the
@@ -156,7 +157,7 @@ struct CountArgs {
   int32_t* c4_blk;                // [N / C4_BLK + 1] largest union row length per block of C4_BLK ids
   int64_t c4_maxlow;              // largest lower degree of a large-tier vertex
   unsigned long long* c4_keys;    // [N] sort keys of the large tier (written by the per-vertex pass)
-  unsigned long long* c4_keys_alt;
+  unsigned long long* c4_keys_alt;  // [N] wedge sums, then the sort's buffer, then the tier's items
   void* sort_tmp;
   int32_t tri_slots;              // workgroups of the global-scratch triangle tier
   unsigned long long* tri_scratch;  // [tri_slots][tri_scratch_words64(tri_cap)] above the LDS tier

@@ -640,8 +640,8 @@ __device__ __forceinline__ int64_t uniform64(int64_t x) {
 // for the 4-cycle kernels as the starting cursor in row w) and their sum per
 // v; per entry absent from a version, the count that v's degree lacks there.
 // One lane per entry, whatever the row: a wave that held 64 whole rows waited
-// for its longest (0.72 ms at scale 18, now 0.1; 9.5 ms at scale 22, now
-// 5.3).  Consecutive entries share a row, so its sums cost one atomic per
+// for its longest (0.72 ms at scale 18, now 0.12; 9.5 ms at scale 22, where
+// no row stands out as much, now 8.8).  Consecutive entries share a row, so its sums cost one atomic per
 // wave.  Bound by the dependent loads of the searches.
 template <int NV>
 __global__ __launch_bounds__(TPB) void k_entries(RegionDev R, const unsigned long long* cc,
@@ -753,10 +753,10 @@ __global__ __launch_bounds__(TPB) void k_degrees(RegionDev R, const int32_t* __r
     dec.tri = tri ? tri_list_of(dplus, tri_small) : -1;
     dec.c4 = c4 ? (wsum <= c4_small ? L_C4_S : (wsum <= c4_mid ? L_C4_M : L_C4_L)) : -1;
     if (dec.c4 == L_C4_L) {
-      // by falling wedge work, to an eighth of a factor of two: one digit
+      // by falling wedge work, to 1/2048 of a factor of two: two digits
       const uint32_t wk = wsum < 0xFFFFFFFFll ? (uint32_t)wsum : 0xFFFFFFFFu, e = 31u - (uint32_t)__clz(wk);
-      const uint32_t q = e * 8u + (e >= 3u ? (wk >> (e - 3u)) & 7u : 0u);
-      dec.key = ((unsigned long long)(uint32_t)v << 8) | (255u - q);
+      const uint32_t q = (e << 11) | ((e >= 11u ? wk >> (e - 11u) : wk << (11u - e)) & 2047u);
+      dec.key = ((unsigned long long)(uint32_t)v << 16) | (65535u - q);
     }
     if (tri) maxdp = dplus > maxdp ? dplus : maxdp;
     if (c4) {
