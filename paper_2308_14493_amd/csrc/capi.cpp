@@ -143,6 +143,10 @@ constexpr int C4_MID_MAX = 4096;
 
 void gc_set_error(const char* msg) { g_err = msg ? msg : ""; }
 
+// Bytes of the triangle counts t and td of E entries: two halves, each cleared
+// four entries at a time.
+size_t t_bytes(int64_t E) { return (size_t)E * 8 + 32; }
+
 // Device bytes a single-graph handle reaches, from the sizing rules of
 // build(), alloc_vertex_arrays() and size_count_scratch() (multi-version
 // passes included), for a graph of n vertices and m edges whose largest
@@ -337,7 +341,8 @@ struct gc_graph {
     R.rlow = rlow.as<int32_t>();
     R.rrow = rrow.as<int32_t>();
     R.d = dver.as<int32_t>();
-    R.t = t.as<unsigned long long>();
+    R.t = t.as<uint32_t>();
+    R.td = t.as<int32_t>() + t.cap / 8 / 4 * 4;  // the second half, at a multiple of 16 bytes
     R.tp = tp.as<unsigned long long>();
     R.vpos = vpos.as<int32_t>();
     return R;
@@ -390,7 +395,7 @@ void size_count_scratch(gc_graph* G, int nv, int64_t entries) {
   const int64_t E = G->e_alloc;
   G->rcol.ensure(E * sizeof(uint32_t));
   G->rrow.ensure(E * sizeof(int32_t));
-  G->t.ensure(E * sizeof(unsigned long long));
+  G->t.ensure(t_bytes(E));
   G->vpos.ensure(E * sizeof(int32_t));
   if (nv > 2) G->tp.ensure(2 * E * sizeof(unsigned long long));
   G->dver.ensure((size_t)N * GC_NV_MAX * sizeof(int32_t));
@@ -442,7 +447,7 @@ const char* count_scratch_short(const gc_graph* G, int nv, int64_t entries) {
   if (entries > G->e_alloc) return "region view (entries)";
   const int64_t E = G->e_alloc;
   if (!has(G->rcol, E * sizeof(uint32_t)) || !has(G->rrow, E * sizeof(int32_t)) ||
-      !has(G->t, E * sizeof(unsigned long long)) || !has(G->vpos, E * sizeof(int32_t)))
+      !has(G->t, t_bytes(E)) || !has(G->vpos, E * sizeof(int32_t)))
     return "region view (arrays)";
   if (nv > 2 && !has(G->tp, 2 * E * sizeof(unsigned long long))) return "multi-version triangle counts";
   if (!has(G->dver, (size_t)N * GC_NV_MAX * sizeof(int32_t))) return "per-version degrees";

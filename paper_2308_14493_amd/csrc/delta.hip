@@ -1011,8 +1011,7 @@ __global__ __launch_bounds__(TPB) void k_tv_entries(PoolDev P, RegionDev R, cons
       v = R.rrow[p];
       if ((int64_t)w > (int64_t)v) {
         if constexpr (NV == 2) {
-          const unsigned long long x = R.t[p];
-          d = (int64_t)(x >> 32) - (int64_t)(x & 0xFFFFFFFFull);
+          d = R.td[p];
         } else {
           // t_x = t[p] + field x of tp[2p] (x = 0, 1) and tp[2p + 1] (x = 2, 3)
           d = (int64_t)(R.tp[2 * p + 1] >> 32) - (int64_t)(R.tp[2 * p] & 0xFFFFFFFFull);

@@ -95,10 +95,12 @@ struct RegionDev {
   int32_t* rrow;       // [E_R] row (vertex) of every entry
   int32_t* d;          // [N][NV] degree of v in version x inside the region: d[v * NV + x]
   // triangles through the edge of each entry, per version.  Two versions:
-  // t[p] = t_0 | t_1 << 32.  Four versions: t_x = t[p] + field x of the
-  // 32-bit pairs tp[2p] (x = 0, 1) and tp[2p + 1] (x = 2, 3) (t[p] holds the
-  // triangles present in every version, tp the others)
-  unsigned long long* t;   // [E_R]
+  // t_0 = t[p], t_1 = t[p] + td[p].  Four versions: t_x = t[p] + field x of
+  // the 32-bit pairs tp[2p] (x = 0, 1) and tp[2p + 1] (x = 2, 3) (t[p] holds
+  // the triangles present in every version, tp the others).  Most triangles
+  // are present in every version: one 32-bit atomic on a dense array.
+  uint32_t* t;             // [E_R] (rounded up to 4)
+  int32_t* td;             // [E_R] (rounded up to 4; two versions only)
   unsigned long long* tp;  // [2 E_R] (four versions only)
   int32_t* vpos;       // [E_R] per lower entry v -> w: position of v in row w
 };
@@ -220,6 +222,3 @@ void fill_u64(unsigned long long* p, unsigned long long v, int64_t n, hipStream_
 // three arrays cleared by one launch
 void zero3_u64(unsigned long long* a, int64_t na, unsigned long long* b, int64_t nb, unsigned long long* c, int64_t nc,
                hipStream_t s);
-// p[i] = v for i < min(mult * (*count), max_n), count on the device
-void fill_u64_count(unsigned long long* p, unsigned long long v, const unsigned long long* count, int64_t mult,
-                    int64_t max_n, hipStream_t s);
