@@ -173,7 +173,7 @@ typedef struct {
   int64_t c4_windows;                /* dense LDS windows of the large 4-cycle tier */
   int64_t c4_searches;               /* cursor visits of that tier (lower neighbours x window passes) */
   int64_t tri_global_vertices;       /* vertices whose out-degree exceeds the LDS triangle tiers (global scratch) */
-  int64_t tri_exc_rebuilds;          /* triangle-tier vertices counted once per version (too many version-specific edges) */
+  int64_t tri_exc_rebuilds;          /* triangle-tier vertices probed once per version (more version-specific edges than their list holds) */
   int32_t retries;                   /* counting stages run again after growing scratch for a larger vertex */
   int32_t delta;                     /* 1: the pass was edge-local (gc_options.delta) */
   int64_t tri_entries;               /* adjacency entries read by the triangle tiers (N+(u) and each N+(v) probed) */

@@ -475,9 +475,11 @@ __global__ __launch_bounds__(256) void k_tri_small(CountArgs A) {
 // equal P_x share one count).  Edges among N+(u) that are absent from some
 // version are few; the triangles of E that contain such an edge absent from
 // version x are removed from K4_x one by one (each once, at its first such
-// edge in list order).  If the list overflows, the matrix is rebuilt per
-// version instead.
-constexpr int TL_EXC = 256;  // edges with flags tracked per vertex
+// edge in list order), or the edges are taken out of the matrix and K4_x
+// counted for each version alone.  If the list overflows, the matrix is
+// rebuilt per version instead.
+constexpr int TL_EXC = 256;       // edges with flags tracked per vertex (twice as many above 128 slots)
+constexpr int32_t EXC_DP = 1 << 14;  // largest out-degree they are tracked for
 
 // Words of the triangular bit matrix of n slots with W words per full row:
 // row i keeps only words (i >> 6) .. W - 1 (its bits j > i).
@@ -491,8 +493,10 @@ struct TriL {
   using TU = typename Fields<NV, 16>::T;  // per-slot triangle counts, 16-bit field per version
   unsigned long long* E;    // triangular row bitsets, tri_words(dp, W) words
   // word w >= (i >> 6) of row i is erow(i)[w]
+  // (32 bits hold the index: a slot of 2^31 words would not fit the memory)
   __device__ __forceinline__ unsigned long long* erow(int32_t i) const {
-    return E + tri_words(i, W) - (i >> 6);
+    const int32_t b = i >> 6;
+    return E + (uint32_t)(i * W - (32 * b * (b - 1) + (i - 64 * b) * b) - b);
   }
   unsigned long long* P;    // [NV][W] slot masks per version
   uint32_t* ids;            // [dp]
@@ -500,16 +504,11 @@ struct TriL {
   uint32_t* hval;           // [H] slot | its flags
   int32_t hcap;             // slots of hkey / hval (a power of two)
   TU* tuc;                  // [dp]
-  unsigned long long* exc;  // [TL_EXC] i << 32 | j << 4 | absence mask
+  int32_t xcap;             // entries of exc
+  uint32_t* exc;            // [xcap] i << 18 | j << 4 | absence mask
   int32_t* nexc;            // [1]
   int32_t W;                // words per row
 };
-
-template <int NV>
-__device__ __forceinline__ bool Ebit(const TriL<NV>& S, int32_t p, int32_t q) {  // edge between slots p != q
-  if (p > q) { int32_t t = p; p = q; q = t; }
-  return (S.erow(p)[q >> 6] >> (q & 63)) & 1ull;
-}
 
 __device__ __forceinline__ bool bit_of(const unsigned long long* m, int32_t k) { return (m[k >> 6] >> (k & 63)) & 1ull; }
 
@@ -549,8 +548,8 @@ __device__ __forceinline__ void tri_large_probe(const CountArgs& A, const TriL<N
     atomicOr(&Ei[j >> 6], 1ull << (j & 63));
     if (fy) {
       const int32_t p = atomicAdd(S.nexc, 1);
-      if (p < TL_EXC)
-        S.exc[p] = ((unsigned long long)i << 32) | ((unsigned long long)j << 4) | (unsigned long long)(fy >> GC_VSHIFT);
+      if (p < S.xcap)
+        S.exc[p] = ((uint32_t)i << 18) | ((uint32_t)j << 4) | (fy >> GC_VSHIFT);
     }
     const uint32_t pm = vpresent<NV>(fs | (jv & GC_FLAGS) | fy);
     if (!pm) return (TU)0;
@@ -577,25 +576,60 @@ __device__ __forceinline__ void tri_large_probe(const CountArgs& A, const TriL<N
   });
 }
 
-// sum over i in mask, j in E[i] & mask of |E[i] & E[j] & mask|  (one wave's rows)
+// kv[x] += sum over i in P_x, j in E[i] & P_x of |E[i] & E[j] & P_x|, for the
+// versions x of `vers` (one wave's rows).  Most bits of a row's words are 0:
+// the edges i -> j are packed into a list first (in hval, free by then), and
+// 64 of them at a time take a lane each, whose AND-popcounts serve every
+// version.  With a lane per bit of a word and a pass per version (and the
+// exceptions below searched slot by slot) k_tri_large<128> took 1.01 ms on a
+// scale-18 graph with 5% of the edges in the batch, all tiers 81 ms at scale
+// 22; now 0.54 and 70 ms.
 template <int NV>
-__device__ __forceinline__ int64_t k4_rows(const TriL<NV>& S, const unsigned long long* mask, int32_t dp, int nwaves) {
+__device__ __forceinline__ void k4_edges(const TriL<NV>& S, int32_t dp, int nwaves, int vers, int64_t (&kv)[NV]) {
   const int w = threadIdx.x >> 6, l = lane_id();
-  int64_t cnt = 0;
-  for (int32_t i = w; i < dp; i += nwaves) {
-    if (!bit_of(mask, i)) continue;
+  const int32_t W = S.W;
+  uint32_t* qi = S.hval + w * 256;
+  uint32_t* qj = qi + 128;
+  int32_t n = 0;  // listed edges
+  auto run = [&](int32_t k) {
+    const int32_t i = (int32_t)qi[k], j = (int32_t)qj[k];
     const unsigned long long* Ei = S.erow(i);
-    for (int32_t w0 = i >> 6; w0 < S.W; ++w0) {
-      const unsigned long long m = Ei[w0] & mask[w0];
+    const unsigned long long* Ej = S.erow(j);
+    uint32_t c[NV];
+#pragma unroll
+    for (int x = 0; x < NV; ++x) c[x] = 0;
+    for (int32_t q = j >> 6; q < W; ++q) {
+      const unsigned long long e = Ei[q] & Ej[q];
+#pragma unroll
+      for (int x = 0; x < NV; ++x)
+        if ((vers >> x) & 1) c[x] += (uint32_t)__popcll(e & S.P[x * W + q]);
+    }
+#pragma unroll
+    for (int x = 0; x < NV; ++x)
+      if (((vers >> x) & 1) && bit_of(S.P + x * W, i) && bit_of(S.P + x * W, j)) kv[x] += c[x];
+  };
+  for (int32_t i = w; i < dp; i += nwaves) {
+    const unsigned long long* Ei = S.erow(i);
+    for (int32_t w0 = i >> 6; w0 < W; ++w0) {
+      const bool in = (Ei[w0] >> l) & 1ull;
+      const uint64_t m = __ballot(in);
       if (!m) continue;
-      if ((m >> l) & 1ull) {
-        const int32_t j = w0 * 64 + l;
-        const unsigned long long* Ej = S.erow(j);
-        for (int32_t q = j >> 6; q < S.W; ++q) cnt += __popcll(Ei[q] & Ej[q] & mask[q]);
+      if (in) {
+        const int32_t k = n + __popcll(m & lanemask_lt());
+        qi[k] = (uint32_t)i;
+        qj[k] = (uint32_t)(w0 * 64 + l);
+      }
+      n += __popcll(m);
+      if (n >= 64) {
+        n -= 64;
+        wave_sync();
+        run(n + l);
+        wave_sync();
       }
     }
   }
-  return cnt;
+  wave_sync();
+  if (l < n) run(l);
 }
 
 template <int NV>
@@ -632,87 +666,114 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
   if (threadIdx.x == 0) ent += dp;
   for (int32_t g0 = w; g0 < dp; g0 += nwaves * 64) tri_large_probe<NV>(A, S, hmask, shift, g0, nwaves, dp, 0, ent);
   __syncthreads();
-  const int32_t ne = *S.nexc;
-  if (ne <= TL_EXC) {
+  // more slots than an exception can name: as many exceptions as none could hold
+  const int32_t ne = dp <= EXC_DP || *S.nexc == 0 ? *S.nexc : INT32_MAX;
+  if (ne <= S.xcap && 4 * ne > (NV - 1) * dp) {
+    // Many of them: per version, the bits of the absent edges are taken out of
+    // E for its count and put back.  One by one each costs a few dozen
+    // instructions per 64 slots, a further count about as much as dp / 4 of
+    // them.  Scale 18 with 5% of the edges in the batch, <128> and <256>: 0.91
+    // and 0.67 ms all one by one, 0.54 and 0.54 with this; four versions with
+    // 0.5%: <256> 0.44 ms one by one, 0.54 with this from dp / 4 on.
+    auto flip = [&](int x, bool out) {
+      for (int32_t e = threadIdx.x; e < ne; e += blockDim.x) {
+        const uint32_t ex = S.exc[e];
+        const int32_t i = (int32_t)(ex >> 18), j = (int32_t)((ex >> 4) & 0x3FFFu);
+        if (!((ex >> x) & 1u)) continue;
+        unsigned long long* at = S.erow(i) + (j >> 6);
+        if (out) atomicAnd(at, ~(1ull << (j & 63)));
+        else atomicOr(at, 1ull << (j & 63));
+      }
+    };
+    for (int x = 0; x < NV; ++x) {
+      flip(x, true);
+      __syncthreads();
+      k4_edges<NV>(S, dp, nwaves, 1 << x, kacc);
+      __syncthreads();
+      if (x < NV - 1) flip(x, false);
+    }
+  } else if (ne <= S.xcap) {
     // versions with the same slot mask share one count
     int64_t kv[NV];
+    int same[NV], vers = 0;
 #pragma unroll
     for (int x = 0; x < NV; ++x) {
-      int same = -1;
-      for (int y = 0; y < x && same < 0; ++y) {
-        bool eq = true;
-        for (int32_t q = 0; q < W && eq; ++q) eq = S.P[x * W + q] == S.P[y * W + q];
-        if (eq) same = y;
-      }
-      if (same >= 0) {
+      kv[x] = 0;
+      same[x] = x;
 #pragma unroll
-        for (int y = 0; y < NV; ++y)
-          if (y == same) kv[x] = kv[y];
-      } else {
-        kv[x] = k4_rows<NV>(S, S.P + x * W, dp, nwaves);
+      for (int y = 0; y < x; ++y) {
+        bool eq = same[x] == x;
+        for (int32_t q = 0; q < W && eq; ++q) eq = S.P[x * W + q] == S.P[y * W + q];
+        if (eq) same[x] = y;
       }
+      if (same[x] == x) vers |= 1 << x;
     }
-    // The exceptions by slot pair, in the probe hash table (not read again
-    // for this vertex): key min << 16 | max, value the exception's index.
-    // Pairs are unique (each found from its lower slot's list only).
-    const bool keyed = dp <= 65536;
-    if (keyed) {
+    k4_edges<NV>(S, dp, nwaves, vers, kv);
+#pragma unroll
+    for (int x = 1; x < NV; ++x)
+#pragma unroll
+      for (int y = 0; y < x; ++y)
+        if (same[x] == y) kv[x] = kv[y];
+    if (ne > 0) {
+      // The exceptions by slot pair, in the probe hash table (not read again
+      // for this vertex): key min << 16 | max, value the exception's index.
+      // Pairs are unique (each found from its lower slot's list only).  The
+      // waves that still list edges use hval alone until the first barrier.
       for (int32_t k = threadIdx.x; k < H; k += blockDim.x) S.hkey[k] = -1;
       __syncthreads();
       for (int32_t e = threadIdx.x; e < ne; e += blockDim.x) {
-        const unsigned long long ex = S.exc[e];
-        const uint32_t a = (uint32_t)(ex >> 32), b = (uint32_t)((ex >> 4) & 0xFFFFFFFull);
-        const uint32_t key = (min(a, b) << 16) | max(a, b);
+        const uint32_t ex = S.exc[e], a = ex >> 18, b = (ex >> 4) & 0x3FFFu;
+        const uint32_t key = (a << 16) | b;  // a < b: found from the lower slot's list
         uint32_t h = hash32(key) >> shift;
         while (atomicCAS(&S.hkey[h], -1, (int32_t)key) != -1) h = (h + 1) & hmask;
         S.hval[h] = (uint32_t)e;
       }
       __syncthreads();
-    }
-    // index of the exception on slot pair (a, b), or -1
-    auto exc_of = [&](int32_t a, int32_t b) -> int32_t {
-      const uint32_t key = ((uint32_t)min(a, b) << 16) | (uint32_t)max(a, b);
-      uint32_t h = hash32(key) >> shift;
-      for (;;) {
-        const int32_t q = S.hkey[h];
-        if (q == -1) return -1;
-        if ((uint32_t)q == key) return (int32_t)S.hval[h];
-        h = (h + 1) & hmask;
-      }
-    };
-    // triangles of E (inside P_x) holding an edge absent from version x
-    const int l = lane_id();
-    for (int32_t e = w; e < ne; e += nwaves) {
-      const unsigned long long ex = S.exc[e];
-      const int32_t i = (int32_t)(ex >> 32), j = (int32_t)((ex >> 4) & 0xFFFFFFFull);
-      const uint32_t am = (uint32_t)(ex & 0xFull);
-#pragma unroll
-      for (int x = 0; x < NV; ++x) {
-        if (!((am >> x) & 1u)) continue;
-        const unsigned long long* Px = S.P + x * W;
-        if (!bit_of(Px, i) || !bit_of(Px, j)) continue;
-        int64_t sub = 0;
-        for (int32_t k = l; k < dp; k += 64) {
-          if (k == i || k == j || !bit_of(Px, k)) continue;
-          if (!Ebit<NV>(S, i, k) || !Ebit<NV>(S, j, k)) continue;
-          // count once: skip if an earlier listed edge of this triangle is absent from x
-          bool first = true;
-          if (keyed) {
-            const int32_t f1 = exc_of(i, k), f2 = exc_of(j, k);
-            if (f1 >= 0 && f1 < e && ((S.exc[f1] >> x) & 1ull)) first = false;
-            if (f2 >= 0 && f2 < e && ((S.exc[f2] >> x) & 1ull)) first = false;
-          } else {
-            for (int32_t f = 0; f < e && first; ++f) {
-              const unsigned long long ef = S.exc[f];
-              if (!((ef >> x) & 1ull)) continue;
-              const int32_t fi = (int32_t)(ef >> 32), fj = (int32_t)((ef >> 4) & 0xFFFFFFFull);
-              if ((fi == i && fj == k) || (fi == k && fj == i) || (fi == j && fj == k) || (fi == k && fj == j))
-                first = false;
-            }
-          }
-          sub += first;
+      // index of the exception on slot pair (a, b), or -1
+      auto exc_of = [&](int32_t a, int32_t b) -> int32_t {
+        const uint32_t key = ((uint32_t)min(a, b) << 16) | (uint32_t)max(a, b);
+        uint32_t h = hash32(key) >> shift;
+        for (;;) {
+          const int32_t q = S.hkey[h];
+          if (q == -1) return -1;
+          if ((uint32_t)q == key) return (int32_t)S.hval[h];
+          h = (h + 1) & hmask;
         }
-        kv[x] -= sub;
+      };
+      // Triangles of E (inside P_x) holding an edge i -> j absent from version
+      // x: the slots adjacent to both, 64 at a time.  Above i they are the words
+      // of row i, below it bit i of their own rows.
+      const int l = lane_id();
+      for (int32_t e = w; e < ne; e += nwaves) {
+        const uint32_t ex = S.exc[e];
+        const int32_t i = (int32_t)(ex >> 18), j = (int32_t)((ex >> 4) & 0x3FFFu);
+        int av = 0;
+#pragma unroll
+        for (int x = 0; x < NV; ++x)
+          if (((ex >> x) & 1u) && bit_of(S.P + x * W, i) && bit_of(S.P + x * W, j)) av |= 1 << x;
+        if (!av) continue;
+        const unsigned long long* Ei = S.erow(i);
+        const unsigned long long* Ej = S.erow(j);
+        for (int32_t c = 0; c < W; ++c) {
+          const int32_t k = 64 * c + l;
+          unsigned long long mi = 0, mj = 0, pm = 0;
+          if (c >= (i >> 6)) mi = Ei[c];
+          if (c <= (i >> 6)) mi |= __ballot(k < i && bit_of(S.erow(min(k, i)), i));
+          if (c >= (j >> 6)) mj = Ej[c];
+          if (c <= (j >> 6)) mj |= __ballot(k < j && bit_of(S.erow(min(k, j)), j));
+#pragma unroll
+          for (int x = 0; x < NV; ++x)
+            if ((av >> x) & 1) pm |= S.P[x * W + c];
+          if (!((mi & mj & pm) >> l & 1ull)) continue;
+          // count once: not where an earlier listed edge of this triangle is absent too
+          uint32_t early = 0;
+          const int32_t f1 = exc_of(i, k), f2 = exc_of(j, k);
+          if (f1 >= 0 && f1 < e) early |= S.exc[f1];
+          if (f2 >= 0 && f2 < e) early |= S.exc[f2];
+#pragma unroll
+          for (int x = 0; x < NV; ++x)
+            if (((av >> x) & 1) && ((S.P[x * W + c] >> l) & 1ull) && !((early >> x) & 1u)) --kv[x];
+        }
       }
     }
 #pragma unroll
@@ -723,13 +784,16 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
     for (int x = 0; x < NV; ++x) {
       __syncthreads();
       for (int64_t k = threadIdx.x; k < ew; k += blockDim.x) S.E[k] = 0ull;
+      for (int32_t k = threadIdx.x; k < dp; k += blockDim.x) {  // the slots again (k4_edges lists edges there)
+        const uint32_t y = S.ids[k], id = y & GC_ID;
+        uint32_t h = hash32(id) >> shift;
+        while (S.hkey[h] != (int32_t)id) h = (h + 1) & hmask;
+        S.hval[h] = (uint32_t)k | (y & GC_FLAGS);
+      }
       __syncthreads();
       for (int32_t g0 = w; g0 < dp; g0 += nwaves * 64) tri_large_probe<NV>(A, S, hmask, shift, g0, nwaves, dp, x + 1, ent);
       __syncthreads();
-      const int64_t c = k4_rows<NV>(S, S.P + x * W, dp, nwaves);
-#pragma unroll
-      for (int y = 0; y < NV; ++y)
-        if (y == x) kacc[y] += c;
+      k4_edges<NV>(S, dp, nwaves, 1 << x, kacc);
     }
   }
   __syncthreads();
@@ -746,7 +810,7 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
 }
 
 // global-scratch slot layout (u64 words): E [tri_words(cap, W)] | P [NV*W] |
-// tuc [cap] | exc [TL_EXC] | then u32 words: ids [cap] | hkey [4 cap] |
+// tuc [cap] | then u32 words: exc [2 TL_EXC] | ids [cap] | hkey [4 cap] |
 // hval [4 cap] | nexc [2]
 template <int NV>
 __host__ __device__ inline int64_t tri_slot_words64(int64_t cap) {
@@ -763,8 +827,11 @@ constexpr int pow2_at_least(int x) {
 // The vertices of work list L (out-degree at most CAP; CAP = 0 selects the
 // global-memory scratch), taken one at a time from the queue whose head is
 // qhead.
+// Registers: the tiers up to 256 hide their latencies with 6 waves per SIMD (5
+// with four versions, which spill below 96 registers); without the bound they
+// took 13.3 -> 17.8 ms and 9.5 -> 12.5 ms a count at scale 22.
 template <int CAP, int THREADS, int NV>
-__global__ __launch_bounds__(THREADS) void k_tri_large(CountArgs A, int L, unsigned long long* qhead) {
+__global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 : 5)) void k_tri_large(CountArgs A, int L, unsigned long long* qhead) {
   const RegionDev& R = A.R;
   const int64_t n = (int64_t)A.c[C_LIST0 + L];
   const int32_t* list = A.lists + L * A.list_stride;
@@ -784,8 +851,9 @@ __global__ __launch_bounds__(THREADS) void k_tri_large(CountArgs A, int L, unsig
     S.E = base;
     S.P = base + tri_words(cap, W);
     S.tuc = (TU*)(S.P + NV * W);
-    S.exc = S.P + NV * W + cap;
-    uint32_t* u32 = (uint32_t*)(S.exc + TL_EXC);
+    S.exc = (uint32_t*)(S.P + NV * W + cap);
+    S.xcap = 2 * TL_EXC;
+    uint32_t* u32 = S.exc + 2 * TL_EXC;
     S.ids = u32;
     S.hkey = (int32_t*)(u32 + cap);
     S.hval = u32 + 5 * cap;
@@ -796,15 +864,19 @@ __global__ __launch_bounds__(THREADS) void k_tri_large(CountArgs A, int L, unsig
   } else {
     constexpr int CW = CAP / 64;
     constexpr int HC = CAP <= 1024 ? pow2_at_least(8 * CAP) : pow2_at_least(2 * CAP);
+    static_assert(THREADS / 64 * 256 <= HC, "edge lists of k4_edges");
     __shared__ unsigned long long E[32 * CW * CW + 32 * CW];  // tri_words(CAP, CW)
     __shared__ unsigned long long P[NV * CW];
     __shared__ uint32_t ids[CAP];
     __shared__ TU tuc[CAP];
     __shared__ int32_t hkey[HC];
     __shared__ uint32_t hval[HC];
-    __shared__ unsigned long long exc[TL_EXC];
+    constexpr int XC = CAP > 128 ? 2 * TL_EXC : TL_EXC;
+    static_assert(CAP <= EXC_DP, "exceptions hold slots in 14 bits");
+    __shared__ uint32_t exc[XC];
     __shared__ int32_t nexc;
     S.E = E; S.P = P; S.ids = ids; S.tuc = tuc; S.hkey = hkey; S.hval = hval; S.exc = exc; S.nexc = &nexc;
+    S.xcap = XC;
     S.W = CW;
     S.hcap = HC;
   }
