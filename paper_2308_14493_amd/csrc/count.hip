@@ -41,35 +41,18 @@ __device__ __forceinline__ uint32_t hash32(uint32_t x) { return x * 2654435761u;
 
 __device__ __forceinline__ int32_t ld_relaxed(int32_t* p) { return __atomic_load_n(p, __ATOMIC_RELAXED); }
 
-// Lookups in two steps so that the lookups of several entries overlap:
-// read() loads the first two slots of the key's run (no branch between the
-// loads and their use), pos() picks the key's position from them, going on
-// in a loop only for longer runs (rare at load factor <= 1/2), and val()
-// reads the 32-bit value of a position.
+// Open addressing, linear probing; -1 marks a free slot.
 struct HashLook {
   const int32_t* keys;
-  const uint32_t* vals;
   uint32_t mask;
   int shift;
-  struct Two { uint32_t h; int32_t k0, k1; };
-  __device__ __forceinline__ Two read(uint32_t key) const {
-    const uint32_t h = hash32(key) >> shift;
-    return Two{h, keys[h], keys[(h + 1) & mask]};
-  }
-  __device__ __forceinline__ int pos(const Two& t, uint32_t key) const {
-    const int32_t k = (int32_t)key;
-    int r = t.k0 == k ? (int)t.h : (t.k1 == k ? (int)((t.h + 1) & mask) : -1);
-    if (r < 0 && t.k0 != -1 && t.k1 != -1) {
-      for (uint32_t q = (t.h + 2) & mask;; q = (q + 1) & mask) {
-        const int32_t kq = keys[q];
-        if (kq == k) { r = (int)q; break; }
-        if (kq == -1) break;
-      }
+  __device__ __forceinline__ int find(uint32_t key) const {  // position or -1
+    for (uint32_t h = hash32(key) >> shift;; h = (h + 1) & mask) {
+      const int32_t k = keys[h];
+      if (k == (int32_t)key) return (int)h;
+      if (k == -1) return -1;
     }
-    return r;
   }
-  __device__ __forceinline__ uint32_t val(int p) const { return vals[p]; }
-  __device__ __forceinline__ int find(uint32_t key) const { return pos(read(key), key); }  // position or -1
 };
 
 // add `add` to the counter of key (insert on first use)
@@ -173,61 +156,97 @@ __device__ __forceinline__ void wave_walk(const uint32_t* col, int64_t sb, int32
   }
 }
 
-__device__ __forceinline__ unsigned long long wave_or64(unsigned long long v) {
-  for (int o = 32; o > 0; o >>= 1) v |= (unsigned long long)__shfl_xor((long long)v, o);
-  return v;
-}
-template <class T>
-__device__ __forceinline__ T wave_add(T v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    if constexpr (sizeof(T) == 8) v += (T)__shfl_xor((long long)v, o);
-    else v += (T)__shfl_xor((int)v, o);
-  }
-  return v;
-}
-
-// The long lists of a wave's lanes (at least WALK_LONG entries), one at a
-// time through the whole wave: begin(s) -> per-list state; every entry y is
-// looked up (hl, key y & GC_ID) and f(state, s, pos, y, value) is called for
-// the keys found; end(state, s).  Each lane loads WALK_DEPTH entries (indexes
-// clamped to the list, so the loads need no branch), reads the hash slots of
-// all of them before picking any and their values before handling any, so
-// their memory and LDS accesses overlap.  The list's lane s is uniform, so
-// per-list work can be hoisted into begin/end.
-constexpr int WALK_DEPTH = 3;  // entries per lane loaded and looked up together (more waves fit than with 4)
-
-template <class B, class F, class E>
-__device__ __forceinline__ void wave_walk_long(const uint32_t* col, int64_t sb, int32_t sl, B begin,
-                                               const HashLook& hl, F f, E end) {
+// The entries of the lists of a wave's lanes (lane l: [sb, sb + sl) of col)
+// that are in a set of ids: f(s, pos, y) for every entry y at pos of lane s's
+// list whose bit in `filt` is set -- a superset of those in the set, which f
+// looks up.  filt holds 2^(32 - fsh) bits, one per hash value; about one id in
+// ten passes in the triangle tiers, so the ids that pass are packed into a
+// list in LDS (q, 256 words of the wave) and 64 at a time take a lane each:
+// the lookup and what a hit does, some 100 instructions, ran for nearly every
+// 64 entries before, for the few lanes that hit.  Long lists go one at a time
+// through the whole wave, 128 entries a step with the next step's loads in
+// flight (also across lists); short ones are flattened over the lanes.
+// Bound by issue (about 30 instructions per 64 entries) and, in dense graphs,
+// by the atomics of the hits.  Scale 22, a count: k_tri_small 12.1 -> 7.6 ms,
+// <128> 9.5 -> 6.5, <256> 13.3 -> 9.7, <512> 14.9 -> 12.9, <1024> 18.7 -> 18.2.
+template <class F>
+__device__ __forceinline__ void wave_probe(const uint32_t* __restrict__ col, int64_t sb, int32_t sl,
+                                           const uint32_t* filt, int fsh, uint32_t* q, F f) {
   const int l = lane_id();
-  uint64_t lm = __ballot(sl >= WALK_LONG);
-  while (lm) {
-    const int s = __builtin_ctzll(lm);
-    lm &= lm - 1;
-    const int64_t b = rdl64(sb, s);
-    const int32_t n = rdl32(sl, s);
-    auto st = begin(s);
-    for (int32_t k = l; k < n; k += 64 * WALK_DEPTH) {
-      uint32_t y[WALK_DEPTH], jv[WALK_DEPTH];
-      HashLook::Two tw[WALK_DEPTH];
-      int hp[WALK_DEPTH];
-#pragma unroll
-      for (int u = 0; u < WALK_DEPTH; ++u) y[u] = col[b + min(k + 64 * u, n - 1)];
-#pragma unroll
-      for (int u = 0; u < WALK_DEPTH; ++u) tw[u] = hl.read(y[u] & GC_ID);
-#pragma unroll
-      for (int u = 0; u < WALK_DEPTH; ++u) {
-        const int p = hl.pos(tw[u], y[u] & GC_ID);
-        hp[u] = k + 64 * u < n ? p : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < WALK_DEPTH; ++u) jv[u] = hl.val(max(hp[u], 0));
-#pragma unroll
-      for (int u = 0; u < WALK_DEPTH; ++u)
-        if (hp[u] >= 0) f(st, s, b + k + 64 * u, y[u], jv[u]);
+  int32_t n = 0;  // listed entries
+  auto run = [&](int32_t k, bool in) {
+    const uint32_t y = in ? q[k] : 0u, at = in ? q[128 + k] : 0u;
+    const int s = (int)(at >> 26);
+    const int64_t b = __shfl(sb, s);
+    f(s, b + (int64_t)(at & 0x3FFFFFFu), y, in);
+  };
+  // offsets in a list take 26 bits: the bit matrix of a vertex with more
+  // out-neighbours would not fit the memory
+  auto probe = [&](uint32_t y, bool in, uint32_t at) {
+    const uint32_t h = hash32(y & GC_ID) >> fsh;
+    const bool pass = in && ((filt[h >> 5] >> (h & 31u)) & 1u);
+    const uint64_t m = __ballot(pass);
+    if (!m) return;
+    if (pass) {
+      const int32_t k = n + __popcll(m & lanemask_lt());
+      q[k] = y;
+      q[128 + k] = at;
     }
-    end(st, s);
+    n += __popcll(m);
+    if (n >= 64) {
+      n -= 64;
+      wave_sync();
+      run(n + l, true);
+      wave_sync();
+    }
+  };
+  uint64_t lm = __ballot(sl >= WALK_LONG);
+  if (lm) {
+    int s = __builtin_ctzll(lm);
+    int64_t b = rdl64(sb, s);
+    int32_t len = rdl32(sl, s), k = 0;
+    uint32_t y0 = col[b + min(l, len - 1)], y1 = col[b + min(64 + l, len - 1)];
+    while (true) {
+      const int sc = s;
+      const int32_t kc = k, lc = len;
+      const uint32_t c0 = y0, c1 = y1;
+      bool more = true;
+      if (k + 128 < len) {
+        k += 128;
+      } else {
+        lm &= lm - 1;
+        more = lm != 0;
+        if (more) {
+          s = __builtin_ctzll(lm);
+          b = rdl64(sb, s);
+          len = rdl32(sl, s);
+          k = 0;
+        }
+      }
+      if (more) {
+        y0 = col[b + min(k + l, len - 1)];
+        y1 = col[b + min(k + 64 + l, len - 1)];
+      }
+      const uint32_t at = ((uint32_t)sc << 26) | (uint32_t)(kc + l);
+      probe(c0, kc + l < lc, at);
+      if (kc + 64 < lc) probe(c1, kc + 64 + l < lc, at + 64u);
+      if (!more) break;
+    }
   }
+  const int32_t ss = sl >= WALK_LONG ? 0 : sl;
+  const int32_t incl = wave_incl_scan32(ss);
+  const int32_t tot = __shfl(incl, 63), excl = incl - ss;
+  for (int32_t base = 0; base < tot; base += 64) {
+    const int32_t idx = base + l;
+    const int s = seg_of(excl, idx);
+    const int64_t sbs = __shfl(sb, s);
+    const int32_t k = idx - __shfl(excl, s);
+    const bool in = idx < tot;
+    probe(in ? col[sbs + k] : 0u, in, ((uint32_t)s << 26) | (uint32_t)(in ? k : 0));
+  }
+  wave_sync();
+  if (n) run(l, l < n);
+  wave_sync();
 }
 
 __device__ __forceinline__ unsigned long long pack2(uint32_t b, uint32_t a) {
@@ -351,8 +370,10 @@ constexpr int TS_WAVES = 4;
 
 template <int NV>
 __global__ __launch_bounds__(256) void k_tri_small(CountArgs A) {
-  __shared__ int32_t hkey[TS_WAVES][256];  // load factor <= 1/4
-  __shared__ uint32_t hval[TS_WAVES][256];  // slot | its flags
+  __shared__ int32_t hkey[TS_WAVES][128];   // load factor <= 1/2: few ids that are not there are looked up
+  __shared__ uint32_t hval[TS_WAVES][128];  // slot | its flags
+  __shared__ uint32_t filt[TS_WAVES][128];  // 4096 bits
+  __shared__ uint32_t queue[TS_WAVES][256];
   __shared__ unsigned long long EU[TS_WAVES][64], TU[TS_WAVES][64];
   __shared__ unsigned long long EX[TS_WAVES][NV][64], TX[TS_WAVES][NV][64];
   __shared__ uint32_t dirty[TS_WAVES];
@@ -378,29 +399,34 @@ __global__ __launch_bounds__(256) void k_tri_small(CountArgs A) {
     uint32_t vi = 0, fi = 0;
     if (l < dp) { const uint32_t x = R.rcol[ub + l]; vi = x & GC_ID; fi = x & GC_FLAGS; }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) hkey[w][l + 64 * q] = -1;
+    for (int q = 0; q < 2; ++q) { hkey[w][l + 64 * q] = -1; filt[w][l + 64 * q] = 0u; }
     EU[w][l] = 0; TU[w][l] = 0;
 #pragma unroll
     for (int x = 0; x < NV; ++x) { EX[w][x][l] = 0; TX[w][x][l] = 0; }
     if (l == 0) dirty[w] = 0;
     wave_sync();
     if (l < dp) {
-      uint32_t h = hash32(vi) >> 24;
-      while (atomicCAS(&hkey[w][h], -1, (int32_t)vi) != -1) h = (h + 1) & 255u;
+      const uint32_t fh = hash32(vi) >> 20;
+      atomicOr(&filt[w][fh >> 5], 1u << (fh & 31u));
+      uint32_t h = hash32(vi) >> 25;
+      while (atomicCAS(&hkey[w][h], -1, (int32_t)vi) != -1) h = (h + 1) & 127u;
       hval[w][h] = (uint32_t)l | fi;
     }
     wave_sync();
     int64_t sb = 0;
     int32_t sl = 0;
     if (l < dp) { sb = R.roff[vi] + R.rlow[vi]; sl = (int32_t)(R.roff[vi + 1] - sb); ent += 1 + sl; }
-    // one probe of list i: a hit (slot j with flags, jv) is the triangle
-    // (u, v_i, v_j); row i's bits collect in ei (the caller writes them)
-    const HashLook hl{hkey[w], hval[w], 255u, 24};
-    auto hit = [&](int i, int64_t pos, uint32_t fs, uint32_t y, uint32_t jv, unsigned long long& ei) {
+    // a hit of list i (slot j with flags, jv) is the triangle (u, v_i, v_j)
+    const HashLook hl{hkey[w], 127u, 25};
+    wave_probe(R.rcol, sb, sl, filt[w], 20, queue[w], [&](int i, int64_t pos, uint32_t y, bool in) {
+      const uint32_t fs = (uint32_t)__shfl((int32_t)fi, i);
+      if (!in) return;
+      const int p = hl.find(y & GC_ID);
+      if (p < 0) return;
+      const uint32_t jv = hval[w][p], fy = y & GC_FLAGS;
       const int j = (int)(jv & GC_ID);
-      const uint32_t fy = y & GC_FLAGS;
       const unsigned long long bj = 1ull << j, bi = 1ull << i;
-      ei |= bj;
+      atomicOr(&EU[w][i], bj);
       atomicOr(&TU[w][j], bi);
       if (fy) {
         dirty[w] = 1u;
@@ -410,22 +436,6 @@ __global__ __launch_bounds__(256) void k_tri_small(CountArgs A) {
       }
       const uint32_t pm = vpresent<NV>(fs | (jv & GC_FLAGS) | fy);
       if (pm) t_add<NV>(R, pos, pm);
-    };
-    struct LongState { int i; uint32_t fs; unsigned long long ei; };
-    wave_walk_long(
-        R.rcol, sb, sl,
-        [&](int s) { return LongState{s, (uint32_t)rdl32((int32_t)fi, s), 0ull}; }, hl,
-        [&](LongState& st, int, int64_t pos, uint32_t y, uint32_t jv) { hit(st.i, pos, st.fs, y, jv, st.ei); },
-        [&](LongState& st, int) {
-          const unsigned long long e = wave_or64(st.ei);
-          if (lane_id() == 0 && e) atomicOr(&EU[w][st.i], e);
-        });
-    wave_walk(R.rcol, sb, sl >= WALK_LONG ? 0 : sl, fi, [&](int i, int64_t pos, uint32_t fs, uint32_t y) {
-      const int p = hl.find(y & GC_ID);
-      if (p < 0) return;
-      unsigned long long ei = 0;
-      hit(i, pos, fs, y, hl.val(p), ei);
-      atomicOr(&EU[w][i], ei);
     });
     wave_sync();
     const bool clean = __ballot(l < dp && fi != 0) == 0ull && dirty[w] == 0u;
@@ -463,7 +473,11 @@ __global__ __launch_bounds__(256) void k_tri_small(CountArgs A) {
 }
 
 // ------------------------------------------------------ triangles, tier L
-// One workgroup per vertex u with out-degree above 64.  N+(u) goes into a
+// One workgroup per vertex u with out-degree above 64, twice as many threads
+// as slots up to 512: fewer vertices at a time, each done sooner, so the last
+// round of a tier is shorter.  Scale 18, <256> with 256 and 512 threads 0.54
+// and 0.42 ms, <512> 0.20 and 0.12, <128> 0.46 and 0.43; scale 22, where the
+// rounds are many, 9.1 and 9.7, 12.3 and 12.9, 6.3 and 6.5 ms.  N+(u) goes into a
 // hash (slot = position in the sorted suffix, i.e. id order).  The waves
 // walk the lists N+(v_i) of 64 slots i at a time, flattened over lanes: a
 // hit j is a triangle (u, v_i, w_j); it updates t of the three edges and
@@ -503,6 +517,9 @@ struct TriL {
   int32_t* hkey;            // [H]
   uint32_t* hval;           // [H] slot | its flags
   int32_t hcap;             // slots of hkey / hval (a power of two)
+  uint32_t* filt;           // [2^(27 - fsh)] bits of the ids in the table (wave_probe)
+  int32_t fsh;
+  uint32_t* queue;          // [256] per wave: entries that passed, then edges (k4_edges)
   TU* tuc;                  // [dp]
   int32_t xcap;             // entries of exc
   uint32_t* exc;            // [xcap] i << 18 | j << 4 | absence mask
@@ -534,52 +551,46 @@ __device__ __forceinline__ void tri_large_probe(const CountArgs& A, const TriL<N
     if (only == 0) ent += sl;
   }
   using TU = typename TriL<NV>::TU;
-  // one probe of list i: a hit (slot j with flags, jv) is the triangle
-  // (u, v_i, w_j); returns the increment of t(u, v_i), which the caller adds
-  // to tuc[i]
-  const HashLook hl{S.hkey, S.hval, hmask, shift};
-  auto hit = [&](int32_t i, unsigned long long* Ei, uint32_t fs, int64_t pos, uint32_t y, uint32_t jv) -> TU {
-    const int j = (int)(jv & GC_ID);
-    const uint32_t fy = y & GC_FLAGS;
+  // a hit of list i (slot j with flags, jv) is the triangle (u, v_i, w_j)
+  const HashLook hl{S.hkey, hmask, shift};
+  wave_probe(R.rcol, sb, sl, S.filt, S.fsh, S.queue + (threadIdx.x >> 6) * 256,
+             [&](int s, int64_t pos, uint32_t y, bool in) {
+    const uint32_t fs = (uint32_t)__shfl((int32_t)fi, s);
+    if (!in) return;
+    const int p = hl.find(y & GC_ID);
+    if (p < 0) return;
+    const uint32_t jv = S.hval[p], fy = y & GC_FLAGS;
+    const int32_t i = g0 + gs * s, j = (int32_t)(jv & GC_ID);
+    unsigned long long* at = S.erow(i) + (j >> 6);
     if (only) {
-      if (!absent_in(fy, only - 1)) atomicOr(&Ei[j >> 6], 1ull << (j & 63));
-      return (TU)0;
+      if (!absent_in(fy, only - 1)) atomicOr(at, 1ull << (j & 63));
+      return;
     }
-    atomicOr(&Ei[j >> 6], 1ull << (j & 63));
+    atomicOr(at, 1ull << (j & 63));
     if (fy) {
-      const int32_t p = atomicAdd(S.nexc, 1);
-      if (p < S.xcap)
-        S.exc[p] = ((uint32_t)i << 18) | ((uint32_t)j << 4) | (fy >> GC_VSHIFT);
+      const int32_t e = atomicAdd(S.nexc, 1);
+      if (e < S.xcap) S.exc[e] = ((uint32_t)i << 18) | ((uint32_t)j << 4) | (fy >> GC_VSHIFT);
     }
     const uint32_t pm = vpresent<NV>(fs | (jv & GC_FLAGS) | fy);
-    if (!pm) return (TU)0;
+    if (!pm) return;
     t_add<NV>(R, pos, pm);
     const TU add = Fields<NV, 16>::spread(pm);
     atomicAdd(&S.tuc[j], add);
-    return add;
-  };
-  struct LongState { int32_t i; unsigned long long* Ei; uint32_t fs; TU acc; };
-  wave_walk_long(
-      R.rcol, sb, sl,
-      [&](int s) { return LongState{g0 + gs * s, S.erow(g0 + gs * s), (uint32_t)rdl32((int32_t)fi, s), (TU)0}; }, hl,
-      [&](LongState& st, int, int64_t pos, uint32_t y, uint32_t jv) { st.acc += hit(st.i, st.Ei, st.fs, pos, y, jv); },
-      [&](LongState& st, int) {
-        const TU tot = wave_add<TU>(st.acc);
-        if (lane_id() == 0 && tot) atomicAdd(&S.tuc[st.i], tot);
-      });
-  wave_walk(R.rcol, sb, sl >= WALK_LONG ? 0 : sl, fi, [&](int s, int64_t pos, uint32_t fs, uint32_t y) {
-    const int p = hl.find(y & GC_ID);
-    if (p < 0) return;
-    const int32_t i = g0 + gs * s;
-    const TU add = hit(i, S.erow(i), fs, pos, y, hl.val(p));
-    if (add) atomicAdd(&S.tuc[i], add);
+    // the hits of the first lane's list (in a dense graph: most of the wave)
+    // add to the same word: one atomic for them
+    const bool mine = i == __builtin_amdgcn_readfirstlane(i);
+    TU tot = 0;
+#pragma unroll
+    for (int x = 0; x < NV; ++x) tot |= (TU)__popcll(__ballot(mine && ((pm >> x) & 1u))) << (16 * x);
+    const uint64_t act = __ballot(mine);
+    if (!mine) atomicAdd(&S.tuc[i], add);
+    else if (lane_id() == __builtin_ctzll(act)) atomicAdd(&S.tuc[i], tot);
   });
 }
 
 // kv[x] += sum over i in P_x, j in E[i] & P_x of |E[i] & E[j] & P_x|, for the
 // versions x of `vers` (one wave's rows).  Most bits of a row's words are 0:
-// the edges i -> j are packed into a list first (in hval, free by then), and
-// 64 of them at a time take a lane each, whose AND-popcounts serve every
+// the edges i -> j are packed into a list first, and 64 of them at a time take a lane each, whose AND-popcounts serve every
 // version.  With a lane per bit of a word and a pass per version (and the
 // exceptions below searched slot by slot) k_tri_large<128> took 1.01 ms on a
 // scale-18 graph with 5% of the edges in the batch, all tiers 81 ms at scale
@@ -588,7 +599,7 @@ template <int NV>
 __device__ __forceinline__ void k4_edges(const TriL<NV>& S, int32_t dp, int nwaves, int vers, int64_t (&kv)[NV]) {
   const int w = threadIdx.x >> 6, l = lane_id();
   const int32_t W = S.W;
-  uint32_t* qi = S.hval + w * 256;
+  uint32_t* qi = S.queue + w * 256;
   uint32_t* qj = qi + 128;
   int32_t n = 0;  // listed edges
   auto run = [&](int32_t k) {
@@ -639,14 +650,16 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
   const int w = threadIdx.x >> 6;
   const int nwaves = blockDim.x >> 6;
   const int32_t W = S.W;
-  // load factor <= 1/8 where the table has room, else as low as it allows
+  // load factor <= 1/4 where the table has room, else as low as it allows
   int H = 1;
-  while (H < 8 * dp) H <<= 1;
+  while (H < 4 * dp) H <<= 1;
   while (H > S.hcap) H >>= 1;
   const uint32_t hmask = (uint32_t)H - 1u;
   const int shift = 32 - log2i((uint32_t)H);
   for (int32_t k = threadIdx.x; k < dp; k += blockDim.x) { S.ids[k] = R.rcol[ub + k]; S.tuc[k] = 0; }
   for (int32_t k = threadIdx.x; k < H; k += blockDim.x) S.hkey[k] = -1;
+  const int32_t fw = 1 << (27 - S.fsh);
+  for (int32_t k = threadIdx.x; k < fw; k += blockDim.x) S.filt[k] = 0u;
   const int64_t ew = tri_words(dp, W);
   for (int64_t k = threadIdx.x; k < ew; k += blockDim.x) S.E[k] = 0ull;
   for (int32_t k = threadIdx.x; k < NV * W; k += blockDim.x) S.P[k] = 0ull;
@@ -655,6 +668,8 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
   for (int32_t k = threadIdx.x; k < dp; k += blockDim.x) {
     const uint32_t x = S.ids[k];
     const uint32_t id = x & GC_ID;
+    const uint32_t fh = hash32(id) >> S.fsh;
+    atomicOr(&S.filt[fh >> 5], 1u << (fh & 31u));
     uint32_t h = hash32(id) >> shift;
     while (atomicCAS(&S.hkey[h], -1, (int32_t)id) != -1) h = (h + 1) & hmask;
     S.hval[h] = (uint32_t)k | (x & GC_FLAGS);
@@ -717,8 +732,7 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
     if (ne > 0) {
       // The exceptions by slot pair, in the probe hash table (not read again
       // for this vertex): key min << 16 | max, value the exception's index.
-      // Pairs are unique (each found from its lower slot's list only).  The
-      // waves that still list edges use hval alone until the first barrier.
+      // Pairs are unique (each found from its lower slot's list only).
       for (int32_t k = threadIdx.x; k < H; k += blockDim.x) S.hkey[k] = -1;
       __syncthreads();
       for (int32_t e = threadIdx.x; e < ne; e += blockDim.x) {
@@ -784,12 +798,6 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
     for (int x = 0; x < NV; ++x) {
       __syncthreads();
       for (int64_t k = threadIdx.x; k < ew; k += blockDim.x) S.E[k] = 0ull;
-      for (int32_t k = threadIdx.x; k < dp; k += blockDim.x) {  // the slots again (k4_edges lists edges there)
-        const uint32_t y = S.ids[k], id = y & GC_ID;
-        uint32_t h = hash32(id) >> shift;
-        while (S.hkey[h] != (int32_t)id) h = (h + 1) & hmask;
-        S.hval[h] = (uint32_t)k | (y & GC_FLAGS);
-      }
       __syncthreads();
       for (int32_t g0 = w; g0 < dp; g0 += nwaves * 64) tri_large_probe<NV>(A, S, hmask, shift, g0, nwaves, dp, x + 1, ent);
       __syncthreads();
@@ -829,7 +837,7 @@ constexpr int pow2_at_least(int x) {
 // qhead.
 // Registers: the tiers up to 256 hide their latencies with 6 waves per SIMD (5
 // with four versions, which spill below 96 registers); without the bound they
-// took 13.3 -> 17.8 ms and 9.5 -> 12.5 ms a count at scale 22.
+// took 17.8 against 13.3 ms (<256>) and 12.5 against 9.5 ms (<128>) at scale 22.
 template <int CAP, int THREADS, int NV>
 __global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 : 5)) void k_tri_large(CountArgs A, int L, unsigned long long* qhead) {
   const RegionDev& R = A.R;
@@ -861,10 +869,18 @@ __global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 :
     int32_t hc = 1;
     while (2 * hc <= 4 * cap) hc <<= 1;
     S.hcap = hc;
+    __shared__ uint32_t filt[8192];
+    __shared__ uint32_t queue[THREADS / 64 * 256];
+    S.filt = filt;
+    S.fsh = 14;
+    S.queue = queue;
   } else {
     constexpr int CW = CAP / 64;
-    constexpr int HC = CAP <= 1024 ? pow2_at_least(8 * CAP) : pow2_at_least(2 * CAP);
-    static_assert(THREADS / 64 * 256 <= HC, "edge lists of k4_edges");
+    constexpr int HC = CAP <= 1024 ? pow2_at_least(4 * CAP) : pow2_at_least(CAP);
+    // 64 filter bits per slot, 32 in the last tier (LDS)
+    constexpr int FSH = CAP <= 128 ? 19 : CAP <= 256 ? 18 : CAP <= 512 ? 17 : CAP <= 1024 ? 16 : 17;
+    __shared__ uint32_t filt[1 << (27 - FSH)];
+    __shared__ uint32_t queue[THREADS / 64 * 256];
     __shared__ unsigned long long E[32 * CW * CW + 32 * CW];  // tri_words(CAP, CW)
     __shared__ unsigned long long P[NV * CW];
     __shared__ uint32_t ids[CAP];
@@ -876,6 +892,7 @@ __global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 :
     __shared__ uint32_t exc[XC];
     __shared__ int32_t nexc;
     S.E = E; S.P = P; S.ids = ids; S.tuc = tuc; S.hkey = hkey; S.hval = hval; S.exc = exc; S.nexc = &nexc;
+    S.filt = filt; S.fsh = FSH; S.queue = queue;
     S.xcap = XC;
     S.W = CW;
     S.hcap = HC;
@@ -1799,11 +1816,11 @@ void launch_count_t(const CountArgs& A, hipStream_t s, hipEvent_t* ev) {
   hipLaunchKernelGGL(k_tri_small<NV>, dim3(cap_grid((N + 3) / 4, 8192)), dim3(256), 0, s, A);
   // out-degree tiers (64,128] (256] (512] (1024] (TLM] and above, one list each
   unsigned long long* qt = (unsigned long long*)(A.c + C_QTRI) - L_TRI_1;
-  hipLaunchKernelGGL((k_tri_large<128, 128, NV>), dim3(cap_grid(N, 8192)), dim3(128), 0, s, A, (int)L_TRI_1,
+  hipLaunchKernelGGL((k_tri_large<128, 256, NV>), dim3(cap_grid(N, 8192)), dim3(256), 0, s, A, (int)L_TRI_1,
                      qt + L_TRI_1);
-  hipLaunchKernelGGL((k_tri_large<256, 256, NV>), dim3(cap_grid(N, 4096)), dim3(256), 0, s, A, (int)L_TRI_2,
+  hipLaunchKernelGGL((k_tri_large<256, 512, NV>), dim3(cap_grid(N, 4096)), dim3(512), 0, s, A, (int)L_TRI_2,
                      qt + L_TRI_2);
-  hipLaunchKernelGGL((k_tri_large<512, 512, NV>), dim3(cap_grid(N, 2048)), dim3(512), 0, s, A, (int)L_TRI_3,
+  hipLaunchKernelGGL((k_tri_large<512, 1024, NV>), dim3(cap_grid(N, 2048)), dim3(1024), 0, s, A, (int)L_TRI_3,
                      qt + L_TRI_3);
   hipLaunchKernelGGL((k_tri_large<1024, 1024, NV>), dim3(cap_grid(N, 1024)), dim3(1024), 0, s, A, (int)L_TRI_4,
                      qt + L_TRI_4);
