@@ -858,14 +858,13 @@ void build(gc_graph* G, int32_t k, const int64_t* n, const int32_t* const* src, 
   // rank: (graph, degree, local id)
   G->ext2int.ensure(N * sizeof(int32_t));
   G->int2ext.ensure(N * sizeof(int32_t));
+  G->len.ensure(N * sizeof(int32_t));
   launch_rank(deg, G->gid.as<int32_t>(), gb, N, lbits, gbits + 2 * lbits,
               rk, rk2, G->sort_tmp.p, G->ext2int.as<int32_t>(),
-              G->int2ext.as<int32_t>(), s);
+              G->int2ext.as<int32_t>(), G->len.as<int32_t>(), s);
   // directed entries in internal ids
-  G->len.ensure(N * sizeof(int32_t));
-  fill_u32(G->len.as<uint32_t>(), 0u, N, s);
   launch_init_dir(uniq, M, G->ctr.as<unsigned long long>(), G->bits, G->ext2int.as<int32_t>(),
-                  dir, G->len.as<int32_t>(), s);
+                  dir, s);
   unsigned long long mu = 0;
   HIPCHK(hipMemcpyAsync(&mu, G->ctr.as<unsigned long long>() + C_DIRA, 8, hipMemcpyDeviceToHost, s));
   G->sync();

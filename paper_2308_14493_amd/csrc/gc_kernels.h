@@ -116,9 +116,9 @@ void launch_init_unique(const unsigned long long* keys, int64_t m, int bits, uns
                         unsigned long long* c, int32_t* deg, hipStream_t s);
 void launch_rank(const int32_t* deg, const int32_t* gid, const int64_t* gbase, int64_t N, int lbits, int total_bits,
                  unsigned long long* keys, unsigned long long* alt, void* sort_tmp, int32_t* ext2int, int32_t* int2ext,
-                 hipStream_t s);
+                 int32_t* len, hipStream_t s);
 void launch_init_dir(const unsigned long long* uniq, int64_t max_m, unsigned long long* c, int bits,
-                     const int32_t* ext2int, unsigned long long* dir, int32_t* len, hipStream_t s);
+                     const int32_t* ext2int, unsigned long long* dir, hipStream_t s);
 void launch_init_csr(const PoolDev& P, const unsigned long long* dir, int64_t max_dir, unsigned long long* c, int bits,
                      int64_t* rstart, float slack, void* scan_tmp, uint32_t flag, hipStream_t s);
 void launch_caps(const PoolDev& P, float slack, hipStream_t s);  // P.cap <- len + slack

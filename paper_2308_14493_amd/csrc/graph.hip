@@ -853,17 +853,35 @@ __global__ void k_init_keys(const int32_t* __restrict__ src, const int32_t* __re
   }
 }
 
-// unique edges -> degree count (external ids)
+// unique edges -> degree count (external ids).  Waves append to the list, and
+// the edges of one smaller end, consecutive in the sorted keys, add to its
+// degree together: with an atomic each a build of scale 16 (10^6 edges) took
+// 0.26 ms here, now 0.22 (the larger ends are hubs).
 __global__ void k_init_unique(const unsigned long long* __restrict__ keys, int64_t m, int bits,
                               unsigned long long* __restrict__ uniq, unsigned long long* __restrict__ cc,
                               int32_t* __restrict__ deg) {
   const uint64_t idmask = (1ull << bits) - 1ull;
-  for (int64_t i = gtid(); i < m; i += gstride()) {
-    const unsigned long long k = keys[i];
-    if (k == ~0ull || (i > 0 && keys[i - 1] == k)) continue;
-    unsigned long long p = atomicAdd(&cc[C_DIRA], 1ull);
+  const int l = lane_id();
+  for (int64_t b0 = gtid() - l; b0 < m; b0 += gstride()) {  // the same for a whole wave
+    const int64_t i = b0 + l;
+    const unsigned long long k = i < m ? keys[i] : ~0ull;
+    const bool take = k != ~0ull && !(i > 0 && keys[i - 1] == k);
+    const uint64_t tm = __ballot(take);
+    if (!tm) continue;
+    unsigned long long p = 0;
+    if (l == 0) p = atomicAdd(&cc[C_DIRA], (unsigned long long)__popcll(tm));
+    p = (unsigned long long)__shfl((long long)p, 0) + (unsigned long long)__popcll(tm & lanemask_lt());
+    // runs of one smaller end (keys that are no edges come last in the order)
+    const long long a = (long long)(k >> bits), before = __shfl_up(a, 1);
+    const uint64_t heads = __ballot(l == 0 || before != a);
+    if ((heads >> l) & 1ull) {
+      const uint64_t later = heads & ~(lanemask_lt() | (1ull << l));
+      const uint64_t run = (later ? (later & -later) - 1ull : ~0ull) & ~lanemask_lt();
+      const int n = __popcll(tm & run);
+      if (n) atomicAdd(&deg[a], n);
+    }
+    if (!take) continue;
     uniq[p] = k;
-    atomicAdd(&deg[k >> bits], 1);
     atomicAdd(&deg[k & idmask], 1);
   }
 }
@@ -880,19 +898,21 @@ __global__ void k_rank_keys(const int32_t* __restrict__ deg, const int32_t* __re
 }
 
 __global__ void k_rank_assign(const unsigned long long* __restrict__ sorted, const int64_t* __restrict__ gbase,
-                              int64_t N, int lbits, int32_t* __restrict__ ext2int) {
+                              int64_t N, int lbits, int32_t* __restrict__ ext2int, int32_t* __restrict__ len) {
   const uint64_t lmask = (1ull << lbits) - 1ull;
   for (int64_t p = gtid(); p < N; p += gstride()) {
     const unsigned long long k = sorted[p];
     const int g = (int)(k >> (2 * lbits));
     const int64_t ext = gbase[g] + (int64_t)(k & lmask);
     ext2int[ext] = (int32_t)p;
+    len[p] = (int32_t)((k >> lbits) & lmask);
   }
 }
 
+// (The row lengths come with the ranks: counted here, with two atomics per
+// edge, this took 0.83 ms of a build of scale 16, now less than 0.02.)
 __global__ void k_init_dir(const unsigned long long* __restrict__ uniq, const unsigned long long* cc, int bits,
-                           const int32_t* __restrict__ ext2int, unsigned long long* __restrict__ dir,
-                           int32_t* __restrict__ len) {
+                           const int32_t* __restrict__ ext2int, unsigned long long* __restrict__ dir) {
   const int64_t m = ctr(cc, C_DIRA);
   const uint64_t idmask = (1ull << bits) - 1ull;
   for (int64_t i = gtid(); i < m; i += gstride()) {
@@ -900,8 +920,6 @@ __global__ void k_init_dir(const unsigned long long* __restrict__ uniq, const un
     const uint64_t b = (uint64_t)(uint32_t)ext2int[uniq[i] & idmask];
     dir[2 * i] = (a << bits) | b;
     dir[2 * i + 1] = (b << bits) | a;
-    atomicAdd(&len[a], 1);
-    atomicAdd(&len[b], 1);
   }
 }
 
@@ -1160,16 +1178,16 @@ void launch_init_unique(const unsigned long long* keys, int64_t m, int bits, uns
 }
 void launch_rank(const int32_t* deg, const int32_t* gid, const int64_t* gbase, int64_t N, int lbits, int total_bits,
                  unsigned long long* keys, unsigned long long* alt, void* sort_tmp, int32_t* ext2int, int32_t* int2ext,
-                 hipStream_t s) {
+                 int32_t* len, hipStream_t s) {
   hipLaunchKernelGGL(k_rank_keys, dim3(grid_for(N)), dim3(TPB), 0, s, deg, gid, gbase, N, lbits, keys);
   unsigned long long* sorted = radix_sort_u64(keys, alt, sort_tmp, N, nullptr, total_bits, s);
-  hipLaunchKernelGGL(k_rank_assign, dim3(grid_for(N)), dim3(TPB), 0, s, sorted, gbase, N, lbits, ext2int);
+  hipLaunchKernelGGL(k_rank_assign, dim3(grid_for(N)), dim3(TPB), 0, s, sorted, gbase, N, lbits, ext2int, len);
   hipLaunchKernelGGL(k_invert_perm, dim3(grid_for(N)), dim3(TPB), 0, s, ext2int, N, int2ext);
 }
 void launch_init_dir(const unsigned long long* uniq, int64_t max_m, unsigned long long* c, int bits,
-                     const int32_t* ext2int, unsigned long long* dir, int32_t* len, hipStream_t s) {
+                     const int32_t* ext2int, unsigned long long* dir, hipStream_t s) {
   if (max_m == 0) return;
-  hipLaunchKernelGGL(k_init_dir, dim3(grid_for(max_m)), dim3(TPB), 0, s, uniq, c, bits, ext2int, dir, len);
+  hipLaunchKernelGGL(k_init_dir, dim3(grid_for(max_m)), dim3(TPB), 0, s, uniq, c, bits, ext2int, dir);
 }
 void launch_init_csr(const PoolDev& P, const unsigned long long* dir, int64_t max_dir, unsigned long long* c, int bits,
                      int64_t* rstart, float slack, void* scan_tmp, uint32_t flag, hipStream_t s) {
