@@ -224,7 +224,7 @@ struct gc_graph {
   DevBuf c4_dense, c4_touch, c4_cur, c4_blk, c4_keys, c4_keys_alt, tri_scratch;
   // triangles at each vertex (kept for the edge-local passes) and the
   // scratch of those passes
-  DevBuf Tv, dTs, ce, hk, hd, hl, e_ns, e_dt, e_kw, slist, dctr, c4_nch, c4_side, c4_low, c4_off, pair_edge, pair_idx,
+  DevBuf Tv, dTs, ce, hk, hd, hl, e_ns, e_dt, e_out, e_kw, slist, lay_list, lay_off, dctr, c4_nch, c4_side, c4_low, c4_off, pair_edge, pair_idx,
       pair_len, pair_off, pair_hlen, pair_hoff, tv_items, tv_ioff;
   int64_t ae_cap = 0, pair_cap = 0;
   uint32_t hmask = 0;                // slots of hk, hd less one
@@ -278,6 +278,9 @@ struct gc_graph {
   // ids covered by the bitmaps of the edge-local 4-cycles, 0: the most
   // (GC_DELTA_BITS lowers it: tests reach the ids below the window)
   int32_t delta_bits = 0;
+  // members an edge's bitmap may leave out before it is walked in layers, 0:
+  // the rule of the kernels (GC_DELTA_OUT: tests reach the layers)
+  int32_t delta_out = 0;
   double region_frac[8] = {-1, -1, -1, -1, -1, -1, -1, -1};
   // counting attempts after the first when scratch proves too small
   // (GC_RETRY_LIMIT overrides it: tests set 0 to reach the failure path)
@@ -737,6 +740,7 @@ void* noalloc_scratch_ptr(int device) {
 void setup_handle(gc_graph* G, const gc_options* opt) {
   if (opt) G->opt = *opt; else gc_options_default(&G->opt);
   if (const char* e = std::getenv("GC_DELTA_BITS")) G->delta_bits = std::max(0, std::atoi(e));
+  if (const char* e = std::getenv("GC_DELTA_OUT")) G->delta_out = std::max(0, std::atoi(e));
   if (const char* e = std::getenv("GC_RETRY_LIMIT")) G->retry_limit = std::max(0, std::min(8, std::atoi(e)));
   if (G->opt.radius < 0 || G->opt.radius > 4) raise(GC_EINVAL, "radius must be in [0, 4]");
   if (!(G->opt.slack >= 0.0f && G->opt.slack <= 16.0f)) raise(GC_EINVAL, "slack must be in [0, 16]");
@@ -1024,6 +1028,7 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
   D.ce_cap = (int64_t)(G->ce.cap / 8);
   D.e_ns = G->e_ns.as<int32_t>();
   D.e_dt = G->e_dt.as<int32_t>();
+  D.e_out = G->e_out.as<int32_t>();
   D.e_kw = G->e_kw.as<int64_t>();
   D.hk = G->hk.as<unsigned long long>();
   D.hd = G->hd.as<int32_t>();
@@ -1035,6 +1040,10 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
   D.c4_side = G->c4_side.as<int32_t>();
   D.c4_low = G->c4_low.as<int32_t>();
   D.c4_ids = (uint32_t)G->delta_bits;
+  D.c4_out = G->delta_out;
+  D.lay_ids = 0;
+  D.lay_list = G->lay_list.as<int32_t>();
+  D.lay_off = G->lay_off.as<int64_t>();
   D.c4_off = G->c4_off.as<int64_t>();
   D.pair_edge = G->pair_edge.as<int32_t>();
   D.pair_idx = G->pair_idx.as<int32_t>();
@@ -1057,7 +1066,7 @@ void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t pair_need) 
   const int64_t ce_cap = std::max<int64_t>(cap_t, 64);
   G->ce.ensure(ce_cap * 8);
   const int64_t ce = (int64_t)(G->ce.cap / 8);
-  for (DevBuf* b : {&G->c4_nch, &G->c4_side, &G->c4_low, &G->e_ns, &G->e_dt}) b->ensure(ce * 4);
+  for (DevBuf* b : {&G->c4_nch, &G->c4_side, &G->c4_low, &G->e_ns, &G->e_dt, &G->e_out}) b->ensure(ce * 4);
   G->e_kw.ensure(ce * 8);
   G->c4_off.ensure((ce + 1) * 8);
   G->pair_cap = std::max<int64_t>(G->pair_cap, std::max<int64_t>(pair_need, 64 * cap_t + 4096));
@@ -1067,6 +1076,8 @@ void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t pair_need) 
   // touched rows: at most both ends of every change
   G->tv_items.ensure(2 * ce * 4);
   G->tv_ioff.ensure((2 * ce + 1) * 8);
+  G->lay_list.ensure(2 * ce * 4);
+  G->lay_off.ensure(2 * ce * 8);
   G->scan_tmp.ensure(scan_tmp_bytes(std::max<int64_t>(2 * ce, 2 * G->pair_cap) + 1) + 64);
   // affected edges: the list, and a table at most two thirds full (free
   // between passes)
@@ -1260,7 +1271,7 @@ std::vector<uint64_t> pass_signature(gc_graph* G, const PassPlan& L, const Count
                           &G->sort_tmp, &G->scan_tmp, &G->roff, &G->rcol, &G->rrow, &G->rlow, &G->dver, &G->t,
                           &G->tp, &G->vpos, &G->level, &G->rlist, &G->rlen, &G->lists, &G->c4_dense, &G->c4_touch,
                           &G->c4_cur, &G->c4_blk, &G->c4_keys, &G->c4_keys_alt, &G->tri_scratch, &G->Tv, &G->dTs,
-                          &G->ce, &G->hk, &G->hd, &G->hl, &G->e_ns, &G->e_dt, &G->e_kw, &G->slist, &G->dctr,
+                          &G->ce, &G->hk, &G->hd, &G->hl, &G->e_ns, &G->e_dt, &G->e_out, &G->e_kw, &G->slist, &G->lay_list, &G->lay_off, &G->dctr,
                           &G->c4_nch, &G->c4_side, &G->c4_low, &G->c4_off, &G->pair_edge, &G->pair_idx, &G->pair_len,
                           &G->pair_off, &G->pair_hlen, &G->pair_hoff, &G->tt, &G->scratch_t, &G->dead_d, &G->tv_items,
                           &G->tv_ioff};

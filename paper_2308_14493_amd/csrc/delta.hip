@@ -36,6 +36,8 @@
 //               searched in the other.
 #include "gc_kernels.h"
 
+#include <algorithm>
+
 namespace {
 
 constexpr int TPB = 256;
@@ -134,6 +136,7 @@ __global__ void k_delta_edges(DeltaArgs D) {
     if ((int64_t)p < D.ce_cap) {
       D.ce[p] = key | ((unsigned long long)(i < na ? 1u : 2u) << DIR_MASK_SHIFT);
       D.e_ns[p] = 0;
+      D.e_out[p] = 0;
       D.e_dt[p] = 0;
       D.e_kw[p] = 0;
     }
@@ -271,21 +274,46 @@ constexpr int64_t C4B_RATIO = 64;
 constexpr int64_t C4B_MIN = 4096;
 constexpr int C4B_T = 1024;
 constexpr int C4B_SMALL = 16384, C4B_LARGE = 36864;  // 32-bit words of the two bitmaps: 64 and 144 KB
+// Members that a bitmap leaves out (below its window, or with an edge to the
+// changed pair that is in the batch too) are searched one by one.  At a hub
+// they are as many as the batch's updates there, or as its neighbours among
+// the low ids, for every changed edge of the hub: 1,000 deletions at a star of
+// 2,000,000 leaves listed 8e8 searched pairs (33 GB of lists, 179 ms; 3.3 now).
+// So an edge that leaves out more than C4B_OUT is walked in layers
+// (k_delta_layers) where its searches, at C4B_SEARCH walked entries each, cost
+// more than the walk and its share of C4B_FREE, or would list more than
+// C4B_OUT_MAX pairs or its share of C4B_OUT_ALL.  A few edges in layers are a
+// tail of long chunks: with every edge above C4B_OUT, 2,500 updates at scale
+// 22 took 13.8 ms a call instead of 8.6, with no C4B_FREE and half of
+// C4B_OUT_ALL 9.1.  No batch of 128 updates on ids that fit a bitmap leaves
+// out more than C4B_OUT: small passes do not launch the kernel of the layers.
+constexpr int32_t C4B_OUT = 128;
+constexpr int64_t C4B_SEARCH = 16, C4B_FREE = 1ll << 32, C4B_OUT_MAX = 16384, C4B_OUT_ALL = 1 << 25;
+
+// entries: those the searches would walk; cost: those the walk does; ne: changed edges
+__device__ __forceinline__ bool in_layers(const DeltaArgs& D, int64_t out, int64_t entries, int64_t cost, int64_t ne) {
+  if (D.c4_out > 0) return out > D.c4_out;
+  return out > C4B_OUT && (entries * C4B_SEARCH > cost + C4B_FREE / ne ||
+                           out > max((int64_t)C4B_OUT, min(C4B_OUT_MAX, C4B_OUT_ALL / ne)));
+}
 
 __device__ __forceinline__ int64_t pair_cost(int32_t al, int32_t ol) {
   return min((int64_t)al, C4B_RATIO * (int64_t)ol);
 }
 // The bitmap of N(o) covers D.c4_ids ids downwards from N(o)'s last one: ids
 // are a degree order, so the ids below that window have few entries.
+__device__ __forceinline__ uint32_t c4b_top(const DeltaArgs& D, uint32_t o) {
+  return (D.P.col[D.P.off[o] + D.P.len[o] - 1] & GC_ID) + 1u;
+}
 __device__ __forceinline__ uint32_t c4b_base(const DeltaArgs& D, uint32_t o) {
-  const uint32_t top = (D.P.col[D.P.off[o] + D.P.len[o] - 1] & GC_ID) + 1u;
+  const uint32_t top = c4b_top(D, o);
   return top > D.c4_ids ? top - D.c4_ids : 0u;
 }
 // pairs of an edge with a bitmap that are walked against it
 __device__ __forceinline__ bool pair_walked(int32_t al, int32_t ol) { return (int64_t)al <= C4B_RATIO * (int64_t)ol; }
 
 // per changed edge: the end to walk from, whether it earns a bitmap, and its
-// number of pairs.  An end u costs sum_{a in N(u)} pair_cost(d_a, d_v); both rows of every
+// number of pairs.  An end u costs sum_{a in N(u) - {v}} pair_cost(d_a, d_v); both rows of every
 // changed edge are cut in pieces of at most TV_CHUNK entries (the touched
 // rows' arrays hold the numbering; they are free again after the degree
 // passes), each wave sums one piece at a time into the edge's two totals
@@ -327,12 +355,15 @@ __global__ void k_delta_c4_plan(DeltaArgs D) {
     const int64_t nu = max(1, (du + TV_CHUNK - 1) / TV_CHUNK);
     const int64_t pk = k - D.tv_ioff[i];
     const bool side_v = pk >= nu;  // pieces of u first, then of v
-    const uint32_t x = side_v ? v : u;
+    const uint32_t x = side_v ? v : u, z = side_v ? u : v;
     const int32_t dx = side_v ? dv : du, other = side_v ? du : dv;
     const int32_t k0 = (int32_t)((side_v ? pk - nu : pk) * TV_CHUNK), k1 = min(dx, k0 + TV_CHUNK);
     const uint32_t* rx = D.P.col + D.P.off[x];
     int64_t c = 0;
-    for (int32_t q = k0 + l; q < k1; q += 64) c += pair_cost(D.P.len[rx[q] & GC_ID], other);
+    for (int32_t q = k0 + l; q < k1; q += 64) {
+      const uint32_t a = rx[q] & GC_ID;
+      if (a != z) c += pair_cost(D.P.len[a], other);
+    }
     c = wave_sum64(c);
     if (l == 0 && c) atomicAdd((unsigned long long*)&D.pair_off[2 * i + (side_v ? 1 : 0)], (unsigned long long)c);
   }
@@ -354,11 +385,18 @@ __global__ void k_delta_plan_fin(DeltaArgs D) {
     const bool bitmap = cost >= C4B_MIN;
     const uint32_t s = from_u ? u : v, o = from_u ? v : u;
     int32_t low = 0;  // N(o) below the window
+    bool layers = false;
     if (bitmap) {
       const uint32_t base = c4b_base(D, o);
-      if (base) low = lower_bound_id(D.P.col + D.P.off[o], D.P.len[o], base);
+      const int64_t sl = D.P.len[s], flagged = (int64_t)D.na[o] + D.nr[o];
+      int64_t entries = flagged * sl;  // walked and searched: the shorter row of each pair
+      if (base) {
+        low = lower_bound_id(D.P.col + D.P.off[o], D.P.len[o], base);
+        entries += low * min(sl, (int64_t)D.P.len[base - 1]);  // ids are a degree order
+      }
+      layers = in_layers(D, low + flagged, entries, cost, ne);
     }
-    D.c4_side[i] = (from_u ? 0 : 1) | (bitmap ? 2 : 0);
+    D.c4_side[i] = (from_u ? 0 : 1) | (bitmap ? 2 : 0) | (layers ? 4 : 0);
     D.c4_low[i] = low;
     D.c4_nch[i] = D.P.len[s];
   }
@@ -482,6 +520,7 @@ __global__ void k_delta_pairs(DeltaArgs D) {
     if (!hm) continue;
     if (l == 0) atomicAdd(&D.dc[DC_AFF_INST], 2ull * (unsigned long long)__popcll(hm));
     const uint32_t fs = nib(es), fo = nib(eo);
+    const bool outside = hit && ((fs | fo) != 0 || (D.N > (int64_t)D.c4_ids && a < c4b_base(D, o)));
     for (uint64_t m = hm; m;) {  // S(e): one reservation per edge met by the wave
       const int src = __builtin_ctzll(m);
       const int32_t ii = __builtin_amdgcn_readlane((int32_t)i, src);
@@ -490,6 +529,8 @@ __global__ void k_delta_pairs(DeltaArgs D) {
       int32_t at = 0;
       if (l == src) at = atomicAdd(&D.e_ns[ii], (int32_t)__popcll(same));
       at = __shfl(at, src);
+      const uint64_t om = __ballot(mine && outside);
+      if (om && l == src) atomicAdd(&D.e_out[ii], (int32_t)__popcll(om));
       if (mine) D.slist[D.c4_off[i] + at + __popcll(same & lanemask_lt())] = a | (fs << 28) | (fo << 30);
       m &= ~same;
     }
@@ -509,15 +550,16 @@ __global__ void k_delta_pairs(DeltaArgs D) {
     aff_append(D, n1, a, h1);
     aff_append(D, n2, a, h2);
   }
-  // the pairs (e, b)
-  for (int64_t i = w0; i < ne; i += ws) {
-    if (!(D.c4_side[i] & 2)) continue;
+  // the pairs (e, b), several waves per edge while there are fewer edges than waves
+  const int32_t parts = (int32_t)max(ws / ne, (int64_t)1);
+  for (int64_t i = w0 % ne, part = w0 / ne; i < ne && part < parts; i += ws) {
+    if ((D.c4_side[i] & 6) != 2) continue;  // no bitmap, or walked in layers
     const unsigned long long K = D.ce[i] & DIR_KEY_MASK;
     const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
     const uint32_t s = (D.c4_side[i] & 1) ? v : u, o = s == u ? v : u;
     const int32_t sl = D.P.len[s];
     const int32_t low = D.c4_low[i], out = low + D.na[o] + D.nr[o];
-    for (int32_t k0 = 0; k0 < out; k0 += 64) {
+    for (int32_t k0 = (int32_t)part * 64; k0 < out; k0 += parts * 64) {
       const int32_t k = k0 + l;
       uint32_t b = s, fob = 0;
       if (k < out) c4_out_pair(D, o, low, k, b, fob);
@@ -534,6 +576,10 @@ __global__ void k_delta_pairs(DeltaArgs D) {
 __device__ __forceinline__ bool k4_walked(int32_t ns, int64_t kw) {
   return kw >= C4B_MIN && kw <= 3 * C4B_RATIO / 8 * (int64_t)ns * ns;
 }
+__device__ __forceinline__ bool k4_layers(const DeltaArgs& D, int64_t i) {
+  const int64_t out = D.e_out[i];
+  return in_layers(D, out, out * D.e_ns[i], D.e_kw[i], ctr(D.dc, DC_EDGES));
+}
 // members of S(e) (id | flags of both edges << 28) that its bitmap leaves out
 __device__ __forceinline__ bool k4_outside(uint32_t w, uint32_t base) { return (w & GC_FLAGS) || (w & GC_ID) < base; }
 
@@ -541,8 +587,8 @@ __device__ __forceinline__ bool k4_outside(uint32_t w, uint32_t base) { return (
 // the work lists of the 4-cliques, a lane per member w of a list S(e) (the
 // lists sit in the pair space).  An edge that walks: each member inside the
 // bitmap walks its row above itself; a member outside is searched against
-// the whole list.  An edge that searches: each member against those listed
-// after it.
+// the whole list (in layers: every member walks).  An edge that searches:
+// each member against those listed after it.
 __global__ void k_delta_k4_pairs(DeltaArgs D) {
   const int64_t ne = min(ctr(D.dc, DC_EDGES), D.ce_cap);
   const int64_t npairs = D.c4_off[D.ce_cap];
@@ -589,7 +635,7 @@ __global__ void k_delta_k4_pairs(DeltaArgs D) {
         const unsigned long long K = D.ce[i] & DIR_KEY_MASK;
         const uint32_t o = (uint32_t)((D.c4_side[i] & 1) ? K >> D.bits : K & idmask);
         const uint32_t e = D.slist[p], w = e & GC_ID;
-        if (k4_outside(e, c4b_base(D, o))) {
+        if (!k4_layers(D, i) && k4_outside(e, c4b_base(D, o))) {
           search = ns;
         } else {
           const int32_t wl = D.P.len[w];
@@ -767,13 +813,22 @@ __global__ __launch_bounds__(TPB) void k_delta_search(DeltaArgs D) {
 // Walked entries per chunk of a bitmap edge: enough chunks to fill the chip
 // several times over, each long enough to pay for its bitmap (four times
 // |N(o)|, and a floor for the fixed cost of a chunk).
-__device__ __forceinline__ int64_t c4b_chunk(int64_t total, int32_t ol) {
+__device__ __forceinline__ int64_t c4b_chunk(int64_t total, int64_t ol) {
   const int64_t even = total / 4096;
-  return max(min(max(even, (int64_t)16384), (int64_t)131072), 4 * (int64_t)ol);
+  return max(min(max(even, (int64_t)16384), (int64_t)131072), 4 * ol);
+}
+
+// Walked entries per chunk of an edge in layers with nm members: the members
+// of S(e), in no order, are read once per window.
+__device__ __forceinline__ int64_t layers_chunk(const DeltaArgs& D, int64_t total, bool k4, int32_t nm, uint32_t top) {
+  const int64_t nw = k4 ? ((int64_t)top + D.lay_ids - 1) / D.lay_ids : 1;
+  return c4b_chunk(total, nw * nm);
 }
 
 // Chunks of the walked entries per changed edge: of its 4-cycles at i, of its
-// 4-cliques at ne + i (0 past them, for the scan).
+// 4-cliques at ne + i (0 past them, for the scan).  Those in layers go to a
+// list of their own, whose entries are taken together with the number of
+// their first chunk: one word counts entries (above DC_LAY_SHIFT) and chunks.
 __global__ void k_delta_hitems(DeltaArgs D) {
   const int64_t ne = min(ctr(D.dc, DC_EDGES), D.ce_cap);
   const int64_t npairs = D.c4_off[D.ce_cap];
@@ -789,8 +844,17 @@ __global__ void k_delta_hitems(DeltaArgs D) {
       if (h > 0) {
         const unsigned long long K = D.ce[i] & DIR_KEY_MASK;
         const uint32_t o = (uint32_t)((D.c4_side[i] & 1) ? K >> D.bits : K & idmask);
-        const int64_t T = c4b_chunk(total, k4 ? D.e_ns[i] : D.P.len[o]);
-        n = (int32_t)((h + T - 1) / T);
+        const int32_t nm = k4 ? D.e_ns[i] : D.P.len[o];
+        if (k4 ? k4_layers(D, i) : (D.c4_side[i] & 4) != 0) {
+          const int64_t T = layers_chunk(D, total, k4, nm, c4b_top(D, o));
+          const unsigned long long at =
+              atomicAdd(&D.dc[DC_LAY], (1ull << DC_LAY_SHIFT) | (unsigned long long)((h + T - 1) / T));
+          D.lay_list[at >> DC_LAY_SHIFT] = (int32_t)t;
+          D.lay_off[at >> DC_LAY_SHIFT] = (int64_t)(at & ((1ull << DC_LAY_SHIFT) - 1ull));
+        } else {
+          const int64_t T = c4b_chunk(total, nm);
+          n = (int32_t)((h + T - 1) / T);
+        }
       }
     }
     D.tv_items[t] = n;
@@ -921,6 +985,151 @@ __global__ __launch_bounds__(C4B_T, WORDS <= 16384 ? 8 : 4) void k_delta_bits(De
       }
     }
     acc[k4 ? 1 : 0] += (int64_t)clean * delta_of(fe) + rest;
+  }
+  if (cur_g >= 0) { add_sig(D, cur_g, SG_C4, acc[0]); add_sig(D, cur_g, SG_K4, acc[1]); }
+}
+
+// The walked entries of the edges in layers: as above, but N(o) or S(e) is
+// taken in windows of ids from its largest member downwards (those without a
+// member skipped), and every member gets a bit, with a second bit where one
+// of its edges to the changed pair is in the batch, so that nothing is left
+// to searches.  A piece of a row is cut to the window by two searches; an entry is read in one
+// window only.  Members in the batch are looked up again when they are hit.
+// Bound like k_delta_bits; per window a chunk also pays for clearing the
+// window's words and for three barriers.
+__global__ __launch_bounds__(C4B_T, 4) void k_delta_layers(DeltaArgs D) {
+  __shared__ uint32_t bm[C4B_LARGE / 2];  // members
+  __shared__ uint32_t bf[C4B_LARGE / 2];  // those with an edge in the batch
+  __shared__ int64_t item_s, entry_s;
+  __shared__ int32_t next_s;
+  if (D.bstats[BS_RETRY]) return;
+  const unsigned long long lay = D.dc[DC_LAY];
+  const int64_t nent = (int64_t)(lay >> DC_LAY_SHIFT), nitems = (int64_t)(lay & ((1ull << DC_LAY_SHIFT) - 1ull));
+  if (nent == 0) return;
+  const int64_t ne = min(ctr(D.dc, DC_EDGES), D.ce_cap);
+  const int64_t npairs = D.c4_off[D.ce_cap];
+  const int64_t total = D.pair_hoff[2 * npairs];
+  const unsigned long long idmask = (1ull << D.bits) - 1ull;
+  const int32_t l = lane_id(), wv = (int32_t)(threadIdx.x >> 6);
+  constexpr int32_t NW = C4B_T / 64;
+  const uint32_t* __restrict__ col = D.P.col;
+  int64_t acc[2] = {0, 0};
+  int cur_g = -1;
+  while (true) {
+    __syncthreads();
+    if (wv == 0) {
+      int64_t it0 = 0;
+      if (l == 0) it0 = (int64_t)atomicAdd(&D.dc[DC_QL], 1ull);
+      it0 = __shfl(it0, 0);
+      const int64_t q0 = it0 < nitems ? wave_upper_bound(D.lay_off, nent, it0) : 0;
+      if (l == 0) { item_s = it0; entry_s = q0; }
+    }
+    __syncthreads();
+    const int64_t it = item_s, q = entry_s;
+    if (it >= nitems) break;
+    const int64_t t = D.lay_list[q];
+    const bool k4 = t >= ne;
+    const int64_t i = k4 ? t - ne : t;
+    const unsigned long long ek = D.ce[i];
+    const unsigned long long K = ek & DIR_KEY_MASK;
+    const uint32_t fe = (uint32_t)(ek >> DIR_MASK_SHIFT) & 3u;
+    const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
+    const uint32_t s = (D.c4_side[i] & 1) ? v : u, o = s == u ? v : u;
+    const int g = D.gid[u];
+    if (g != cur_g) {
+      if (cur_g >= 0) { add_sig(D, cur_g, SG_C4, acc[0]); add_sig(D, cur_g, SG_K4, acc[1]); }
+      acc[0] = acc[1] = 0;
+      cur_g = g;
+    }
+    const int64_t p0 = D.c4_off[i], so = D.P.off[s], oo = D.P.off[o];
+    const int32_t sl = D.P.len[s], ol = D.P.len[o];
+    const uint32_t* mem = k4 ? D.slist + p0 : col + oo;
+    const int32_t nm = k4 ? D.e_ns[i] : ol;  // > 0
+    const uint32_t top0 = c4b_top(D, o);
+    const int64_t* __restrict__ hoff = D.pair_hoff + (k4 ? npairs : 0) + p0;
+    const int64_t nr = D.c4_off[i + 1] - p0;
+    const int64_t T = layers_chunk(D, total, k4, nm, top0);
+    const int64_t r0 = hoff[0] + (it - D.lay_off[q]) * T, r1 = min(hoff[nr], r0 + T);
+    const int64_t per = (r1 - r0 + NW - 1) / NW;
+    const int64_t w0 = min(r1, r0 + wv * per), w1 = min(r1, w0 + per);
+    int64_t clean = 0, rest = 0;
+    int32_t mhi = nm;  // members not taken yet (N(o): sorted)
+    for (uint32_t top = top0;;) {
+      const uint32_t base = top > D.lay_ids ? top - D.lay_ids : 0u, wsz = top - base;
+      const int32_t words = (int32_t)((wsz + 31u) >> 5);  // <= C4B_LARGE / 2
+      __syncthreads();  // the window before is done with
+      for (int32_t k = (int32_t)threadIdx.x; k < words; k += C4B_T) { bm[k] = 0u; bf[k] = 0u; }
+      if (threadIdx.x == 0) next_s = -1;
+      __syncthreads();
+      auto put = [&](uint32_t y) {
+        const uint32_t x = (y & GC_ID) - base;
+        if (x >= wsz || (y & GC_ID) == s) return;
+        atomicOr(&bm[x >> 5], 1u << (x & 31u));
+        if (y & GC_FLAGS) atomicOr(&bf[x >> 5], 1u << (x & 31u));
+      };
+      int32_t next = -1;  // largest member below the window
+      if (k4) {
+        for (int32_t k = (int32_t)threadIdx.x; k < nm; k += C4B_T) {
+          const uint32_t y = mem[k];
+          put(y);
+          if ((y & GC_ID) < base) next = max(next, (int32_t)(y & GC_ID));
+        }
+        next = wave_max32(next);
+        if (l == 0 && next >= 0) atomicMax(&next_s, next);
+      } else {
+        const int32_t mlo = base ? lower_bound_id(mem, mhi, base) : 0;
+        for (int32_t k = mlo + (int32_t)threadIdx.x; k < mhi; k += C4B_T) put(mem[k]);
+        if (mlo) next = (int32_t)(mem[mlo - 1] & GC_ID);
+        mhi = mlo;
+      }
+      __syncthreads();
+      if (k4) next = next_s;
+      if (w0 < w1) {
+        for (int64_t p = wave_upper_bound(hoff, nr, w0); p < nr; p += 64) {
+          if (hoff[p] >= w1) break;
+          const int64_t pl = p + l;
+          int64_t sb = 0;
+          int32_t sn = 0;
+          uint32_t ea = 0;
+          if (pl < nr) {
+            const int64_t hb = hoff[pl], he = hoff[pl + 1];
+            const int64_t c0 = max(hb, w0), c1 = min(he, w1);
+            if (c0 < c1) {
+              ea = k4 ? mem[pl] : col[so + pl];
+              const uint32_t a = ea & GC_ID;
+              sb = D.P.off[a] + (k4 ? D.P.len[a] - (he - hb) : 0) + (c0 - hb);
+              sn = (int32_t)(c1 - c0);
+              if (top < top0) sn = lower_bound_id(col + sb, sn, top);
+              if (base) {
+                const int32_t b0 = lower_bound_id(col + sb, sn, base);
+                sb += b0;
+                sn -= b0;
+              }
+            }
+          }
+          wave_rows(col, sb, sn, ea, [&](uint32_t ea_, uint32_t y) {
+            const uint32_t b = y & GC_ID, x = b - base;
+            if (x >= wsz || !((bm[x >> 5] >> (x & 31u)) & 1u)) return;
+            const bool fb = (bf[x >> 5] >> (x & 31u)) & 1u;
+            if (!fb && !((ea_ | y) & GC_FLAGS)) { ++clean; return; }
+            const uint32_t a = ea_ & GC_ID, fsa = (ea_ >> 28) & 3u, foa = ea_ >> 30, fab = nib(y);
+            uint32_t fsb = 0, fob = 0;
+            if (fb) {
+              fob = nib(col[oo + lower_bound_id(col + oo, ol, b)]);
+              if (k4) fsb = nib(col[so + lower_bound_id(col + so, sl, b)]);
+            }
+            if ((fsa && pkey(s, a, D.bits) < K) || (foa && pkey(o, a, D.bits) < K) ||
+                (fsb && pkey(s, b, D.bits) < K) || (fob && pkey(o, b, D.bits) < K) ||
+                (fab && pkey(a, b, D.bits) < K))
+              return;
+            rest += delta_of(fe | fsa | foa | fsb | fob | fab);
+          });
+        }
+      }
+      if (next < 0) break;
+      top = (uint32_t)next + 1u;
+    }
+    acc[k4 ? 1 : 0] += clean * delta_of(fe) + rest;
   }
   if (cur_g >= 0) { add_sig(D, cur_g, SG_C4, acc[0]); add_sig(D, cur_g, SG_K4, acc[1]); }
 }
@@ -1066,6 +1275,8 @@ void launch_delta(const DeltaArgs& D_, hipStream_t s) {
   const bool small_bits = D.N <= C4B_SMALL * 32;
   const uint32_t ids = (small_bits ? C4B_SMALL : C4B_LARGE) * 32;
   if (D.c4_ids == 0 || D.c4_ids > ids) D.c4_ids = ids;
+  // two bits per id: half as many ids per window
+  D.lay_ids = std::min<uint32_t>(D.c4_ids, C4B_LARGE * 16);
   fill_u64(D.dc, 0ull, DC_COUNT, s);
   hipLaunchKernelGGL(k_delta_edges, dim3(1024), dim3(TPB), 0, s, D);
   hipLaunchKernelGGL(k_delta_titems, dim3(1024), dim3(TPB), 0, s, D);
@@ -1094,6 +1305,10 @@ void launch_delta(const DeltaArgs& D_, hipStream_t s) {
     hipLaunchKernelGGL(k_delta_bits<C4B_SMALL>, dim3(512), dim3(C4B_T), 0, s, D);
   else
     hipLaunchKernelGGL(k_delta_bits<C4B_LARGE>, dim3(256), dim3(C4B_T), 0, s, D);
+  // an edge's members outside its bitmap: flagged ones, at most one per
+  // changed pair (and two ends for S(e)), and ids below the window
+  if (D.ce_cap > C4B_OUT || D.N > (int64_t)D.c4_ids || D.c4_out > 0)
+    hipLaunchKernelGGL(k_delta_layers, dim3(256), dim3(C4B_T), 0, s, D);
 }
 
 void launch_tv_region(int nv, const PoolDev& P, const RegionDev& R, const int32_t* level, int32_t radius,

@@ -189,8 +189,11 @@ enum {
   DC_SEARCH,     // searched pairs
   DC_WALK,       // walk lengths (twice the pairs)
   DC_QH,         // queue of the walked chunks
+  DC_LAY,        // edges walked in layers (above DC_LAY_SHIFT) and their chunks
+  DC_QL,         // queue of those chunks
   DC_COUNT
 };
+constexpr int DC_LAY_SHIFT = 36;
 constexpr int32_t TV_CHUNK = 4096;      // entries of a touched row per piece in the edge-local degree passes
 struct DeltaArgs {
   PoolDev P;                          // union view left by the tombstone merge
@@ -212,6 +215,7 @@ struct DeltaArgs {
   unsigned long long* ce;             // changed pairs (u < v) | nibble << 60
   int64_t ce_cap;
   int32_t *e_ns, *e_dt;               // [ce_cap] per changed pair: common neighbours, change of t
+  int32_t* e_out;                     // [ce_cap] common neighbours that the pair's bitmap leaves out
   int64_t* e_kw;                      // [ce_cap] and the entries of the common neighbours' rows
   // affected edges: a hash table of resident positions + 1 (0: free; all free
   // between passes) with the change of t, and the slots taken (slot | an end << 32)
@@ -222,9 +226,14 @@ struct DeltaArgs {
   int64_t ae_cap;
   unsigned long long* dc;             // [DC_COUNT] counters of the stage
   int32_t* c4_nch;                    // [ce_cap] pairs (e, a) per changed edge: degree of the end walked from
-  int32_t* c4_side;                   // [ce_cap] bit 0: walk from v instead of u; bit 1: against a bitmap
+  int32_t* c4_side;                   // [ce_cap] bit 0: walk from v instead of u; bit 1: against a bitmap; bit 2: in layers
   int32_t* c4_low;                    // [ce_cap] entries of the other end's row below the bitmap's window
   uint32_t c4_ids;                    // ids a bitmap covers (0 or too many: launch_delta sets the most)
+  int32_t c4_out;                     // > 0: an edge whose bitmap leaves out more members is walked in layers (tests)
+  uint32_t lay_ids;                   // ids a window of the layers covers (set by launch_delta)
+  // edges walked in layers: their index (4-cliques: after all 4-cycles) and first chunk
+  int32_t* lay_list;                  // [2 ce_cap]
+  int64_t* lay_off;                   // [2 ce_cap]
   int64_t* c4_off;                    // [ce_cap + 1] exclusive scan of c4_nch
   // searched pairs (DC_SEARCH of them): changed edge, index (below the degree
   // of the end walked from: pair (e, a), else (e, b)) and entries walked
