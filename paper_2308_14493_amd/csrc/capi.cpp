@@ -1062,7 +1062,7 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
 
 // Buffers of an edge-local pass for batches of capacity cap_t (allocates:
 // never called during stream capture).
-void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t pair_need) {
+void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t pair_need, int64_t min_slots = 0) {
   const int64_t ce_cap = std::max<int64_t>(cap_t, 64);
   G->ce.ensure(ce_cap * 8);
   const int64_t ce = (int64_t)(G->ce.cap / 8);
@@ -1083,7 +1083,7 @@ void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t pair_need) 
   // between passes)
   G->ae_cap = std::max<int64_t>(G->ae_cap, std::max<int64_t>(ae_need, 8 * cap_t + 4096));
   G->hl.ensure(G->ae_cap * 8);
-  const int64_t slots = pow2_at_least(G->ae_cap + G->ae_cap / 2);
+  const int64_t slots = std::max(min_slots, pow2_at_least(G->ae_cap + G->ae_cap / 2));
   if (slots > (int64_t)G->hmask + 1 || !G->hk.p) {
     G->hmask = 0;
     G->hk.ensure(slots * 8);
@@ -1234,14 +1234,17 @@ int settle_delta(gc_graph* G, const PassPlan& L, BatchWork& W) {
     HIPCHK(hipMemcpyAsync(dc, G->dctr.p, sizeof(dc), hipMemcpyDeviceToHost, s));
     G->sync();
     const double tot = (double)std::max<int64_t>(L.total, 1);
-    G->ae_per_update = std::max(G->ae_per_update, (double)dc[DC_AFF_NEED] / tot);
+    // (the moves counted may be many more than the edges there are)
+    const int64_t edges = L.union_bound / 2, ae_need = std::min((int64_t)dc[DC_AFF_NEED], edges);
+    G->ae_per_update = std::max(G->ae_per_update, (double)ae_need / tot);
     G->pair_per_update = std::max(G->pair_per_update, (double)dc[DC_PAIR_NEED] / tot);
     // what the stopped attempt left in the tables goes, then they may grow
     fill_u64(G->hk.as<unsigned long long>(), 0ull, (int64_t)G->hmask + 1, s);
     fill_u32(G->hd.as<uint32_t>(), 0u, (int64_t)G->hmask + 1, s);
     fill_u64(G->dTs.as<unsigned long long>(), 0ull, G->N, s);
-    size_delta(G, L.cap_t, (int64_t)dc[DC_AFF_NEED] + (int64_t)dc[DC_AFF_NEED] / 4,
-               (int64_t)dc[DC_PAIR_NEED] + (int64_t)dc[DC_PAIR_NEED] / 4);
+    size_delta(G, L.cap_t, std::min(ae_need + ae_need / 4, edges),
+               (int64_t)dc[DC_PAIR_NEED] + (int64_t)dc[DC_PAIR_NEED] / 4,
+               dc[DC_AFF_FULL] ? 2 * ((int64_t)G->hmask + 1) : 0);
     reset_count_stage(G);
     launch_delta(make_delta_args(G, W), s);
     launch_combine(2, G->sig.as<unsigned long long>(), G->state.as<long long>(), G->vout.as<long long>(), G->k,
@@ -1372,10 +1375,11 @@ void apply(gc_graph* G, const gc_batch_desc* b, int nb, bool dev, bool seq, int6
   G->scan_tmp.ensure(scan_tmp_bytes(std::max<int64_t>(L.max_touched, G->N) + 1) + 64);
   size_count_scratch(G, L.nv, L.union_bound);
   if (L.delta) {
-    // at the demand per update seen so far (within 2^26 entries a list: a
-    // larger demand is met by the retry, which sizes for the batch at hand)
+    // at the demand per update seen so far (within 2^26 entries a list, and
+    // the edges there are: a larger demand is met by the retry, which sizes
+    // for the batch at hand)
     const double lim = (double)(1ll << 26);
-    size_delta(G, L.cap_t, (int64_t)std::min(lim, 1.25 * G->ae_per_update * (double)L.cap_t),
+    size_delta(G, L.cap_t, (int64_t)std::min({lim, 0.5 * (double)L.union_bound, 1.25 * G->ae_per_update * (double)L.cap_t}),
                (int64_t)std::min(lim, 1.25 * G->pair_per_update * (double)L.cap_t));
   }
   // arena reserve: enough for every touched row to move

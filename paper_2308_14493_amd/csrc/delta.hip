@@ -445,7 +445,11 @@ __device__ __forceinline__ bool t_move(const DeltaArgs& D, int64_t pos, int32_t 
   for (int k = 0; k < 512; ++k, h = (h + 1) & D.hmask) {
     unsigned long long old = __hip_atomic_load(&D.hk[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (old == 0ull) old = atomicCAS(&D.hk[h], 0ull, key);
-    if (old != 0ull && old != key) continue;
+    if (old != 0ull && old != key) {
+      // a table found full is not searched to the end again
+      if ((k & 31) == 31 && __hip_atomic_load(&D.dc[DC_AFF_FULL], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
+      continue;
+    }
     atomicAdd(&D.hd[h], d);
     slot = h;
     return old == 0ull;
@@ -658,7 +662,7 @@ __global__ void k_delta_check(DeltaArgs D) {
   }
   if ((int64_t)D.dc[DC_AFF] > D.ae_cap || D.dc[DC_AFF_FULL]) {
     atomicAdd(&D.bstats[BS_RETRY], 1ull);
-    // distinct edges are fewer than the moves
+    // distinct edges are fewer than the moves (and than the edges: the host)
     atomicMax(&D.dc[DC_AFF_NEED], D.dc[DC_AFF_INST] + D.dc[DC_EDGES]);
   }
 }
