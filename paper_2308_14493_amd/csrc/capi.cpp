@@ -224,8 +224,8 @@ struct gc_graph {
   DevBuf c4_dense, c4_touch, c4_cur, c4_blk, c4_keys, c4_keys_alt, tri_scratch;
   // triangles at each vertex (kept for the edge-local passes) and the
   // scratch of those passes
-  DevBuf Tv, dTs, ce, hk, hd, hl, e_ns, e_dt, e_out, e_kw, slist, lay_list, lay_off, dctr, c4_nch, c4_side, c4_low, c4_off, pair_edge, pair_idx,
-      pair_len, pair_off, pair_hlen, pair_hoff, tv_items, tv_ioff;
+  DevBuf Tv, dTs, ce, hk, hd, hl, e_ns, e_dt, e_out, e_kw, slist, lay_list, lay_off, c4_nch, c4_side, c4_low, c4_off,
+      pair_edge, pair_idx, pair_len, pair_off, pair_hlen, pair_hoff, tv_items, tv_ioff;
   int64_t ae_cap = 0, pair_cap = 0;
   uint32_t hmask = 0;                // slots of hk, hd less one
   // largest affected-edge and 4-cycle-pair demand per update seen in an
@@ -371,7 +371,7 @@ struct gc_graph {
 namespace {
 
 void zero_small(gc_graph* G) {
-  zero3_u64(G->ctr.as<unsigned long long>(), C_COUNT, G->bstats.as<unsigned long long>(), BS_COUNT,
+  zero3_u64(G->ctr.as<unsigned long long>(), C_COUNT, G->bstats.as<unsigned long long>(), BS_COUNT + DC_COUNT,
             G->sig.as<unsigned long long>(), (int64_t)G->k * GC_NV_MAX * SG_N, G->stream);
 }
 
@@ -379,7 +379,7 @@ void zero_small(gc_graph* G) {
 // and sums (the ingest and merge counters stay).
 void reset_count_stage(gc_graph* G) {
   fill_u64(G->ctr.as<unsigned long long>() + C_RLIST, 0ull, C_COUNT - C_RLIST, G->stream);
-  fill_u64(G->bstats.as<unsigned long long>() + BS_COUNT_STAGE, 0ull, BS_COUNT - BS_COUNT_STAGE, G->stream);
+  fill_u64(G->bstats.as<unsigned long long>() + BS_COUNT_STAGE, 0ull, BS_COUNT + DC_COUNT - BS_COUNT_STAGE, G->stream);
   fill_u64(G->sig.as<unsigned long long>(), 0ull, (int64_t)G->k * GC_NV_MAX * SG_N, G->stream);
 }
 
@@ -669,13 +669,12 @@ void alloc_vertex_arrays(gc_graph* G) {
   G->vout.ensure((size_t)(GC_NV_MAX - 1) * G->k * ST_STRIDE * sizeof(long long));
   G->sig.ensure((size_t)G->k * GC_NV_MAX * SG_N * sizeof(unsigned long long));
   G->ctr.ensure(C_COUNT * sizeof(unsigned long long));
-  G->bstats.ensure(BS_COUNT * sizeof(unsigned long long));
+  G->bstats.ensure((BS_COUNT + DC_COUNT) * sizeof(unsigned long long));  // with the edge-local stage's counters
   G->top.ensure(sizeof(unsigned long long));
   for (DevBuf* b : {&G->Tv, &G->dTs}) {
     b->ensure(N * sizeof(long long));
     fill_u64(b->as<unsigned long long>(), 0ull, N, s);
   }
-  G->dctr.ensure(DC_COUNT * sizeof(unsigned long long));
   if (!G->pout) HIPCHK(hipHostMalloc(&G->pout, G->out_bytes(), hipHostMallocDefault));
 }
 
@@ -1035,7 +1034,7 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
   D.hmask = G->hmask;
   D.hl = G->hl.as<unsigned long long>();
   D.ae_cap = G->ae_cap;
-  D.dc = G->dctr.as<unsigned long long>();
+  D.dc = D.bstats + BS_COUNT;
   D.c4_nch = G->c4_nch.as<int32_t>();
   D.c4_side = G->c4_side.as<int32_t>();
   D.c4_low = G->c4_low.as<int32_t>();
@@ -1231,7 +1230,7 @@ int settle_delta(gc_graph* G, const PassPlan& L, BatchWork& W) {
     if (++attempts > G->retry_limit)
       raise(GC_EDEVICE, "edge-local scratch still too small after %d more attempts", G->retry_limit);
     unsigned long long dc[DC_COUNT];
-    HIPCHK(hipMemcpyAsync(dc, G->dctr.p, sizeof(dc), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipMemcpyAsync(dc, G->bstats.as<unsigned long long>() + BS_COUNT, sizeof(dc), hipMemcpyDeviceToHost, s));
     G->sync();
     const double tot = (double)std::max<int64_t>(L.total, 1);
     // (the moves counted may be many more than the edges there are)
@@ -1274,7 +1273,8 @@ std::vector<uint64_t> pass_signature(gc_graph* G, const PassPlan& L, const Count
                           &G->sort_tmp, &G->scan_tmp, &G->roff, &G->rcol, &G->rrow, &G->rlow, &G->dver, &G->t,
                           &G->tp, &G->vpos, &G->level, &G->rlist, &G->rlen, &G->lists, &G->c4_dense, &G->c4_touch,
                           &G->c4_cur, &G->c4_blk, &G->c4_keys, &G->c4_keys_alt, &G->tri_scratch, &G->Tv, &G->dTs,
-                          &G->ce, &G->hk, &G->hd, &G->hl, &G->e_ns, &G->e_dt, &G->e_out, &G->e_kw, &G->slist, &G->lay_list, &G->lay_off, &G->dctr,
+                          &G->ce, &G->hk, &G->hd, &G->hl, &G->e_ns, &G->e_dt, &G->e_out, &G->e_kw, &G->slist,
+                          &G->lay_list, &G->lay_off,
                           &G->c4_nch, &G->c4_side, &G->c4_low, &G->c4_off, &G->pair_edge, &G->pair_idx, &G->pair_len,
                           &G->pair_off, &G->pair_hlen, &G->pair_hoff, &G->tt, &G->scratch_t, &G->dead_d, &G->tv_items,
                           &G->tv_ioff};

@@ -224,7 +224,7 @@ struct DeltaArgs {
   uint32_t hmask;
   unsigned long long* hl;             // [ae_cap]
   int64_t ae_cap;
-  unsigned long long* dc;             // [DC_COUNT] counters of the stage
+  unsigned long long* dc;             // [DC_COUNT] counters of the stage, zero on entry
   int32_t* c4_nch;                    // [ce_cap] pairs (e, a) per changed edge: degree of the end walked from
   int32_t* c4_side;                   // [ce_cap] bit 0: walk from v instead of u; bit 1: against a bitmap; bit 2: in layers
   int32_t* c4_low;                    // [ce_cap] entries of the other end's row below the bitmap's window
