@@ -595,21 +595,38 @@ __device__ __forceinline__ void tri_large_probe(const CountArgs& A, const TriL<N
 // exceptions below searched slot by slot) k_tri_large<128> took 1.01 ms on a
 // scale-18 graph with 5% of the edges in the batch, all tiers 81 ms at scale
 // 22; now 0.54 and 70 ms.
-template <int NV>
-__device__ __forceinline__ void k4_edges(const TriL<NV>& S, int32_t dp, int nwaves, int vers, int64_t (&kv)[NV]) {
+//
+// DENSE, the tiers above 512 slots, whose counts take longest in dense graphs:
+// a word with at least K4_DENSE of its edges is not packed (row i and the
+// first word are then the same for every lane), and ONE version alone, the
+// usual case there, masks the words as they are read and keeps one sum.
+// Without these a count of the complete graph of 1,500 vertices with 20,000
+// of its edges in the batch took 87 ms instead of 74, of 3,000 vertices 2.05 s
+// instead of 1.71 (with a lane per bit throughout, 84 ms and 1.54 s).
+constexpr int K4_DENSE = 48;
+
+template <int NV, bool DENSE, bool ONE>
+__device__ __forceinline__ void k4_edges_(const TriL<NV>& S, int32_t dp, int nwaves, int vers, int64_t (&kv)[NV]) {
   const int w = threadIdx.x >> 6, l = lane_id();
   const int32_t W = S.W;
   uint32_t* qi = S.queue + w * 256;
   uint32_t* qj = qi + 128;
   int32_t n = 0;  // listed edges
-  auto run = [&](int32_t k) {
-    const int32_t i = (int32_t)qi[k], j = (int32_t)qj[k];
+  const unsigned long long* Pm = S.P + (__ffs(vers) - 1) * W;  // ONE: the version's slots
+  int64_t one = 0;
+  auto edge = [&](int32_t i, int32_t j, int32_t q0) {
     const unsigned long long* Ei = S.erow(i);
     const unsigned long long* Ej = S.erow(j);
+    if constexpr (ONE) {
+      uint32_t c = 0;
+      for (int32_t q = q0; q < W; ++q) c += (uint32_t)__popcll(Ei[q] & Ej[q] & Pm[q]);
+      one += c;
+      return;
+    }
     uint32_t c[NV];
 #pragma unroll
     for (int x = 0; x < NV; ++x) c[x] = 0;
-    for (int32_t q = j >> 6; q < W; ++q) {
+    for (int32_t q = q0; q < W; ++q) {
       const unsigned long long e = Ei[q] & Ej[q];
 #pragma unroll
       for (int x = 0; x < NV; ++x)
@@ -619,12 +636,22 @@ __device__ __forceinline__ void k4_edges(const TriL<NV>& S, int32_t dp, int nwav
     for (int x = 0; x < NV; ++x)
       if (((vers >> x) & 1) && bit_of(S.P + x * W, i) && bit_of(S.P + x * W, j)) kv[x] += c[x];
   };
+  auto run = [&](int32_t k) {
+    const int32_t j = (int32_t)qj[k];
+    edge((int32_t)qi[k], j, j >> 6);
+  };
   for (int32_t i = w; i < dp; i += nwaves) {
+    if (ONE && !bit_of(Pm, i)) continue;
     const unsigned long long* Ei = S.erow(i);
     for (int32_t w0 = i >> 6; w0 < W; ++w0) {
-      const bool in = (Ei[w0] >> l) & 1ull;
+      const unsigned long long word = ONE ? Ei[w0] & Pm[w0] : Ei[w0];
+      const bool in = (word >> l) & 1ull;
       const uint64_t m = __ballot(in);
       if (!m) continue;
+      if (DENSE && __popcll(m) >= K4_DENSE) {
+        if (in) edge(i, w0 * 64 + l, w0);
+        continue;
+      }
       if (in) {
         const int32_t k = n + __popcll(m & lanemask_lt());
         qi[k] = (uint32_t)i;
@@ -641,9 +668,19 @@ __device__ __forceinline__ void k4_edges(const TriL<NV>& S, int32_t dp, int nwav
   }
   wave_sync();
   if (l < n) run(l);
+  if constexpr (ONE) {
+#pragma unroll
+    for (int x = 0; x < NV; ++x) kv[x] += (vers >> x) & 1 ? one : 0;
+  }
 }
 
-template <int NV>
+template <int NV, bool DENSE>
+__device__ __forceinline__ void k4_edges(const TriL<NV>& S, int32_t dp, int nwaves, int vers, int64_t (&kv)[NV]) {
+  if (DENSE && (vers & (vers - 1)) == 0) k4_edges_<NV, DENSE, true>(S, dp, nwaves, vers, kv);
+  else k4_edges_<NV, DENSE, false>(S, dp, nwaves, vers, kv);
+}
+
+template <int NV, bool DENSE>
 __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t ub, int32_t dp,
                                  int64_t (&kacc)[NV], int64_t& ent) {
   const RegionDev& R = A.R;
@@ -703,7 +740,7 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
     for (int x = 0; x < NV; ++x) {
       flip(x, true);
       __syncthreads();
-      k4_edges<NV>(S, dp, nwaves, 1 << x, kacc);
+      k4_edges<NV, DENSE>(S, dp, nwaves, 1 << x, kacc);
       __syncthreads();
       if (x < NV - 1) flip(x, false);
     }
@@ -723,7 +760,7 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
       }
       if (same[x] == x) vers |= 1 << x;
     }
-    k4_edges<NV>(S, dp, nwaves, vers, kv);
+    k4_edges<NV, DENSE>(S, dp, nwaves, vers, kv);
 #pragma unroll
     for (int x = 1; x < NV; ++x)
 #pragma unroll
@@ -801,7 +838,7 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
       __syncthreads();
       for (int32_t g0 = w; g0 < dp; g0 += nwaves * 64) tri_large_probe<NV>(A, S, hmask, shift, g0, nwaves, dp, x + 1, ent);
       __syncthreads();
-      k4_edges<NV>(S, dp, nwaves, 1 << x, kacc);
+      k4_edges<NV, DENSE>(S, dp, nwaves, 1 << x, kacc);
     }
   }
   __syncthreads();
@@ -838,6 +875,7 @@ constexpr int pow2_at_least(int x) {
 // Registers: the tiers up to 256 hide their latencies with 6 waves per SIMD (5
 // with four versions, which spill below 96 registers); without the bound they
 // took 17.8 against 13.3 ms (<256>) and 12.5 against 9.5 ms (<128>) at scale 22.
+constexpr int TG_HASH = 8192;
 template <int CAP, int THREADS, int NV>
 __global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 : 5)) void k_tri_large(CountArgs A, int L, unsigned long long* qhead) {
   const RegionDev& R = A.R;
@@ -850,6 +888,13 @@ __global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 :
   int64_t ent = 0;  // entries of N+(u) and of the lists probed (algorithmic reads)
   TriL<NV> S;
   using TU = typename TriL<NV>::TU;
+  // CAP = 0: the hash in LDS up to TG_HASH / 2 slots, else in the scratch (a
+  // lookup waits for its loads: 79 instead of 74 ms for the graph of 1,500)
+  __shared__ int32_t tkey[CAP == 0 ? TG_HASH : 1];
+  __shared__ uint32_t tval[CAP == 0 ? TG_HASH : 1];
+  int32_t* gkey = nullptr;
+  uint32_t* gval = nullptr;
+  int32_t ghc = 0;
   if constexpr (CAP == 0) {
     // slot layout for capacity tri_cap (no slot is touched while tri_cap == 0)
     const int64_t cap = A.tri_cap > 0 ? A.tri_cap : 1;
@@ -863,12 +908,12 @@ __global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 :
     S.xcap = 2 * TL_EXC;
     uint32_t* u32 = S.exc + 2 * TL_EXC;
     S.ids = u32;
-    S.hkey = (int32_t*)(u32 + cap);
-    S.hval = u32 + 5 * cap;
+    gkey = (int32_t*)(u32 + cap);
+    gval = u32 + 5 * cap;
     S.nexc = (int32_t*)(u32 + 9 * cap);
     int32_t hc = 1;
     while (2 * hc <= 4 * cap) hc <<= 1;
-    S.hcap = hc;
+    ghc = hc;
     __shared__ uint32_t filt[8192];
     __shared__ uint32_t queue[THREADS / 64 * 256];
     S.filt = filt;
@@ -920,8 +965,15 @@ __global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 :
       if (cur_g >= 0) flushv<NV>(A.sig, cur_g, SG_K4, kacc);
       cur_g = g;
     }
-    if constexpr (CAP != 0) S.W = (dp + 63) / 64;
-    tri_large_vertex<NV>(A, S, ub, dp, kacc, ent);
+    if constexpr (CAP != 0) {
+      S.W = (dp + 63) / 64;
+    } else {
+      const bool lds = 2 * dp <= TG_HASH;
+      S.hkey = lds ? tkey : gkey;
+      S.hval = lds ? tval : gval;
+      S.hcap = lds ? TG_HASH : ghc;
+    }
+    tri_large_vertex<NV, (CAP == 0 || CAP > 512)>(A, S, ub, dp, kacc, ent);
   }
   if (cur_g >= 0) flushv<NV>(A.sig, cur_g, SG_K4, kacc);
   ent = wave_sum64(ent);
