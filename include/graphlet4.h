@@ -320,7 +320,9 @@ int gc_export_edges(gc_graph* g, int32_t graph, int32_t* src, int32_t* dst, int6
 
 /* Estimated device bytes a single-graph handle built from this edge list
  * reaches (resident rows with slack, region view, per-edge triangle counts,
- * hub counters, multi-version passes, the transient arrays of the build),
+ * hub counters, multi-version passes, the transient arrays of the build or of
+ * a compaction of the rows, and, unless opt->delta is -1, the lists of
+ * edge-local batches of up to 2^18 updates, at the size they start with),
  * from the same sizing rules the library allocates by; batch staging is not
  * included.  Host arrays; needs no device.  The server's admission uses it.
  * Library interface, not in the paper. */

@@ -147,24 +147,41 @@ void gc_set_error(const char* msg) { g_err = msg ? msg : ""; }
 // four entries at a time.
 size_t t_bytes(int64_t E) { return (size_t)E * 8 + 32; }
 
+// Sizes of the edge-local passes' lists for batches of capacity cap_t whose
+// demand is not known: changed edges, pairs, affected edges and the slots of
+// their table (at most two thirds full).
+struct DeltaSizes {
+  int64_t ce, pairs, ae, slots;
+  static int64_t slots_for(int64_t ae) { return pow2_at_least(ae + ae / 2); }
+  explicit DeltaSizes(int64_t cap_t)
+      : ce(std::max<int64_t>(cap_t, 64)), pairs(64 * cap_t + 4096), ae(8 * cap_t + 4096), slots(slots_for(ae)) {}
+  // ce, c4_nch, c4_side, c4_low, e_ns, e_dt, e_out, e_kw, c4_off, tv_items,
+  // tv_ioff, lay_list, lay_off; pair_edge, pair_idx, pair_len, pair_hlen (two
+  // a pair), pair_off, pair_hoff, slist; hl; hk, hd; scans of the pairs
+  int64_t bytes() const {
+    return 96 * ce + 68 * pairs + 8 * ae + 12 * slots + (int64_t)scan_tmp_bytes(2 * pairs + 1);
+  }
+};
+
 // Device bytes a single-graph handle reaches, from the sizing rules of
-// build(), alloc_vertex_arrays() and size_count_scratch() (multi-version
-// passes included), for a graph of n vertices and m edges whose largest
-// degree is max_deg and whose largest out-degree under the build order is
-// max_out.  Batch staging is not included.
-int64_t gc_footprint_estimate(int64_t n, int64_t m, double slack, int64_t max_deg, int64_t max_out) {
+// build(), alloc_vertex_arrays(), size_count_scratch() (multi-version passes
+// included), compact() and, with local, size_delta(), for a graph of n
+// vertices and m edges whose largest degree is max_deg and whose largest
+// out-degree under the build order is max_out.  Batch staging is not included.
+int64_t gc_footprint_estimate(int64_t n, int64_t m, double slack, int64_t max_deg, int64_t max_out, bool local) {
   const int64_t N = std::max<int64_t>(n, 1), E = 2 * m;
   int64_t b = 0;
   // resident rows (off, len, cap, gid, ext2int, int2ext) and the arena
   b += 28 * N;
   const int64_t used = (int64_t)((1.0 + slack) * (double)E) + 2 * N;
-  b += 8 * std::max<int64_t>(4 * used, used + (1 << 20));  // entries and their triangle counts
+  const int64_t arena = 8 * std::max<int64_t>(4 * used, used + (1 << 20));  // entries and their triangle counts
+  b += arena;
   // per-vertex pass arrays and work lists
   b += (10 + L_NUM) * 4 * N;
   // region view of the union (entries grow by a quarter when exceeded) and
   // the merge scratch: rcol, rrow, t, vpos (20 B) + tp (16 B) per entry
   const int64_t e_alloc = E + E / 2 + (1 << 20);
-  b += 36 * e_alloc + 8 * e_alloc;
+  b += 36 * e_alloc + 4 * e_alloc;
   b += 8 * (N + 1) + 16 * N + 4 * GC_NV_MAX * N;  // roff, c4 keys, degrees per version
   b += (int64_t)radix_sort_tmp_bytes(std::max<int64_t>(2 * m, N)) + (int64_t)scan_tmp_bytes(N + 1);
   // hub counters of the large 4-cycle tier and their cursors
@@ -178,14 +195,15 @@ int64_t gc_footprint_estimate(int64_t n, int64_t m, double slack, int64_t max_de
     const int64_t cap = std::min<int64_t>(32767, max_out + max_out / 8 + 16);
     b += 256 * tri_scratch_words64(4, cap) * 8;
   }
-  // triangles per vertex and the edge-local passes' affected edges (list and
-  // table for a batch of 2^18 updates)
+  // triangles per vertex, and the lists of edge-local batches of up to 2^18
+  // updates (or as many as fit the graph twice)
   b += 16 * N;
-  const int64_t ae = 8 * ((int64_t)1 << 18) + 4096;
-  b += 8 * ae + 12 * pow2_at_least(ae + ae / 2);
-  // the transient arrays of the build (64 bytes per edge) are freed before the
-  // region arrays above, which need more, are allocated
-  return b + ((int64_t)32 << 20);
+  if (local) b += DeltaSizes(std::min<int64_t>((int64_t)1 << 18, std::max<int64_t>(128, 2 * pow2_at_least(m)))).bytes();
+  // for a while: the transient arrays of the build (edge keys, directed
+  // entries, ranks; a larger id space is built beside the region arrays), or
+  // a second arena during compaction
+  b += std::max<int64_t>(64 * m + 24 * N, arena + 12 * N);
+  return b + ((int64_t)64 << 20);
 }
 
 struct gc_graph {
@@ -217,7 +235,7 @@ struct gc_graph {
   // batch scratch
   DevBuf bin, keys, keys_alt, dirA, dirA_alt, dirD, dirR, dirR_alt;
   DevBuf a_beg, na, r_beg, nr, mark, tix;
-  DevBuf touched, dest, newcap, tlen, tpre, scratch, scratch_t, sort_tmp, scan_tmp;
+  DevBuf touched, dest, newcap, tlen, tpre, scratch, sort_tmp, scan_tmp;
 
   // region and counting
   DevBuf roff, rcol, rrow, rlow, dver, t, tp, vpos, level, rlist, rlen, lists;
@@ -587,6 +605,7 @@ int settle_retries(gc_graph* G, int nv, int radius, long long* state_d, BatchWor
       raise(GC_EDEVICE, "counting scratch still too small after %d more attempts", G->retry_limit);
     note_maxima(G);
     size_count_scratch(G, nv, entries);
+    W.scratch_t = G->vpos.as<uint32_t>();
     reset_count_stage(G);
     CountArgs A = make_count_args(G, nv, dense_min, fresh);
     enqueue_count(G, nv, radius, state_d, W, A, false, tv);
@@ -649,7 +668,9 @@ BatchWork make_work(gc_graph* G, const Staging& S) {
   W.tlen = S.tlen;
   W.tpre = S.tpre;
   W.scratch = G->scratch.as<uint32_t>();
-  W.scratch_t = G->scratch_t.as<uint32_t>();
+  // rows are copied before a count reads its cursors and after it is done with
+  // them (vpos holds the entries of the union view, as scratch does)
+  W.scratch_t = G->vpos.as<uint32_t>();
   return W;
 }
 
@@ -904,7 +925,6 @@ void build(gc_graph* G, int32_t k, const int64_t* n, const int32_t* const* src, 
   // the merge's copy of the touched rows, as large as the region view, so
   // that a batch can be applied without growing it
   G->scratch.ensure(std::max<int64_t>(G->e_alloc, 1) * 4);
-  G->scratch_t.ensure(std::max<int64_t>(G->e_alloc, 1) * 4);
   // sort and scan temporaries for batches up to the allocation-free limit
   // (2^18 insertions and 2^18 deletions: 2^20 touched rows at most)
   G->sort_tmp.ensure(radix_sort_tmp_bytes(std::max<int64_t>(std::max<int64_t>(2 * M, N), 1 << 20)) + 64);
@@ -1062,13 +1082,13 @@ DeltaArgs make_delta_args(gc_graph* G, const BatchWork& W) {
 // Buffers of an edge-local pass for batches of capacity cap_t (allocates:
 // never called during stream capture).
 void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t pair_need, int64_t min_slots = 0) {
-  const int64_t ce_cap = std::max<int64_t>(cap_t, 64);
-  G->ce.ensure(ce_cap * 8);
+  const DeltaSizes first(cap_t);
+  G->ce.ensure(first.ce * 8);
   const int64_t ce = (int64_t)(G->ce.cap / 8);
   for (DevBuf* b : {&G->c4_nch, &G->c4_side, &G->c4_low, &G->e_ns, &G->e_dt, &G->e_out}) b->ensure(ce * 4);
   G->e_kw.ensure(ce * 8);
   G->c4_off.ensure((ce + 1) * 8);
-  G->pair_cap = std::max<int64_t>(G->pair_cap, std::max<int64_t>(pair_need, 64 * cap_t + 4096));
+  G->pair_cap = std::max<int64_t>(G->pair_cap, std::max(pair_need, first.pairs));
   for (DevBuf* b : {&G->pair_edge, &G->pair_idx, &G->pair_len, &G->pair_hlen}) b->ensure(2 * G->pair_cap * 4);
   for (DevBuf* b : {&G->pair_off, &G->pair_hoff}) b->ensure((2 * G->pair_cap + 1) * 8);
   G->slist.ensure(G->pair_cap * 4);
@@ -1078,11 +1098,10 @@ void size_delta(gc_graph* G, int64_t cap_t, int64_t ae_need, int64_t pair_need, 
   G->lay_list.ensure(2 * ce * 4);
   G->lay_off.ensure(2 * ce * 8);
   G->scan_tmp.ensure(scan_tmp_bytes(std::max<int64_t>(2 * ce, 2 * G->pair_cap) + 1) + 64);
-  // affected edges: the list, and a table at most two thirds full (free
-  // between passes)
-  G->ae_cap = std::max<int64_t>(G->ae_cap, std::max<int64_t>(ae_need, 8 * cap_t + 4096));
+  // affected edges: the list and the table (free between passes)
+  G->ae_cap = std::max<int64_t>(G->ae_cap, std::max(ae_need, first.ae));
   G->hl.ensure(G->ae_cap * 8);
-  const int64_t slots = std::max(min_slots, pow2_at_least(G->ae_cap + G->ae_cap / 2));
+  const int64_t slots = std::max(min_slots, DeltaSizes::slots_for(G->ae_cap));
   if (slots > (int64_t)G->hmask + 1 || !G->hk.p) {
     G->hmask = 0;
     G->hk.ensure(slots * 8);
@@ -1276,7 +1295,7 @@ std::vector<uint64_t> pass_signature(gc_graph* G, const PassPlan& L, const Count
                           &G->ce, &G->hk, &G->hd, &G->hl, &G->e_ns, &G->e_dt, &G->e_out, &G->e_kw, &G->slist,
                           &G->lay_list, &G->lay_off,
                           &G->c4_nch, &G->c4_side, &G->c4_low, &G->c4_off, &G->pair_edge, &G->pair_idx, &G->pair_len,
-                          &G->pair_off, &G->pair_hlen, &G->pair_hoff, &G->tt, &G->scratch_t, &G->dead_d, &G->tv_items,
+                          &G->pair_off, &G->pair_hlen, &G->pair_hoff, &G->tt, &G->dead_d, &G->tv_items,
                           &G->tv_ioff};
   for (const DevBuf* b : bufs) v.push_back((uint64_t)(uintptr_t)b->p);
   v.push_back((uint64_t)(uintptr_t)G->pin);
@@ -1369,7 +1388,6 @@ void apply(gc_graph* G, const gc_batch_desc* b, int nb, bool dev, bool seq, int6
   G->tlen.ensure(L.max_touched * 4);
   G->tpre.ensure((L.max_touched + 1) * 8);
   G->scratch.ensure(std::max<int64_t>(L.union_bound, 1) * 4);
-  G->scratch_t.ensure(std::max<int64_t>(L.union_bound, 1) * 4);
   G->sort_tmp.ensure(radix_sort_tmp_bytes(std::max<int64_t>(std::max(L.cap_t, 2 * std::max(L.cap_i, L.cap_d)), G->N)) +
                      64);
   G->scan_tmp.ensure(scan_tmp_bytes(std::max<int64_t>(L.max_touched, G->N) + 1) + 64);
@@ -1672,8 +1690,7 @@ void apply_noalloc(gc_graph* G, const int32_t* iu, const int32_t* iv, int64_t n_
   const int64_t arena_need = (int64_t)((1.0 + G->opt.slack) * (double)L.union_bound) + 8 * L.max_touched + 1024;
   const char* short_of = G->sort_tmp.cap < sort_need                                          ? "sort temporaries"
                          : G->scan_tmp.cap < scan_need                                        ? "scan temporaries"
-                         : std::min(G->scratch.cap, G->scratch_t.cap) < (size_t)std::max<int64_t>(L.union_bound, 4) * 4
-                             ? "merge scratch"
+                         : G->scratch.cap < (size_t)std::max<int64_t>(L.union_bound, 4) * 4 ? "merge scratch"
                          : count_scratch_short(G, 2, L.union_bound)                           ? count_scratch_short(G, 2, L.union_bound)
                          : G->arena_cap - G->arena_top < arena_need                           ? "resident rows"
                                                                                               : nullptr;
@@ -2174,7 +2191,7 @@ int gc_graph_footprint(int64_t n, const int32_t* src, const int32_t* dst, int64_
       max_deg = std::max<int64_t>(max_deg, deg[v]);
       max_out = std::max<int64_t>(max_out, out[v]);
     }
-    *bytes = gc_footprint_estimate(std::max<int64_t>(n, o.vertex_capacity), m, o.slack, max_deg, max_out);
+    *bytes = gc_footprint_estimate(std::max<int64_t>(n, o.vertex_capacity), m, o.slack, max_deg, max_out, o.delta >= 0);
   });
 }
 

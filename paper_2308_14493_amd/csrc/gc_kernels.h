@@ -259,4 +259,4 @@ void launch_tv_region(int nv, const PoolDev& P, const RegionDev& R, const int32_
 
 void gc_set_error(const char* msg);
 // device bytes a single-graph handle reaches (capi.cpp); used by the server's admission
-int64_t gc_footprint_estimate(int64_t n, int64_t m, double slack, int64_t max_deg, int64_t max_out);
+int64_t gc_footprint_estimate(int64_t n, int64_t m, double slack, int64_t max_deg, int64_t max_out, bool local);
