@@ -412,7 +412,9 @@ void size_count_scratch(gc_graph* G, int nv, int64_t entries) {
   G->c4_keys_alt.ensure(N * sizeof(unsigned long long));
   G->sort_tmp.ensure(radix_sort_tmp_bytes(N) + 64);
   G->scan_tmp.ensure(scan_tmp_bytes(N + 1) + 64);
-  if (entries > G->e_alloc) G->e_alloc = entries + entries / 4 + 1024;
+  // (a multiple of 4: the hub windows read the rows 16 bytes at a time, with up
+  // to 3 entries past a row's end)
+  if (entries > G->e_alloc) G->e_alloc = (entries + entries / 4 + 1024 + 3) & ~(int64_t)3;
   const int64_t E = G->e_alloc;
   G->rcol.ensure(E * sizeof(uint32_t));
   G->rrow.ensure(E * sizeof(int32_t));

@@ -66,3 +66,18 @@ def test_region_inside_a_path(tail, radius):
             got = g.apply_batch(*b)
             oracle_apply(E, n, *b)
             assert got == native.static_counts(n, *pairs(E))
+
+
+def test_region_view_filled_to_its_last_entry():
+    """A region view of 11,034 entries (2 mod 4) at a capacity of as many, every
+    hub in the windows: the rows are read 16 bytes at a time up to the end."""
+    from paper_2308_14493_amd.graphlet4 import Graph
+    print("case region view full", flush=True)
+    n = 4004
+    E = {(v, v + 1) for v in range(n - 1)} | {(0, n - 1)}
+    ins = {(2 * i, 2 * i + 5) for i in range(1, 1514)}  # 8,008 + 2 x 1,513 entries
+    assert not ins & E and len(ins) == 1513
+    with Graph(n, *pairs(E), delta=-1, radius=0, tiers=(64, 1, 1)) as g:
+        got, st = g.apply_batch(*(pairs(ins) + (Z, Z)), stats=True)
+        assert st["region_entries"] == 2 * n + n // 2 + 1024 and st["tier_c4_large"] > 0
+        assert got == native.static_counts(n, *pairs(E | ins))
