@@ -286,10 +286,11 @@ __device__ __forceinline__ void zerov(int64_t (&a)[NV]) {
 }
 
 // t of entry pos: one triangle (or c of them) present in the versions of pm
-// (at least one).  These atomics are what the dense tiers wait for: as 64-bit
-// words with a field per version, k_tri_large<1024> took 24.8 ms at scale 22
-// and <512> 17.4 ms, now 22.9 and 16.7 (without the 4-cliques, during which
-// the queue drains, 20.5 and 16.1 against 12.1 and 11.2).
+// (at least one).  These atomics are what the dense tiers wait for: 32-bit
+// instead of 64-bit words with a field per version took k_tri_large<1024> from
+// 24.8 to 22.9 ms at scale 22 and <512> from 17.4 to 16.7 (without the
+// 4-cliques, during which the queue drains, 20.5 to 12.1 and 16.1 to 11.2);
+// later changes brought them to 18.2 and 13.0.
 template <int NV>
 __device__ __forceinline__ void t_add(const RegionDev& R, int64_t pos, uint32_t pm, uint32_t c = 1u) {
   if constexpr (NV == 2) {

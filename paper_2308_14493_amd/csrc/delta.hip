@@ -33,7 +33,9 @@
 //               pair (s, a): the rows N(a) walked against an LDS bitmap of
 //               N(o), or, where that costs more (little to walk for the edge,
 //               or an N(a) far longer than N(o)), the shorter row walked and
-//               searched in the other.
+//               searched in the other.  What a bitmap leaves out of N(o) or
+//               S(e) is searched too, or, where it is much, the edge is walked
+//               in layers that leave nothing out.
 #include "gc_kernels.h"
 
 #include <algorithm>
@@ -256,7 +258,7 @@ __global__ void k_delta_s2(DeltaArgs D) {
 // ------------------------------------------------------------- 4-cycles
 // Through a changed edge e = (s, o) run the 4-cycles s - a - b - o with
 // a in N(s) - {o}, b in N(a) & N(o) - {s}.  A pair (e, a) is counted in one
-// of two ways (pair_kind): its row N(a) is walked against a bitmap of N(o)
+// of two ways (pair_walked): its row N(a) is walked against a bitmap of N(o)
 // that a workgroup keeps in LDS (k_delta_bits), or the shorter of N(a) and
 // N(o) is walked and each entry searched in the other row (k_delta_search).  s is
 // the end with the smaller total cost.  The work is balanced over the whole
@@ -264,10 +266,13 @@ __global__ void k_delta_s2(DeltaArgs D) {
 // all pairs in one index space, and waves or workgroups take ranges of that
 // space (a hub pair is spread over many waves).
 
-// A walked entry costs one LDS probe; a search step is a dependent global
-// load.  Measured at scale 22: 9.9 ms for 0.6e9 searched entries (about 15
-// steps each) against 3.5e12 probes a second for the walk, so a search of
-// N(o) in N(a) pays only when N(a) is longer by more than this factor.
+// A walked entry costs one LDS probe, a searched one a chain of dependent
+// loads: 9.2e11 walked entries a second at scale 22 (2,500 updates, 5.9e9 of
+// them) and 4.5e11 at scale 18 (1,000 updates, 1.2e8), against 3.7e10 searched.
+// The line lies above their quotient, as the few pairs searched do not hide
+// their chains behind each other.  With 16 and 24 in the place of 64: 1,000
+// updates at scale 18 10% and 3% slower, on the hub graph 2% and 3%, 100 on
+// livejournal's size 5% and 4%, 2,500 at scale 22 1% and as fast.
 constexpr int64_t C4B_RATIO = 64;
 // An edge whose walks sum to less than this does not earn a bitmap (clearing,
 // filling and the queue cost a workgroup about as much as searching so much).
@@ -878,14 +883,17 @@ __global__ void k_delta_hitems(DeltaArgs D) {
 // two members.  The waves split the chunk's entries evenly, read them with
 // consecutive lanes and probe one bit per entry.  Hits on entries that are in
 // the batch themselves take the general rule (rare).
-// What bounds it: instruction issue, about 13 per 64 entries, while the
-// bitmap costs little (a chunk is at least four times its members).  Before,
-// rows of similar length were merged by a wave (about 35 instructions and nine
-// lane exchanges per 64 entries of each row), shorter rows probed an LDS hash
-// table and the rest was searched: 22 ms in all for 2,500 updates at scale 22
-// (7e9 entries walked), 2.1 ms for 1,000 at scale 18 (1.3e8); now 6.3 + 0.3 ms
-// and 0.25 + 0.02 ms.  WORDS = 16384 (ids up to 2^19) lets two workgroups
-// share a CU.
+// What bounds it: the rows' loads.  At scale 22 3.7 TB/s come from beyond the
+// L2s (a copy reaches 4.7; one entry in ten hits the L2) and 74% of the wave
+// cycles wait; the VALU is 39% busy (17 instructions per 64 entries), the LDS
+// 13%.  At scale 18, where the rows stay in the caches, latency alone (79%
+// waiting).  The bitmap costs little: a chunk is at least four times its
+// members.  Before, rows of similar length were merged by a wave (about 35
+// instructions and nine lane exchanges per 64 entries of each row), shorter
+// rows probed an LDS hash table and the rest was searched: 22 ms in all for
+// 2,500 updates at scale 22 (5.9e9 entries walked), 2.1 ms for 1,000 at scale
+// 18 (1.2e8); now 6.4 ms and 0.6 for the searched pairs, 0.27 and 0.08.
+// WORDS = 16384 (ids up to 2^19) lets two workgroups share a CU.
 template <int WORDS>
 __global__ __launch_bounds__(C4B_T, WORDS <= 16384 ? 8 : 4) void k_delta_bits(DeltaArgs D) {
   __shared__ uint4 bm4[WORDS / 4];

@@ -154,18 +154,8 @@ __device__ __forceinline__ int32_t lower_bound_id(const uint32_t* row, int32_t n
   return lo;
 }
 
-// Largest i in [0, n) with pre[i] <= x (pre ascending, pre[0] <= x).
-__device__ __forceinline__ int64_t upper_bound_i64(const int64_t* pre, int64_t n, int64_t x) {
-  int64_t lo = 0, hi = n;
-  while (hi - lo > 1) {
-    int64_t mid = (lo + hi) >> 1;
-    if (pre[mid] <= x) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-// The same by an exponential search from i0 (pre[i0] <= x), for indexes that
-// lie close by.
+// Largest i in [0, n) with pre[i] <= x (pre ascending), by an exponential
+// search from i0 (pre[i0] <= x), for indexes that lie close by.
 __device__ __forceinline__ int64_t upper_bound_from(const int64_t* __restrict__ pre, int64_t n, int64_t i0, int64_t x) {
   int64_t lo = i0, step = 1;
   while (lo + step < n && pre[lo + step] <= x) { lo += step; step <<= 1; }
@@ -177,7 +167,8 @@ __device__ __forceinline__ int64_t upper_bound_from(const int64_t* __restrict__ 
   return lo;
 }
 
-// The same for one x per wave, the lanes together: 64 samples a round.
+// The same from 0 (pre[0] <= x) for one x per wave, the lanes together: 64
+// samples a round.
 __device__ __forceinline__ int64_t wave_upper_bound(const int64_t* __restrict__ pre, int64_t n, int64_t x) {
   int64_t lo = 0, hi = n;  // pre[lo] <= x, pre[hi] > x (or hi == n)
   while (hi - lo > 1) {

@@ -335,7 +335,9 @@ __global__ __launch_bounds__(SC_THREADS) void k_scan_down(const TIn* __restrict_
 }
 
 // The whole scan in one block, tile after tile: one launch instead of three
-// where the capacity is a few tiles (4 us against 3 x 3 to 4 us).
+// where the capacity is a few tiles (3 us for a few thousand entries, 8.4 on
+// average over the scans of up to 32,768 in a pass of 2,500 updates, against
+// three launches of 3 to 5 us and the gaps between them).
 constexpr int SO_ITEMS = 8;
 constexpr int64_t SO_MAX = 4 * SC_THREADS * SO_ITEMS;
 
