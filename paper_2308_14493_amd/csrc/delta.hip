@@ -289,21 +289,34 @@ constexpr int C4B_SMALL = 16384, C4B_LARGE = 36864;  // 32-bit words of the two 
 // 2,000,000 leaves listed 8e8 searched pairs (33 GB of lists, 179 ms; 3.3 now).
 // So an edge that leaves out more than C4B_OUT is walked in layers
 // (k_delta_layers) where its searches, at C4B_SEARCH walked entries each, cost
-// more than the walk and its share of C4B_FREE, or would list more than
-// C4B_OUT_MAX pairs or its share of C4B_OUT_ALL.  A few edges in layers are a
-// tail of long chunks: with every edge above C4B_OUT, 2,500 updates at scale
-// 22 took 13.8 ms a call instead of 8.6, with no C4B_FREE and half of
-// C4B_OUT_ALL 9.1.  No batch of 128 updates on ids that fit a bitmap leaves
-// out more than C4B_OUT: small passes do not launch the kernel of the layers.
+// more than the walk, or list more pairs than C4B_OUT_MAX or its share of what
+// the lists hold; but for the 4-cycles only in a batch whose searches together
+// cost more than C4B_FREE and a quarter of its walks, or list more pairs than
+// C4B_OUT_ALL and the walked ones, as a few edges in layers are a tail of long
+// chunks: with every edge above C4B_OUT, 2,500 updates at scale 22 took 13.8
+// ms a call instead of 8.6, and with the two limits by equal shares alone
+// 57,032 updates 220 ms instead of 179.  No batch of 128 updates on ids that
+// fit a bitmap leaves out more than C4B_OUT: small passes do not launch the
+// kernel of the layers.
 constexpr int32_t C4B_OUT = 128;
-constexpr int64_t C4B_SEARCH = 16, C4B_FREE = 1ll << 32, C4B_OUT_MAX = 16384, C4B_OUT_ALL = 1 << 25;
+constexpr int64_t C4B_SEARCH = 16, C4B_FREE = 1ll << 32, C4B_OUT_MAX = 16384, C4B_OUT_ALL = 1 << 22;
 
-// entries: those the searches would walk; cost: those the walk does; ne: changed edges
-__device__ __forceinline__ bool in_layers(const DeltaArgs& D, int64_t out, int64_t entries, int64_t cost, int64_t ne) {
-  if (D.c4_out > 0) return out > D.c4_out;
-  return out > C4B_OUT && (entries * C4B_SEARCH > cost + C4B_FREE / ne ||
-                           out > max((int64_t)C4B_OUT, min(C4B_OUT_MAX, C4B_OUT_ALL / ne)));
+// out members of an edge cost more to search (the entries that the searches
+// walk) than to walk the edge (cost) and its share of C4B_FREE among ne edges
+__device__ __forceinline__ bool search_dear(int64_t out, int64_t entries, int64_t cost, int64_t ne) {
+  return out > C4B_OUT && entries * C4B_SEARCH > cost + C4B_FREE / ne;
 }
+// What the batch says (k_delta_plan_fin's sums): the edges marked dear to
+// search, and those marked to list too many, are walked in layers.
+struct C4Layers {
+  bool dear, many;
+  __device__ __forceinline__ explicit C4Layers(const DeltaArgs& D)
+      : dear(ctr(D.dc, DC_OUT_WALK) * C4B_SEARCH > C4B_FREE + ctr(D.dc, DC_COST) / 4),
+        many(ctr(D.dc, DC_OUT) > C4B_OUT_ALL + D.pair_cap) {}
+  __device__ __forceinline__ bool operator()(int32_t side) const {
+    return (side & 4) || (dear && (side & 8)) || (many && (side & 16));
+  }
+};
 
 __device__ __forceinline__ int64_t pair_cost(int32_t al, int32_t ol) {
   return min((int64_t)al, C4B_RATIO * (int64_t)ol);
@@ -380,6 +393,7 @@ __global__ void k_delta_c4_plan(DeltaArgs D) {
 __global__ void k_delta_plan_fin(DeltaArgs D) {
   const int64_t ne = min(ctr(D.dc, DC_EDGES), D.ce_cap);
   const unsigned long long idmask = (1ull << D.bits) - 1ull;
+  int64_t outs = 0, walks = 0, costs = 0;  // of the edges with a bitmap
   for (int64_t i = gtid(); i < D.ce_cap; i += gstride()) {
     if (i >= ne) {
       D.c4_nch[i] = 0;
@@ -393,7 +407,7 @@ __global__ void k_delta_plan_fin(DeltaArgs D) {
     const bool bitmap = cost >= C4B_MIN;
     const uint32_t s = from_u ? u : v, o = from_u ? v : u;
     int32_t low = 0;  // N(o) below the window
-    bool layers = false;
+    int32_t layers = 0;
     if (bitmap) {
       const uint32_t base = c4b_base(D, o);
       const int64_t sl = D.P.len[s], flagged = (int64_t)D.na[o] + D.nr[o];
@@ -402,11 +416,27 @@ __global__ void k_delta_plan_fin(DeltaArgs D) {
         low = lower_bound_id(D.P.col + D.P.off[o], D.P.len[o], base);
         entries += low * min(sl, (int64_t)D.P.len[base - 1]);  // ids are a degree order
       }
-      layers = in_layers(D, low + flagged, entries, cost, ne);
+      const int64_t out = low + flagged, share = (C4B_OUT_ALL + D.pair_cap) / ne;
+      if (D.c4_out > 0)
+        layers = out > D.c4_out ? 4 : 0;
+      else
+        layers = (search_dear(out, entries, cost, ne) ? 8 : 0) |
+                 (out > max((int64_t)C4B_OUT, min(C4B_OUT_MAX, share)) ? 16 : 0);
+      outs += out;
+      walks += entries;
+      costs += cost;
     }
-    D.c4_side[i] = (from_u ? 0 : 1) | (bitmap ? 2 : 0) | (layers ? 4 : 0);
+    D.c4_side[i] = (from_u ? 0 : 1) | (bitmap ? 2 : 0) | layers;
     D.c4_low[i] = low;
     D.c4_nch[i] = D.P.len[s];
+  }
+  outs = wave_sum64(outs);
+  walks = wave_sum64(walks);
+  costs = wave_sum64(costs);
+  if (lane_id() == 0 && outs) {
+    atomicAdd(&D.dc[DC_OUT], (unsigned long long)outs);
+    atomicAdd(&D.dc[DC_OUT_WALK], (unsigned long long)walks);
+    atomicAdd(&D.dc[DC_COST], (unsigned long long)costs);
   }
 }
 
@@ -563,9 +593,10 @@ __global__ void k_delta_pairs(DeltaArgs D) {
     aff_append(D, n2, a, h2);
   }
   // the pairs (e, b), several waves per edge while there are fewer edges than waves
+  const C4Layers layers(D);
   const int32_t parts = (int32_t)max(ws / ne, (int64_t)1);
   for (int64_t i = w0 % ne, part = w0 / ne; i < ne && part < parts; i += ws) {
-    if ((D.c4_side[i] & 6) != 2) continue;  // no bitmap, or walked in layers
+    if (!(D.c4_side[i] & 2) || layers(D.c4_side[i])) continue;
     const unsigned long long K = D.ce[i] & DIR_KEY_MASK;
     const uint32_t u = (uint32_t)(K >> D.bits), v = (uint32_t)(K & idmask);
     const uint32_t s = (D.c4_side[i] & 1) ? v : u, o = s == u ? v : u;
@@ -590,7 +621,8 @@ __device__ __forceinline__ bool k4_walked(int32_t ns, int64_t kw) {
 }
 __device__ __forceinline__ bool k4_layers(const DeltaArgs& D, int64_t i) {
   const int64_t out = D.e_out[i];
-  return in_layers(D, out, out * D.e_ns[i], D.e_kw[i], ctr(D.dc, DC_EDGES));
+  if (D.c4_out > 0) return out > D.c4_out;
+  return search_dear(out, out * D.e_ns[i], D.e_kw[i], ctr(D.dc, DC_EDGES));
 }
 // members of S(e) (id | flags of both edges << 28) that its bitmap leaves out
 __device__ __forceinline__ bool k4_outside(uint32_t w, uint32_t base) { return (w & GC_FLAGS) || (w & GC_ID) < base; }
@@ -847,6 +879,7 @@ __global__ void k_delta_hitems(DeltaArgs D) {
   const bool fits = npairs <= D.pair_cap;  // else the pairs were not listed (count again)
   const int64_t total = fits ? D.pair_hoff[2 * npairs] : 0;
   const unsigned long long idmask = (1ull << D.bits) - 1ull;
+  const C4Layers layers(D);
   for (int64_t t = gtid(); t < D.tcap; t += gstride()) {
     int32_t n = 0;
     if (t < 2 * ne && fits) {
@@ -857,7 +890,7 @@ __global__ void k_delta_hitems(DeltaArgs D) {
         const unsigned long long K = D.ce[i] & DIR_KEY_MASK;
         const uint32_t o = (uint32_t)((D.c4_side[i] & 1) ? K >> D.bits : K & idmask);
         const int32_t nm = k4 ? D.e_ns[i] : D.P.len[o];
-        if (k4 ? k4_layers(D, i) : (D.c4_side[i] & 4) != 0) {
+        if (k4 ? k4_layers(D, i) : layers(D.c4_side[i])) {
           const int64_t T = layers_chunk(D, total, k4, nm, c4b_top(D, o));
           const unsigned long long at =
               atomicAdd(&D.dc[DC_LAY], (1ull << DC_LAY_SHIFT) | (unsigned long long)((h + T - 1) / T));

@@ -191,6 +191,9 @@ enum {
   DC_QH,         // queue of the walked chunks
   DC_LAY,        // edges walked in layers (above DC_LAY_SHIFT) and their chunks
   DC_QL,         // queue of those chunks
+  DC_OUT,        // members of N(o) that the bitmaps leave out
+  DC_OUT_WALK,   // entries that searching them walks, at most
+  DC_COST,       // entries walked against the bitmaps, or searched in their place
   DC_COUNT
 };
 constexpr int DC_LAY_SHIFT = 36;
@@ -226,7 +229,8 @@ struct DeltaArgs {
   int64_t ae_cap;
   unsigned long long* dc;             // [DC_COUNT] counters of the stage, zero on entry
   int32_t* c4_nch;                    // [ce_cap] pairs (e, a) per changed edge: degree of the end walked from
-  int32_t* c4_side;                   // [ce_cap] bit 0: walk from v instead of u; bit 1: against a bitmap; bit 2: in layers
+  int32_t* c4_side;                   // [ce_cap] bit 0: walk from v instead of u; bit 1: against a bitmap; bits 2 to 4: in
+                                      // layers (for certain; when searches are dear; when they list too many)
   int32_t* c4_low;                    // [ce_cap] entries of the other end's row below the bitmap's window
   uint32_t c4_ids;                    // ids a bitmap covers (0 or too many: launch_delta sets the most)
   int32_t c4_out;                     // > 0: an edge whose bitmap leaves out more members is walked in layers (tests)
