@@ -601,12 +601,18 @@ __device__ __forceinline__ void tri_large_probe(const CountArgs& A, const TriL<N
 // a word with at least K4_DENSE of its edges is not packed (row i and the
 // first word are then the same for every lane), and ONE version alone, the
 // usual case there, masks the words as they are read and keeps one sum.
-// Without these a count of the complete graph of 1,500 vertices with 20,000
-// of its edges in the batch took 87 ms instead of 74, of 3,000 vertices 2.05 s
-// instead of 1.71 (with a lane per bit throughout, 84 ms and 1.54 s).
+// MEM, the matrix in memory (the global tier): the waves meet once per row
+// each, as four waves that drift apart read 64 rows each, all that the vector
+// cache holds, and in step the same ones (6.4e9 instead of 6.0e10 reads of the
+// L2 for the complete graph of 3,000 vertices); and a dense word's lanes take
+// row i, the same for all, from registers.  Whole counts with 20,000 edges in
+// the batch, complete graphs of 1,500 and 3,000 vertices: a lane per bit
+// throughout 84 ms and 1.54 s, every word packed 87 ms and 2.05 s, dense words
+// by bit 74 ms and 1.74 s, waves in step 72 ms and 1.54 s, row i in registers
+// 67 ms and 1.33 s.  (With the matrix in LDS, registers took 4% longer.)
 constexpr int K4_DENSE = 48;
 
-template <int NV, bool DENSE, bool ONE>
+template <int NV, bool DENSE, bool MEM, bool ONE>
 __device__ __forceinline__ void k4_edges_(const TriL<NV>& S, int32_t dp, int nwaves, int vers, int64_t (&kv)[NV]) {
   const int w = threadIdx.x >> 6, l = lane_id();
   const int32_t W = S.W;
@@ -641,8 +647,10 @@ __device__ __forceinline__ void k4_edges_(const TriL<NV>& S, int32_t dp, int nwa
     const int32_t j = (int32_t)qj[k];
     edge((int32_t)qi[k], j, j >> 6);
   };
-  for (int32_t i = w; i < dp; i += nwaves) {
-    if (ONE && !bit_of(Pm, i)) continue;
+  // MEM: every wave takes as many turns, and a barrier in each
+  for (int32_t i = w; (MEM ? i - w : i) < dp; i += nwaves) {
+    if constexpr (MEM) __syncthreads();
+    if ((MEM && i >= dp) || (ONE && !bit_of(Pm, i))) continue;
     const unsigned long long* Ei = S.erow(i);
     for (int32_t w0 = i >> 6; w0 < W; ++w0) {
       const unsigned long long word = ONE ? Ei[w0] & Pm[w0] : Ei[w0];
@@ -650,7 +658,18 @@ __device__ __forceinline__ void k4_edges_(const TriL<NV>& S, int32_t dp, int nwa
       const uint64_t m = __ballot(in);
       if (!m) continue;
       if (DENSE && __popcll(m) >= K4_DENSE) {
-        if (in) edge(i, w0 * 64 + l, w0);
+        if constexpr (MEM && ONE) {
+          const unsigned long long* Ej = S.erow(in ? w0 * 64 + l : i);
+          uint32_t c = 0;
+          for (int32_t b = w0; b < W; b += 64) {
+            const int32_t words = min(64, W - b);
+            const int64_t ei = l < words ? (int64_t)(Ei[b + l] & Pm[b + l]) : 0;
+            for (int32_t k = 0; k < words; ++k) c += (uint32_t)__popcll((uint64_t)rdl64(ei, k) & Ej[b + k]);
+          }
+          one += in ? c : 0u;
+        } else if (in) {
+          edge(i, w0 * 64 + l, w0);
+        }
         continue;
       }
       if (in) {
@@ -675,13 +694,13 @@ __device__ __forceinline__ void k4_edges_(const TriL<NV>& S, int32_t dp, int nwa
   }
 }
 
-template <int NV, bool DENSE>
+template <int NV, bool DENSE, bool MEM>
 __device__ __forceinline__ void k4_edges(const TriL<NV>& S, int32_t dp, int nwaves, int vers, int64_t (&kv)[NV]) {
-  if (DENSE && (vers & (vers - 1)) == 0) k4_edges_<NV, DENSE, true>(S, dp, nwaves, vers, kv);
-  else k4_edges_<NV, DENSE, false>(S, dp, nwaves, vers, kv);
+  if (DENSE && (vers & (vers - 1)) == 0) k4_edges_<NV, DENSE, MEM, true>(S, dp, nwaves, vers, kv);
+  else k4_edges_<NV, DENSE, MEM, false>(S, dp, nwaves, vers, kv);
 }
 
-template <int NV, bool DENSE>
+template <int NV, bool DENSE, bool MEM>
 __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t ub, int32_t dp,
                                  int64_t (&kacc)[NV], int64_t& ent) {
   const RegionDev& R = A.R;
@@ -741,7 +760,7 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
     for (int x = 0; x < NV; ++x) {
       flip(x, true);
       __syncthreads();
-      k4_edges<NV, DENSE>(S, dp, nwaves, 1 << x, kacc);
+      k4_edges<NV, DENSE, MEM>(S, dp, nwaves, 1 << x, kacc);
       __syncthreads();
       if (x < NV - 1) flip(x, false);
     }
@@ -761,7 +780,7 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
       }
       if (same[x] == x) vers |= 1 << x;
     }
-    k4_edges<NV, DENSE>(S, dp, nwaves, vers, kv);
+    k4_edges<NV, DENSE, MEM>(S, dp, nwaves, vers, kv);
 #pragma unroll
     for (int x = 1; x < NV; ++x)
 #pragma unroll
@@ -839,7 +858,7 @@ __device__ void tri_large_vertex(const CountArgs& A, const TriL<NV>& S, int64_t 
       __syncthreads();
       for (int32_t g0 = w; g0 < dp; g0 += nwaves * 64) tri_large_probe<NV>(A, S, hmask, shift, g0, nwaves, dp, x + 1, ent);
       __syncthreads();
-      k4_edges<NV, DENSE>(S, dp, nwaves, 1 << x, kacc);
+      k4_edges<NV, DENSE, MEM>(S, dp, nwaves, 1 << x, kacc);
     }
   }
   __syncthreads();
@@ -974,7 +993,7 @@ __global__ __launch_bounds__(THREADS, CAP == 0 || CAP > 256 ? 4 : (NV == 2 ? 6 :
       S.hval = lds ? tval : gval;
       S.hcap = lds ? TG_HASH : ghc;
     }
-    tri_large_vertex<NV, (CAP == 0 || CAP > 512)>(A, S, ub, dp, kacc, ent);
+    tri_large_vertex<NV, (CAP == 0 || CAP > 512), CAP == 0>(A, S, ub, dp, kacc, ent);
   }
   if (cur_g >= 0) flushv<NV>(A.sig, cur_g, SG_K4, kacc);
   ent = wave_sum64(ent);

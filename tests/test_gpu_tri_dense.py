@@ -58,3 +58,19 @@ def test_global_tier_hash(k):
         keep[::50] = False
         assert got == native.static_counts(n, np.concatenate([s[keep], np.zeros(k, np.int32)]),
                                            np.concatenate([d[keep], star]))
+
+
+@pytest.mark.parametrize("k", [4094, 4097, 4230])
+def test_dense_rows_of_many_words(k):
+    """Rows of the bit matrix of 64 words and of more: 150 vertices of the lowest
+    ranks (no edges at the build) joined to all, but for one pair in 50."""
+    from paper_2308_14493_amd.graphlet4 import Graph
+    print("case dense rows of many words", k, flush=True)
+    n, rng = k + 1, np.random.default_rng(k)
+    s, d = np.nonzero(np.triu(rng.random((150, n)) < 0.98, 1))
+    s, d = s.astype(np.int32), d.astype(np.int32)
+    q = rng.permutation(s.size)[:3]
+    some = np.isin(np.arange(s.size), q)
+    with Graph(n, Z, Z, delta=-1, radius=0) as g:
+        assert g.apply_batch(s, d, Z, Z) == native.static_counts(n, s, d)
+        assert g.apply_batch(Z, Z, s[some], d[some]) == native.static_counts(n, s[~some], d[~some])
